@@ -535,7 +535,9 @@ S2D_API int near_wall_features_eval(const s2d_curves *walls, const s2d_targets *
                                     double *frame, void *stream);
 
 /* Delta = D_P - D_1 of the wall double layer (Section 2.1 Eq. (D)) summed over
- * images img_lo..img_hi, at free targets (trg->on_curve must be NULL), FP64:
+ * images img_lo..img_hi, at free targets (trg->on_curve must be NULL), FP64
+ * (both sums by near nodes term by term and far clusters through expansions
+ * truncated below 1e-17, where their sizes favour it):
  * du, dv ([trg->n] device) are written, or Delta is added to them when
  * accumulate != 0 (so a caller adds it to the plain double layer it holds).
  * method (s2d_near_method as for near_correct_eval):

@@ -3,6 +3,7 @@
 // all scratch lives in the caller's workspace.
 #include "lu_plan.h"
 #include "s2d_cell.h"
+#include "s2d_far.h"
 #include "s2d_internal.h"
 #include "s2d_near.h"
 #include "../../include/stokes2d_vesicle.h"
@@ -123,6 +124,58 @@ int hip_fail(hipError_t e, const char *what) {
     return fail(S2D_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// The final step's arguments of an evaluation, the partial and self sums
+// (part, self, n_parts) left to the caller.
+s2d::FinalArgs final_args(int op, const s2d_curves *src, const s2d_targets *trg, bool img0, double mu, double *u,
+                          double *v, int accumulate) {
+    s2d::FinalArgs f{};
+    f.n_trg = trg->n;
+    f.n_src = src->n_nodes;
+    switch (op) {
+    case S2D_OP_SLP: f.pref = 1.0 / (4.0 * M_PI * mu); break;             // Eq. (S)
+    case S2D_OP_DLP: f.pref = 1.0 / M_PI; break;                          // Eq. (D)
+    case S2D_OP_SLP_PRESSURE: f.pref = 1.0 / (2.0 * M_PI); break;         // Eq. (Q)
+    case S2D_OP_DLP_PRESSURE: f.pref = mu / M_PI; break;                  // Eq. (P)
+    default: f.pref = -1.0 / M_PI; break;                                 // Eq. (K)
+    }
+    f.accumulate = accumulate ? 1 : 0;
+    f.ncomp = (op == S2D_OP_SLP_PRESSURE || op == S2D_OP_DLP_PRESSURE) ? 1 : 2;
+    f.u = u;
+    f.v = v;
+    // on-curve targets with an empty or inconsistent curve come out NaN
+    f.dlp_diag = op == S2D_OP_DLP && trg->on_curve != nullptr && img0;
+    f.on_curve = trg->on_curve;
+    f.on_node = trg->on_node;
+    f.curve_off = src->curve_off;
+    f.n_curves = src->n_curves;
+    f.nx = src->nx;
+    f.ny = src->ny;
+    f.w = src->w;
+    f.kappa = src->kappa;
+    f.fx = src->fx;
+    f.fy = src->fy;
+    return f;
+}
+
+// Event pair around the sums of one evaluation while profiling is on.
+ProfEvent prof_begin(int op, bool on, hipStream_t st) {
+    ProfEvent pe{op, nullptr, nullptr};
+    if (!g_prof_on || !on) return pe;
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (hipEventCreate(&pe.a) == hipSuccess && hipEventCreate(&pe.b) == hipSuccess)
+        hipEventRecord(pe.a, st);
+    else
+        pe.a = pe.b = nullptr;
+    return pe;
+}
+
+void prof_end(const ProfEvent &pe, hipStream_t st) {
+    if (!pe.a) return;
+    hipEventRecord(pe.b, st);
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_prof.push_back(pe);
+}
+
 int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
          int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
          void *stream, const double *tnx = nullptr, const double *tny = nullptr, bool may_profile = true) {
@@ -184,52 +237,15 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
     a.tnx = tnx;
     a.tny = tny;
     a.rec64 = (char *)ws + p.off_rec64;
-    FinalArgs f{};
+    FinalArgs f = final_args(op, src, trg, img0, mu, u, v, accumulate);
     f.part = a.part;
     f.self = p.self ? (const double *)((char *)ws + p.off_self) : nullptr;
     f.n_parts = p.n_blocks > 0 ? p.n_groups : 0;
-    f.n_trg = p.n_trg;
-    f.n_src = p.n_src;
-    switch (op) {
-    case S2D_OP_SLP: f.pref = 1.0 / (4.0 * M_PI * mu); break;             // Eq. (S)
-    case S2D_OP_DLP: f.pref = 1.0 / M_PI; break;                          // Eq. (D)
-    case S2D_OP_SLP_PRESSURE: f.pref = 1.0 / (2.0 * M_PI); break;         // Eq. (Q)
-    case S2D_OP_DLP_PRESSURE: f.pref = mu / M_PI; break;                  // Eq. (P)
-    default: f.pref = -1.0 / M_PI; break;                                 // Eq. (K)
-    }
-    f.accumulate = accumulate ? 1 : 0;
-    f.ncomp = ncomp;
-    f.u = u;
-    f.v = v;
-    // on-curve targets with an empty or inconsistent curve come out NaN
-    f.dlp_diag = op == S2D_OP_DLP && trg->on_curve != nullptr && img0;
-    f.on_curve = trg->on_curve;
-    f.on_node = trg->on_node;
-    f.curve_off = src->curve_off;
-    f.n_curves = src->n_curves;
-    f.nx = src->nx;
-    f.ny = src->ny;
-    f.w = src->w;
-    f.kappa = src->kappa;
-    f.fx = src->fx;
-    f.fy = src->fy;
     if (p.n_blocks > 0) {
-        ProfEvent pe{op, nullptr, nullptr};
-        if (g_prof_on && may_profile) {
-            std::lock_guard<std::mutex> lk(g_mu);
-            if (hipEventCreate(&pe.a) == hipSuccess && hipEventCreate(&pe.b) == hipSuccess) {
-                hipEventRecord(pe.a, st);
-            } else {
-                pe.a = pe.b = nullptr;
-            }
-        }
+        const ProfEvent pe = prof_begin(op, may_profile, st);
         e = launch_pair(p, a, f, st);
         if (e != hipSuccess) return hip_fail(e, "pair launch");
-        if (pe.a) {
-            hipEventRecord(pe.b, st);
-            std::lock_guard<std::mutex> lk(g_mu);
-            g_prof.push_back(pe);
-        }
+        prof_end(pe, st);
     }
     // the pair kernel finishes the targets itself when it has one split group
     if (p.n_blocks > 0 && p.n_groups == 1) return S2D_OK;
@@ -241,6 +257,41 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
 }  // namespace
 
 namespace s2d {
+
+size_t layer_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg) {
+    const size_t direct = stokes2d_workspace_size(op, mode, src, trg);
+    if (direct == 0 || !far_worth(src->n_nodes, trg->n, false)) return direct;
+    return std::max(direct, far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr).total);
+}
+
+int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
+               int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
+               void *stream, bool *ready) {
+    const bool far = trg && src && (op == S2D_OP_SLP || op == S2D_OP_DLP) &&
+                     far_worth(src->n_nodes, trg->n, ready != nullptr);
+    const FarLayout L = far ? far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr) : FarLayout{};
+    if (!far || !ws || ws_bytes < L.total)
+        return eval(op, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream);
+    int rc = check_args(op, mode, src, trg, d, img_lo, img_hi, mu);
+    if (rc != S2D_OK) return rc;
+    if (!u || !v) return fail(S2D_EINVAL, "output arrays must not be NULL");
+    int dev = 0;
+    rc = current_device(&dev);
+    if (rc != S2D_OK) return rc;
+    if (((uintptr_t)ws & 255) != 0) return fail(S2D_EWORKSPACE, "workspace must be 256-byte aligned");
+    hipStream_t st = (hipStream_t)stream;
+    hipError_t e = hipSuccess;
+    if (!ready || !*ready) e = far_setup(op, L, src, trg, ws, st);
+    if (e != hipSuccess) return hip_fail(e, "far-field set-up");
+    if (ready) *ready = true;
+    const ProfEvent pe = prof_begin(op, true, st);
+    const bool img0 = img_lo <= 0 && img_hi >= 0;
+    e = far_sum(op, L, src, trg, d, img_lo, img_hi, final_args(op, src, trg, img0, mu, u, v, accumulate), ws, st);
+    if (e != hipSuccess) return hip_fail(e, "far-field sum");
+    prof_end(pe, st);
+    return S2D_OK;
+}
+
 int set_error(int code, const std::string &msg) { return fail(code, msg); }
 int device_ready(int *dev) { return current_device(dev); }
 }  // namespace s2d
@@ -448,7 +499,7 @@ S2D_API int stokes2d_cell_solve(const s2d_cell *cell, const double *v, const dou
 namespace {
 
 struct RespLayout {
-    size_t v, g, tau, c, vw, side, s, tauxy, cxy, prox, poff, geo, eval, eval_bytes, total;
+    size_t v, g, tau, c, vw, side, s, tauxy, cxy, prox, poff, geo, eval, need, total;
 };
 
 RespLayout resp_layout(const s2d_cell *cell, int64_t n, int32_t nc, int mode) {
@@ -497,9 +548,10 @@ RespLayout resp_layout(const s2d_cell *cell, int64_t n, int32_t nc, int mode) {
     e = std::max(e, stokes2d_workspace_size(S2D_OP_DLP, mode, &wal, &tv));
     e = std::max(e, stokes2d_workspace_size(S2D_OP_SLP, mode, &prx, &tv));
     L.eval = o;
-    L.eval_bytes = e;
-    o += align256(e);
-    L.total = o;
+    L.need = o + align256(e);      // the least a call needs; L.total holds the far-field sums too
+    e = std::max(e, s2d::layer_workspace(S2D_OP_SLP, mode, &ves, &tw));
+    e = std::max(e, s2d::layer_workspace(S2D_OP_DLP, mode, &wal, &tv));
+    L.total = o + align256(e);
     return L;
 }
 
@@ -531,8 +583,8 @@ S2D_API int ves_channel_response(const s2d_cell *cell, void *cell_ws, size_t cel
     rc = current_device(&dev);
     if (rc != S2D_OK) return rc;
     const RespLayout L = resp_layout(cell, n_nodes, n_curves, mode);
-    if (!ws || ws_bytes < L.total)
-        return fail(S2D_EWORKSPACE, "response workspace too small: need " + std::to_string(L.total) + " bytes");
+    if (!ws || ws_bytes < L.need)
+        return fail(S2D_EWORKSPACE, "response workspace too small: need " + std::to_string(L.need) + " bytes");
     if (((uintptr_t)ws & 255) != 0) return fail(S2D_EWORKSPACE, "workspace must be 256-byte aligned");
     if (n_nodes == 0) return S2D_OK;
     char *b = (char *)ws;
@@ -541,7 +593,7 @@ S2D_API int ves_channel_response(const s2d_cell *cell, void *cell_ws, size_t cel
     const int K = cell->n_side, M = cell->n_proxy;
     const double d = cell->d, mu = cell->mu;
     void *ew = b + L.eval;
-    const size_t eb = L.eval_bytes;
+    const size_t eb = ws_bytes - L.eval;
     // the vesicles as single-layer sources of f
     double *geo = (double *)(b + L.geo);
     rc = ves_geometry(n, n_curves, curve_off, x, y, nullptr, geo, geo + n, geo + 2 * n, nullptr, nullptr, stream);
@@ -550,7 +602,7 @@ S2D_API int ves_channel_response(const s2d_cell *cell, void *cell_ws, size_t cel
     // step 3: -S^near f on the walls; S and T of the single far images at R and L
     double *vw = (double *)(b + L.vw);
     const s2d_targets tw{nw, cell->walls.x, cell->walls.y, nullptr, nullptr};
-    rc = eval(S2D_OP_SLP, mode, &ves, &tw, d, -1, 1, mu, vw, vw + nw, 0, ew, eb, stream);
+    rc = layer_eval(S2D_OP_SLP, mode, &ves, &tw, d, -1, 1, mu, vw, vw + nw, 0, ew, eb, stream);
     if (rc != S2D_OK) return rc;
     double *side = (double *)(b + L.side), *sxl = side, *sxr = side + K, *mx = side + 2 * K, *my = side + 3 * K;
     hipError_t e = resp_side_launch(K, cell->side_y, cell->x_left, d, sxl, sxr, mx, my, st);
@@ -584,8 +636,8 @@ S2D_API int ves_channel_response(const s2d_cell *cell, void *cell_ws, size_t cel
     wal.fx = tx;
     wal.fy = ty;
     const s2d_targets tv{n, x, y, nullptr, nullptr};
-    if ((rc = eval(S2D_OP_DLP, mode, &wal, &tv, d, -1, 1, 1.0, u_resp_x, u_resp_y, 0, ew, eb, stream)) != S2D_OK)
-        return rc;
+    rc = layer_eval(S2D_OP_DLP, mode, &wal, &tv, d, -1, 1, 1.0, u_resp_x, u_resp_y, 0, ew, eb, stream);
+    if (rc != S2D_OK) return rc;
     const s2d_curves prx{(int64_t)M, 1, poff, px, py, nullptr, nullptr, pw, nullptr, cx, cy};
     return eval(S2D_OP_SLP, mode, &prx, &tv, d, 0, 0, mu, u_resp_x, u_resp_y, 1, ew, eb, stream);
 }
@@ -1105,7 +1157,7 @@ s2d::WallArgs wall_args(const s2d_curves *w, double d, int P, void *scratch, dou
 // the fallback list (MLP, AUTO), pair sums
 struct NearWallLayout {
     WallLayout up;
-    size_t t4, dtab, dscr, X, nrec, flag, list, count, llist, lcount, cxy, pair, pair_bytes, total;
+    size_t t4, dtab, dscr, X, nrec, flag, list, count, llist, lcount, cxy, pair, need, total;
 };
 
 NearWallLayout near_wall_layout(int method, const s2d_curves *w, const s2d_targets *t, int P,
@@ -1145,7 +1197,7 @@ NearWallLayout near_wall_layout(int method, const s2d_curves *w, const s2d_targe
     f.n_nodes = (int64_t)P * w->n_nodes;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDev && g_dev[dev].init) cus = g_dev[dev].cus;
-    size_t pb = 256;
+    size_t pb = 256, fb = 0;      // direct plans (the least a call needs) and the far-field sums
     if (method == S2D_NEAR_UPSAMPLE) {
         pb = std::max(pb, s2d::make_plan(S2D_OP_DLP, S2D_FP64, &f, t, cus).total);
         pb = std::max(pb, s2d::make_plan(S2D_OP_DLP, S2D_FP64, w, t, cus).total);
@@ -1161,9 +1213,14 @@ NearWallLayout near_wall_layout(int method, const s2d_curves *w, const s2d_targe
             pb = std::max(pb, s2d::make_plan(S2D_OP_DLP, S2D_FP64, w, &tm, cus).total);
         }
     }
+    // layouts grow with the target count, so the full one covers AUTO's lists
+    if (method != S2D_NEAR_MLP)
+        for (const s2d_curves *c : {(const s2d_curves *)&f, w})
+            if (s2d::far_worth(c->n_nodes, t->n, false))
+                fb = std::max(fb, s2d::far_layout(S2D_OP_DLP, c->n_nodes, t->n, false).total);
     L.pair = o;
-    L.pair_bytes = pb;
-    L.total = o + align256(pb);
+    L.need = o + align256(pb);
+    L.total = o + align256(std::max(pb, fb));
     if (fine_shape) *fine_shape = f;
     return L;
 }
@@ -1248,8 +1305,9 @@ S2D_API int near_wall_correct_eval(int method, const s2d_curves *walls, const s2
     if (trg->n == 0) return S2D_OK;
     s2d_curves fine{};
     const NearWallLayout L = near_wall_layout(method, walls, trg, upsample, &fine);
-    if (!ws || ws_bytes < L.total)
-        return fail(S2D_EWORKSPACE, "near-wall workspace too small: need " + std::to_string(L.total) + " bytes");
+    if (!ws || ws_bytes < L.need)
+        return fail(S2D_EWORKSPACE, "near-wall workspace too small: need " + std::to_string(L.need) + " bytes");
+    const size_t pair_bytes = ws_bytes - L.pair;
     if (((uintptr_t)ws & 255) != 0) return fail(S2D_EWORKSPACE, "workspace must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     char *base = (char *)ws;
@@ -1259,7 +1317,7 @@ S2D_API int near_wall_correct_eval(int method, const s2d_curves *walls, const s2
     if (walls->n_nodes == 0) {
         // no wall: the correction is zero
         return eval(S2D_OP_DLP, S2D_FP64, walls, trg, d, img_lo, img_hi, 1.0, du, dv, accumulate,
-                    base + L.pair, L.pair_bytes, stream);
+                    base + L.pair, pair_bytes, stream);
     }
     // the refined walls (UPSAMPLE; AUTO when some target falls back)
     const auto refine = [&]() -> int {
@@ -1283,11 +1341,11 @@ S2D_API int near_wall_correct_eval(int method, const s2d_curves *walls, const s2
     };
     if (method == S2D_NEAR_UPSAMPLE) {
         if ((rc = refine()) != S2D_OK) return rc;
-        rc = eval(S2D_OP_DLP, S2D_FP64, &fine, trg, d, img_lo, img_hi, 1.0, t4, t4 + n, 0, base + L.pair,
-                  L.pair_bytes, stream);
+        rc = s2d::layer_eval(S2D_OP_DLP, S2D_FP64, &fine, trg, d, img_lo, img_hi, 1.0, t4, t4 + n, 0, base + L.pair,
+                  pair_bytes, stream);
         if (rc != S2D_OK) return rc;
-        rc = eval(S2D_OP_DLP, S2D_FP64, walls, trg, d, img_lo, img_hi, 1.0, t4 + 2 * n, t4 + 3 * n, 0,
-                  base + L.pair, L.pair_bytes, stream);
+        rc = s2d::layer_eval(S2D_OP_DLP, S2D_FP64, walls, trg, d, img_lo, img_hi, 1.0, t4 + 2 * n, t4 + 3 * n, 0,
+                  base + L.pair, pair_bytes, stream);
         if (rc != S2D_OK) return rc;
         e = s2d::delta_combine_launch(n, accumulate, du, dv, t4, st);
         return e == hipSuccess ? S2D_OK : hip_fail(e, "near-wall combine launch");
@@ -1332,11 +1390,11 @@ S2D_API int near_wall_correct_eval(int method, const s2d_curves *walls, const s2
             static_assert(s2d::kNetRec * sizeof(float) >= 4 * sizeof(double), "four doubles per target fit");
             double *f4 = (double *)(base + L.nrec);
             const s2d_targets tl{m, cx, cy, nullptr, nullptr};
-            rc = eval(S2D_OP_DLP, S2D_FP64, &fine, &tl, d, img_lo, img_hi, 1.0, f4, f4 + m, 0, base + L.pair,
-                      L.pair_bytes, stream);
+            rc = s2d::layer_eval(S2D_OP_DLP, S2D_FP64, &fine, &tl, d, img_lo, img_hi, 1.0, f4, f4 + m, 0, base + L.pair,
+                      pair_bytes, stream);
             if (rc != S2D_OK) return rc;
-            rc = eval(S2D_OP_DLP, S2D_FP64, walls, &tl, d, img_lo, img_hi, 1.0, f4 + 2 * m, f4 + 3 * m, 0,
-                      base + L.pair, L.pair_bytes, stream);
+            rc = s2d::layer_eval(S2D_OP_DLP, S2D_FP64, walls, &tl, d, img_lo, img_hi, 1.0, f4 + 2 * m, f4 + 3 * m, 0,
+                      base + L.pair, pair_bytes, stream);
             if (rc != S2D_OK) return rc;
             e = s2d::fallback_scatter_launch(m, list, f4, tu, tv, st);
             if (e != hipSuccess) return hip_fail(e, "near-wall fallback scatter");

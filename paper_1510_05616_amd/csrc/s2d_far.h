@@ -1,0 +1,40 @@
+// Far-field summation (far.hip): the layer sums of eval() by near tiles taken
+// term by term and far clusters through truncated expansions, all in FP64.
+// Used by the composite entry points (time step, channel response, wall
+// correction), whose sums are large and repeated.
+#pragma once
+#include "s2d_internal.h"
+
+namespace s2d {
+
+// Sizes and workspace carve-up of one (sources, targets) pair; op S2D_OP_SLP
+// or S2D_OP_DLP.
+struct FarLayout {
+    int64_t ns, nt;            // sources, targets
+    int64_t n0, n1, n2, nT;    // source nodes of the three levels, target circles
+    int groups;                // near workgroups per target circle
+    int64_t nblk;              // sort blocks
+    size_t key[2], idx[2], hist, base, box, spos, node, tnode, txy, rec, coef, part, kress, self;
+    size_t total;
+};
+
+FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve);
+
+// Whether the far-field sum is the faster route for these sizes; reuse: one
+// set-up serves several densities.
+bool far_worth(int64_t ns, int64_t nt, bool reuse);
+
+// Orders sources and targets along a space-filling curve and boxes their
+// tiles; with Kress's tables when the single layer's targets sit on curves.
+// Depends on the coordinates and curve_off only: one set-up serves any number
+// of densities.
+hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *src, const s2d_targets *trg, void *ws,
+                     hipStream_t st);
+
+// The sum over images img_lo..img_hi for the densities in src, finished and
+// written (or added) as `f` says (FinalArgs of the same operator; self and
+// part are set here).
+hipError_t far_sum(int op, const FarLayout &L, const s2d_curves *src, const s2d_targets *trg, double d,
+                   int32_t img_lo, int32_t img_hi, FinalArgs f, void *ws, hipStream_t st);
+
+}  // namespace s2d

@@ -14,6 +14,7 @@
 // fixed order (reproducible bit for bit), the small Hessenberg least-squares
 // problem by Givens rotations on the host.
 #include "self_impl.h"
+#include "s2d_far.h"
 #include "s2d_near.h"
 #include "../../include/stokes2d_vesicle.h"
 
@@ -866,7 +867,9 @@ struct StepLayout {
     // offsets, the near pairs (node, curve, shifted coordinates, corrections),
     // the upsampled records
     size_t nbox, ncnt, npos, pnode, pcurve, px, py, pdu, pdv, up;
-    size_t total;
+    // the single layer's far-field sum, last: `need` is what a call cannot do
+    // without, `total` holds this region too
+    size_t need, far, far_bytes, total;
 };
 
 s2d_curves ves_curves(int64_t n, int32_t nc, const int32_t *off, const double *x, const double *y) {
@@ -975,6 +978,12 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
         L.up = o;
         o += al256(4 * ((size_t)p->near_P + 1) * (size_t)n * d);
     }
+    L.need = o;
+    L.far = o;
+    if (far_worth(n, n, true)) {
+        L.far_bytes = far_layout(S2D_OP_SLP, n, n, true).total;
+        o += al256(L.far_bytes);
+    }
     L.total = o;
     return L;
 }
@@ -995,6 +1004,7 @@ struct StepCtx {
     bool pc;
     rocblas_handle h;        // set while the preconditioner is in use (blas_mutex held)
     int64_t nm;              // near pairs (close evaluation)
+    bool far, far_ready;     // the single layer by the far-field sum; its geometry is set up
 };
 
 int ves_fail(int code, const std::string &m) { return set_error(code, m); }
@@ -1051,8 +1061,8 @@ int setup_ctx(StepCtx &C, int64_t n, int32_t nc, const int32_t *off, const doubl
     C.y = y;
     C.p = p;
     C.L = step_layout(n, nc, p);
-    if (!ws || ws_bytes < C.L.total)
-        return ves_fail(S2D_EWORKSPACE, "vesicle step workspace too small: need " + std::to_string(C.L.total));
+    if (!ws || ws_bytes < C.L.need)
+        return ves_fail(S2D_EWORKSPACE, "vesicle step workspace too small: need " + std::to_string(C.L.need));
     if (((uintptr_t)ws & 255) != 0) return ves_fail(S2D_EWORKSPACE, "workspace must be 256-byte aligned");
     C.ws = (char *)ws;
     C.st = (hipStream_t)stream;
@@ -1076,6 +1086,8 @@ int setup_ctx(StepCtx &C, int64_t n, int32_t nc, const int32_t *off, const doubl
     C.trg.y = y;
     C.trg.on_curve = oc;
     C.trg.on_node = on;
+    C.far = C.L.far_bytes > 0 && ws_bytes >= C.L.total;
+    C.far_ready = false;
     C.nm = 0;
     if (p->near && n > 0) {
         char *b = C.ws;
@@ -1134,8 +1146,13 @@ int apply(StepCtx &C, const double *z, double *out, int mode) {
     hipLaunchKernelGGL(ves_op_kernel<RHS>, dim3(C.nc), dim3(kVesBlock), 0, C.st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hipf(e, "vesicle operator launch");
-    S2D_TRY(stokes2d_slp_eval(mode, &C.src, &C.trg, C.p->d, C.p->img_lo, C.p->img_hi, C.p->mu, out, out + C.n, 1,
-                              C.ws + C.L.slp, C.L.slp_bytes, C.st));
+    if (C.far)
+        // one geometry for every density of the solve: ordered and boxed once
+        S2D_TRY(layer_eval(S2D_OP_SLP, mode, &C.src, &C.trg, C.p->d, C.p->img_lo, C.p->img_hi, C.p->mu, out,
+                           out + C.n, 1, C.ws + C.L.far, C.L.far_bytes, C.st, &C.far_ready));
+    else
+        S2D_TRY(stokes2d_slp_eval(mode, &C.src, &C.trg, C.p->d, C.p->img_lo, C.p->img_hi, C.p->mu, out, out + C.n, 1,
+                                  C.ws + C.L.slp, C.L.slp_bytes, C.st));
     if (C.nm > 0) {
         // close evaluation: the upsampled records of every vesicle's layer
         // for this density, the corrections at the near pairs, summed per node
