@@ -34,6 +34,15 @@
  *   - signed curvature kappa = -(x'' . n) / |x'|^2 (positive on a convex curve
  *     with outward normal);  normals are taken as given.
  *
+ * Large sums.  A velocity sum (single or double layer) with at least 2^26
+ * (source, target) pairs, 4,096 sources and 1,024 targets takes the far-field
+ * route, in FP64 in either mode: sources and targets are sorted along a
+ * space-filling curve, near nodes are summed term by term and well separated
+ * clusters through expansions truncated below 1e-17 of their terms, in a fixed
+ * order.  It needs the workspace stokes2d_workspace_size() gives (about 100
+ * bytes per source node and 70 per target); with a smaller one that still
+ * holds the direct sum, the call sums directly in its mode's arithmetic.
+ *
  * Memory and ownership.  Every array argument is a DEVICE pointer to
  * caller-owned memory, structure-of-arrays, FP64 (int32 for indices), in
  * every mode; the mode selects only the internal arithmetic.  The library
@@ -73,8 +82,8 @@ typedef enum {
 } s2d_status;
 
 typedef enum {
-    S2D_FP64 = 0,         /* every pair term in FP64 */
-    S2D_FP32C = 1         /* pair terms in FP32, exact FP64 coordinate differences,
+    S2D_FP64 = 0,         /* every term in FP64 */
+    S2D_FP32C = 1         /* direct pair terms in FP32, exact FP64 coordinate differences,
                              FP32 sub-blocks merged into FP64 accumulators; the own-curve
                              Kress quadrature and the diagonal limit stay FP64 */
 } s2d_mode;
@@ -137,12 +146,13 @@ S2D_API int stokes2d_slp_eval(int mode, const s2d_curves *src, const s2d_targets
  * hipMalloc): no workspace argument; the scratch lives in a device array
  * inside the library, S2D_NOALLOC_SCRATCH_BYTES (32 MiB) per device, set up
  * by stokes2d_init and held until the process ends.  The call allocates
- * nothing and returns S2D_EWORKSPACE, launching nothing, when the problem
- * needs more scratch than that, i.e. when stokes2d_workspace_size(S2D_OP_SLP,
- * ...) exceeds S2D_NOALLOC_SCRATCH_BYTES (about 34 bytes per source node,
- * 8 more with on-curve targets, plus 16 per on-curve target: the 128k-node
- * channel needs about 6 MB; a million source nodes do not fit).
- * The result equals stokes2d_slp_eval's bit for bit.  Every call on one device
+ * nothing and returns S2D_EWORKSPACE, launching nothing, when the direct sum
+ * needs more scratch than that (about 34 bytes per source node, 8 more with
+ * on-curve targets, plus 16 per on-curve target; a million source nodes do not
+ * fit).  Large sums take the far-field route where its scratch fits too (the
+ * 128k-node channel: 20 MB) and the direct one otherwise; where both entry
+ * points take the same route, the result equals stokes2d_slp_eval's bit for bit.
+ * Every call on one device
  * shares that device's scratch: calls that overlap on one device (several
  * streams, several host threads) race and must be serialised by the caller.
  * Nothing in the scratch needs to start at zero; each call overwrites what

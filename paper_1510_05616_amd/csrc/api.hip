@@ -258,20 +258,30 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
 
 namespace s2d {
 
+size_t direct_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg) {
+    if (check_args(op, mode, src, trg, 1.0, 0, 0, 1.0) != S2D_OK) return 0;
+    int dev = 0;
+    int cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDev && g_dev[dev].init) cus = g_dev[dev].cus;
+    const Plan p = make_plan(op, mode, src, trg, cus);
+    return p.total > 0 ? p.total : 256;
+}
+
 size_t layer_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg) {
-    const size_t direct = stokes2d_workspace_size(op, mode, src, trg);
-    if (direct == 0 || !far_worth(src->n_nodes, trg->n, false)) return direct;
+    const size_t direct = direct_workspace(op, mode, src, trg);
+    if (direct == 0 || op > S2D_OP_DLP || !far_worth(src->n_nodes, trg->n)) return direct;
     return std::max(direct, far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr).total);
 }
 
 int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
                int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
-               void *stream, bool *ready) {
+               void *stream, bool *ready, bool may_profile) {
     const bool far = trg && src && (op == S2D_OP_SLP || op == S2D_OP_DLP) &&
-                     far_worth(src->n_nodes, trg->n, ready != nullptr);
+                     far_worth(src->n_nodes, trg->n);
     const FarLayout L = far ? far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr) : FarLayout{};
     if (!far || !ws || ws_bytes < L.total)
-        return eval(op, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream);
+        return eval(op, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream, nullptr,
+                    nullptr, may_profile);
     int rc = check_args(op, mode, src, trg, d, img_lo, img_hi, mu);
     if (rc != S2D_OK) return rc;
     if (!u || !v) return fail(S2D_EINVAL, "output arrays must not be NULL");
@@ -284,7 +294,7 @@ int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, 
     if (!ready || !*ready) e = far_setup(op, L, src, trg, ws, st);
     if (e != hipSuccess) return hip_fail(e, "far-field set-up");
     if (ready) *ready = true;
-    const ProfEvent pe = prof_begin(op, true, st);
+    const ProfEvent pe = prof_begin(op, may_profile, st);
     const bool img0 = img_lo <= 0 && img_hi >= 0;
     e = far_sum(op, L, src, trg, d, img_lo, img_hi, final_args(op, src, trg, img0, mu, u, v, accumulate), ws, st);
     if (e != hipSuccess) return hip_fail(e, "far-field sum");
@@ -329,18 +339,13 @@ S2D_API int stokes2d_init(int device) {
 }
 
 S2D_API size_t stokes2d_workspace_size(int op, int mode, const s2d_curves *src, const s2d_targets *trg) {
-    if (check_args(op, mode, src, trg, 1.0, 0, 0, 1.0) != S2D_OK) return 0;
-    int dev = 0;
-    int cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDev && g_dev[dev].init) cus = g_dev[dev].cus;
-    s2d::Plan p = s2d::make_plan(op, mode, src, trg, cus);
-    return p.total > 0 ? p.total : 256;
+    return s2d::layer_workspace(op, mode, src, trg);
 }
 
 S2D_API int stokes2d_slp_eval(int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
                               int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws,
                               size_t ws_bytes, void *stream) {
-    return eval(S2D_OP_SLP, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream);
+    return s2d::layer_eval(S2D_OP_SLP, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream);
 }
 
 S2D_API int stokes2d_slp_eval_noalloc(int mode, const s2d_curves *src, const s2d_targets *trg, double d,
@@ -358,14 +363,16 @@ S2D_API int stokes2d_slp_eval_noalloc(int mode, const s2d_curves *src, const s2d
         return fail(S2D_EWORKSPACE, "problem needs " + std::to_string(p.total) +
                                         " bytes of scratch; stokes2d_slp_eval_noalloc holds " +
                                         std::to_string(kScratchBytes) + " (use stokes2d_slp_eval with a workspace)");
-    return eval(S2D_OP_SLP, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, sp, kScratchBytes, stream,
-                nullptr, nullptr, false);
+    // the far-field sum where the rule asks for it and the scratch holds it
+    return s2d::layer_eval(S2D_OP_SLP, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, sp, kScratchBytes,
+                           stream, nullptr, false);
 }
 
 S2D_API int stokes2d_dlp_eval(int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
                               int32_t img_hi, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
                               void *stream) {
-    return eval(S2D_OP_DLP, mode, src, trg, d, img_lo, img_hi, 1.0, u, v, accumulate, ws, ws_bytes, stream);
+    return s2d::layer_eval(S2D_OP_DLP, mode, src, trg, d, img_lo, img_hi, 1.0, u, v, accumulate, ws, ws_bytes,
+                           stream);
 }
 
 S2D_API int stokes2d_slp_pressure_eval(int mode, const s2d_curves *src, const s2d_targets *trg, double d,
@@ -542,11 +549,11 @@ RespLayout resp_layout(const s2d_cell *cell, int64_t n, int32_t nc, int mode) {
     const s2d_targets tw{nw, a, a, nullptr, nullptr}, ts{(int64_t)K, a, a, nullptr, nullptr},
         tv{n, a, a, nullptr, nullptr};
     size_t e = 256;
-    e = std::max(e, stokes2d_workspace_size(S2D_OP_SLP, mode, &ves, &tw));
-    e = std::max(e, stokes2d_workspace_size(S2D_OP_SLP, mode, &ves, &ts));
-    e = std::max(e, stokes2d_workspace_size(S2D_OP_SLP_TRACTION, mode, &ves, &ts));
-    e = std::max(e, stokes2d_workspace_size(S2D_OP_DLP, mode, &wal, &tv));
-    e = std::max(e, stokes2d_workspace_size(S2D_OP_SLP, mode, &prx, &tv));
+    e = std::max(e, s2d::direct_workspace(S2D_OP_SLP, mode, &ves, &tw));
+    e = std::max(e, s2d::direct_workspace(S2D_OP_SLP, mode, &ves, &ts));
+    e = std::max(e, s2d::direct_workspace(S2D_OP_SLP_TRACTION, mode, &ves, &ts));
+    e = std::max(e, s2d::direct_workspace(S2D_OP_DLP, mode, &wal, &tv));
+    e = std::max(e, s2d::direct_workspace(S2D_OP_SLP, mode, &prx, &tv));
     L.eval = o;
     L.need = o + align256(e);      // the least a call needs; L.total holds the far-field sums too
     e = std::max(e, s2d::layer_workspace(S2D_OP_SLP, mode, &ves, &tw));
@@ -1216,7 +1223,7 @@ NearWallLayout near_wall_layout(int method, const s2d_curves *w, const s2d_targe
     // layouts grow with the target count, so the full one covers AUTO's lists
     if (method != S2D_NEAR_MLP)
         for (const s2d_curves *c : {(const s2d_curves *)&f, w})
-            if (s2d::far_worth(c->n_nodes, t->n, false))
+            if (s2d::far_worth(c->n_nodes, t->n))
                 fb = std::max(fb, s2d::far_layout(S2D_OP_DLP, c->n_nodes, t->n, false).total);
     L.pair = o;
     L.need = o + align256(pb);

@@ -60,7 +60,9 @@ constexpr int kFarWaves = 4;     // waves per target tile, far kernel
 constexpr int kNearWaves = 8;    // and near kernel
 constexpr int kBoxBlocks = 64;
 constexpr int kSortItems = 2048; // items per sort block
-constexpr int kKeyBits = 30;     // bits of a sort key; the bit above marks targets
+// bits of a sort key (the bit above marks targets), eight to a pass: cells of
+// a few points at most where the points fill their domain evenly
+constexpr int key_bits(int64_t n) { return n <= 1 << 15 ? 15 : n <= 1 << 20 ? 23 : 31; }
 
 // circle around points [lo, hi) of a tile (empty: lo == hi); upper levels keep lo = 0, hi = 1
 struct FarNode {
@@ -169,7 +171,7 @@ __device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y, int bits) {
 // over the bounding square of a long channel leaves the channel and returns
 // elsewhere, and tiles across such a jump are ten times larger.
 __global__ __launch_bounds__(256) void far_keys(int64_t ns, int64_t nt, const double *sx, const double *sy,
-                                                const double *tx, const double *ty, const double *box, FarBox *info,
+                                                const double *tx, const double *ty, const double *box, int bits, FarBox *info,
                                                 uint32_t *key, int32_t *idx) {
     const int lane = threadIdx.x & 63;
     const double x0 = wmin(box[4 * lane]), x1 = wmax(box[4 * lane + 1]);
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(256) void far_keys(int64_t ns, int64_t nt, const do
     const bool ok = ext > 0.0 && ext < 1e300;
     const double side = fmax(wid, ext * (1.0 / 1024.0)) * (1.0 + 1e-9);
     const int nb = ok ? min(1024, (int)(ext / side) + 1) : 1;
-    const int cells = (kKeyBits - (nb > 1 ? 32 - __builtin_clz((unsigned)(nb - 1)) : 0)) / 2;   // bits per coordinate
+    const int cells = (bits - (nb > 1 ? 32 - __builtin_clz((unsigned)(nb - 1)) : 0)) / 2;   // bits per coordinate
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i == 0) {
         const int e = ok ? __builtin_amdgcn_frexp_exp(ext) : 0;
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(256) void far_keys(int64_t ns, int64_t nt, const do
     u = fmin(fmax(u * is, 0.0), (double)nb);
     const int b = min((int)u, nb - 1);
     const uint32_t cx = (uint32_t)fmin((u - (double)b) * c, m), cy = (uint32_t)fmin(fmax(v * is, 0.0) * c, m);
-    key[i] = (uint32_t)b << (2 * cells) | hilbert(cx, cy, cells) | (t ? 1u << kKeyBits : 0u);
+    key[i] = (uint32_t)b << (2 * cells) | hilbert(cx, cy, cells) | (t ? 1u << bits : 0u);
     idx[i] = (int32_t)(t ? i - ns : i);
 }
 
@@ -901,6 +903,9 @@ __global__ __launch_bounds__(256) void far_kress(const int32_t *off, int32_t nc,
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// the index array that holds the order after the last sort pass
+size_t far_sorted(const FarLayout &L) { return L.idx[((L.bits + 1) / 8) & 1]; }
+
 }  // namespace
 
 FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
@@ -914,6 +919,7 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
     // groups per circle: about four near workgroups for each compute unit
     L.groups = (int)std::min<int64_t>(8, std::max<int64_t>(1, 2048 / std::max<int64_t>(L.nT, 1)));
     const size_t N = (size_t)(ns + nt);
+    L.bits = key_bits((int64_t)N);
     L.nblk = (int64_t)((N + kSortItems - 1) / kSortItems);
     size_t o = 0;
     const auto take = [&](size_t bytes) {
@@ -945,13 +951,12 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
     return L;
 }
 
-// The direct sum takes 0.5 ns per 1,000 (target, source, image) triples plus
-// its launches; the set-up takes about 0.1 ms and a sum at least 0.15 ms.  With
-// images -1..1: 16,000^2 0.77 ms direct, 0.33 ms here, set-up included;
-// 9,600^2 0.43 and 0.34 ms; 23,000 x 4,000 about equal without and 0.1 ms
-// slower with the set-up.
-bool far_worth(int64_t ns, int64_t nt, bool reuse) {
-    return ns >= 4096 && nt >= 1024 && ns * nt >= (int64_t)1 << (reuse ? 26 : 28) && ns + nt < (int64_t)1 << 28;
+// Both routes measured at vesicle and wall sources, images -1..1, far / direct
+// in FP64 / direct in FP32C, set-up included (ms): 2^25.7 pairs 0.24 / 0.28 /
+// 0.23; 2^27.2 0.21 / 0.31 / 0.25; 2^28.6 0.30 / 0.89 / 0.53; 2^31 0.42 / 3.7 /
+// 1.9; 2^33.5 0.70 / 19.3 / 9.8.
+bool far_worth(int64_t ns, int64_t nt) {
+    return ns >= 4096 && nt >= 1024 && ns * nt >= (int64_t)1 << 26 && ns + nt < (int64_t)1 << 28;
 }
 
 hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_targets *t, void *ws,
@@ -962,8 +967,8 @@ hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_
     FarBox *info = (FarBox *)(box + 4 * kBoxBlocks);
     hipLaunchKernelGGL(far_box, dim3(kBoxBlocks), dim3(256), 0, st, L.ns, L.nt, s->x, s->y, t->x, t->y, box);
     hipLaunchKernelGGL(far_keys, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, L.ns, L.nt, s->x, s->y, t->x,
-                       t->y, box, info, (uint32_t *)(b + L.key[0]), (int32_t *)(b + L.idx[0]));
-    for (int p = 0; p < 4; ++p) {
+                       t->y, box, L.bits, info, (uint32_t *)(b + L.key[0]), (int32_t *)(b + L.idx[0]));
+    for (int p = 0; 8 * p < L.bits; ++p) {
         const uint32_t *ki = (const uint32_t *)(b + L.key[p & 1]);
         const int32_t *xi = (const int32_t *)(b + L.idx[p & 1]);
         uint32_t *hist = (uint32_t *)(b + L.hist), *base = (uint32_t *)(b + L.base);
@@ -975,7 +980,7 @@ hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_
     FarNode *node = (FarNode *)(b + L.node);
     const int64_t ts = L.n0 / 2, tt = L.nT / 2;
     hipLaunchKernelGGL(far_tiles, dim3((unsigned)((ts + tt + 3) / 4)), dim3(256), 0, st, L.ns, L.nt, ts, tt, s->x,
-                       s->y, t->x, t->y, (const int32_t *)(b + L.idx[0]), (int32_t *)(b + L.spos), node,
+                       s->y, t->x, t->y, (const int32_t *)(b + far_sorted(L)), (int32_t *)(b + L.spos), node,
                        (FarNode *)(b + L.tnode), (double *)(b + L.txy));
     hipLaunchKernelGGL(far_upper, dim3((unsigned)L.n2), dim3(64), 0, st, L.n0, L.n1, node);
     if (op == S2D_OP_SLP && t->on_curve && s->n_curves > 0)
@@ -989,7 +994,7 @@ template <int OP>
 hipError_t far_sum_t(const FarLayout &L, const s2d_curves *s, const s2d_targets *t, double d, int32_t img_lo,
                      int32_t img_hi, FinalArgs f, void *ws, hipStream_t st) {
     char *b = (char *)ws;
-    const int32_t *idx = (const int32_t *)(b + L.idx[0]);
+    const int32_t *idx = (const int32_t *)(b + far_sorted(L));
     const FarNode *node = (const FarNode *)(b + L.node), *tnode = (const FarNode *)(b + L.tnode);
     const FarBox *info = (const FarBox *)((const double *)(b + L.box) + 4 * kBoxBlocks);
     const bool img0 = img_lo <= 0 && img_hi >= 0;

@@ -1,7 +1,6 @@
-// Far-field summation (far.hip): the layer sums of eval() by near tiles taken
-// term by term and far clusters through truncated expansions, all in FP64.
-// Used by the composite entry points (time step, channel response, wall
-// correction), whose sums are large and repeated.
+// Far-field summation (far.hip): large velocity sums of the layers by near
+// tiles taken term by term and far clusters through truncated expansions, all
+// in FP64.
 #pragma once
 #include "s2d_internal.h"
 
@@ -14,15 +13,15 @@ struct FarLayout {
     int64_t n0, n1, n2, nT;    // source nodes of the three levels, target circles
     int groups;                // near workgroups per target circle
     int64_t nblk;              // sort blocks
+    int bits;                  // of a sort key
     size_t key[2], idx[2], hist, base, box, spos, node, tnode, txy, rec, coef, part, kress, self;
     size_t total;
 };
 
 FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve);
 
-// Whether the far-field sum is the faster route for these sizes; reuse: one
-// set-up serves several densities.
-bool far_worth(int64_t ns, int64_t nt, bool reuse);
+// Whether the far-field sum is the faster route for these sizes.
+bool far_worth(int64_t ns, int64_t nt);
 
 // Orders sources and targets along a space-filling curve and boxes their
 // tiles; with Kress's tables when the single layer's targets sit on curves.

@@ -117,14 +117,16 @@ hipError_t launch_final(const Plan &p, const FinalArgs &a, hipStream_t st);
 std::mutex &blas_mutex();
 void *blas_handle(hipStream_t st, std::string &err);
 
-// One layer sum inside a composite call (api.hip): eval(), or where the sizes
-// favour it and the workspace holds it the far-field sum (FP64 in either mode).
+// One layer sum (api.hip): the direct one, or for velocities, where the sizes
+// favour it and the workspace holds it, the far-field sum (FP64 in either mode).
 // ready, when given, is false before the first call for a geometry and then
 // lets later calls with the same nodes, targets and workspace keep the set-up.
+// direct_workspace: the least a call needs.
+size_t direct_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg);
 size_t layer_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg);
 int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
                int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
-               void *stream, bool *ready = nullptr);
+               void *stream, bool *ready = nullptr, bool may_profile = true);
 
 // error state and device checks shared by the entry points (api.hip):
 // set_error records the calling thread's message and returns code;

@@ -921,8 +921,8 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
     t.x = t.y = (const double *)1;
     t.on_curve = t.on_node = (const int32_t *)1;
     // FP64 sums always run (right-hand side and residuals); FP32C ones too in that mode
-    const size_t sz = std::max(stokes2d_workspace_size(S2D_OP_SLP, S2D_FP64, &c, &t),
-                               p->mode == S2D_FP32C ? stokes2d_workspace_size(S2D_OP_SLP, S2D_FP32C, &c, &t) : 0);
+    const size_t sz = std::max(direct_workspace(S2D_OP_SLP, S2D_FP64, &c, &t),
+                               p->mode == S2D_FP32C ? direct_workspace(S2D_OP_SLP, S2D_FP32C, &c, &t) : 0);
     L.slp = o;
     L.slp_bytes = std::max<size_t>(sz, 256);
     o += al256(L.slp_bytes);
@@ -980,7 +980,7 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
     }
     L.need = o;
     L.far = o;
-    if (far_worth(n, n, true)) {
+    if (far_worth(n, n)) {
         L.far_bytes = far_layout(S2D_OP_SLP, n, n, true).total;
         o += al256(L.far_bytes);
     }

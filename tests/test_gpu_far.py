@@ -105,3 +105,121 @@ def test_nan_source_reaches_every_target():
     out, _ = V.step_apply(p, torch.ones(3 * V.n, dtype=torch.float64, device="cuda"), with_rhs=False)
     torch.cuda.synchronize()
     assert torch.isnan(out[:2 * V.n]).all()
+
+
+def _mixed(seed, nv, sizes, n_free):
+    """Vesicle curves with a density, targets at every second node in random
+    order and n_free free points; curve 3 is made odd by dropping its last
+    node, and a few on-curve entries are out of range."""
+    import types
+    from oracle import vesicle as ov
+    x, y, off, d = _lattice(nv, sizes, seed)
+    rng = np.random.default_rng(seed)
+    keep = np.ones(len(x), bool)
+    keep[off[4] - 1] = False
+    g = ov.geometry(x, y, off)
+    cut = off.copy()
+    cut[4:] -= 1
+    cs = types.SimpleNamespace(x=x[keep], y=y[keep], nx=g.nx[keep], ny=g.ny[keep], w=g.w[keep],
+                               kappa=np.ones(keep.sum()), fx=rng.standard_normal(keep.sum()),
+                               fy=rng.standard_normal(keep.sum()), curve_off=cut)
+    node = rng.permutation(np.arange(0, keep.sum(), 2))
+    curve = np.searchsorted(cut, node, side="right") - 1
+    tx, ty = np.r_[cs.x[node], rng.uniform(0, d, n_free)], np.r_[cs.y[node], rng.uniform(1.1, 4.0, n_free)]
+    oc = np.r_[curve, np.full(n_free, -1)].astype(np.int32)
+    on = np.r_[node, np.full(n_free, -1)].astype(np.int32)
+    return cs, tx, ty, oc, on, d
+
+
+@pytest.mark.parametrize("op", [0, 1])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("nv,sizes,n_free,img", [(200, (58, 64), 1, (-1, 1)), (90, (96, 46), 7400, (0, 0)),
+                                                 (400, (62,), 3001, (0, 2))])
+def test_eval_routes(op, mode, nv, sizes, n_free, img):
+    import torch
+    import oracle
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    cs, tx, ty, oc, on, d = _mixed(7 + nv, nv, sizes, n_free)
+    src = s2d.Curves(cs)
+    bad = np.arange(5, 11)
+    res = []
+    print(f"op {op} mode {mode}: {src.n_nodes} sources, {len(tx)} targets, images {img}", flush=True)
+    for wild in (False, True):
+        c, k = oc.copy(), on.copy()
+        if wild:
+            c[bad[:3]], k[bad[3:]] = nv + 5, -7
+        t = s2d.Targets(tx, ty, c, k)
+        need = s2d.stokes2d_workspace_size(op, mode, src, t)
+        for size in (need, need - 256):
+            o = torch.zeros((2, t.n), dtype=torch.float64, device="cuda")
+            ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+            m = mode if size == need else 0
+            if op == 0:
+                s2d.stokes2d_slp_eval(m, src, t, d, img[0], img[1], 0.7, o[0], o[1], 0, ws)
+            else:
+                s2d.stokes2d_dlp_eval(m, src, t, d, img[0], img[1], o[0], o[1], 0, ws)
+            res.append(o)
+    torch.cuda.synchronize()
+    # the odd curve's targets (single layer) and the wild entries are NaN on both routes
+    _close(res[0], res[1])
+    assert torch.isnan(res[2][:, bad]).all()
+    ok = np.setdiff1d(np.arange(len(tx)), bad)
+    _close(res[2][:, ok], res[3][:, ok])
+    idx = np.random.default_rng(1).choice(np.setdiff1d(ok, np.nonzero(oc == 3)[0]), 300, replace=False)
+    if op == 0:
+        ru, rv = oracle.slp(cs, tx[idx], ty[idx], oc[idx], on[idx], d, img[0], img[1], 0.7)
+    else:
+        ru, rv = oracle.dlp(cs, tx[idx], ty[idx], oc[idx], on[idx], d, img[0], img[1])
+    g = res[0].cpu().numpy()[:, idx]
+    e = np.hypot(g[0] - ru, g[1] - rv).max() / np.hypot(ru, rv).max()
+    print(f"against the oracle {e:.1e}", flush=True)
+    assert e < 1e-12
+
+
+def test_capture_and_noalloc():
+    """The far-field route recorded into a graph and replayed on changed
+    densities with eager work between, and the no-allocation entry on the same
+    route: bit for bit the eager call."""
+    import torch
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    cs, tx, ty, oc, on, d = _mixed(3, 240, (96,), 500)
+    src, t = s2d.Curves(cs), s2d.Targets(tx, ty, oc, on)
+    ws = torch.empty(s2d.stokes2d_workspace_size(0, 0, src, t), dtype=torch.uint8, device="cuda")
+    o, e, q = (torch.zeros((2, t.n), dtype=torch.float64, device="cuda") for _ in range(3))
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s2d.stokes2d_slp_eval(0, src, t, d, -1, 1, 1.0, o[0], o[1], 0, ws, st)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            s2d.stokes2d_slp_eval(0, src, t, d, -1, 1, 1.0, o[0], o[1], 0, ws, st)
+    for k in range(3):
+        src.fx.mul_(1.5)
+        g.replay()
+        torch.cuda.synchronize()
+        s2d.stokes2d_slp_eval(0, src, t, d, -1, 1, 1.0, e[0], e[1])
+        s2d.stokes2d_slp_eval_noalloc(0, src, t, d, -1, 1, 1.0, q[0], q[1])
+        torch.cuda.synchronize()
+        assert torch.equal(o.nan_to_num(7.0), e.nan_to_num(7.0)) and torch.equal(q.nan_to_num(7.0), e.nan_to_num(7.0))
+
+
+def test_noalloc_beyond_the_far_scratch():
+    """500,000 sources: the far-field scratch does not fit the 32 MiB, the
+    direct sum's does."""
+    import torch
+    import types
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    n = 500_000
+    rng = np.random.default_rng(0)
+    a = lambda: rng.uniform(0, 1, n)
+    src = s2d.Curves(types.SimpleNamespace(x=100 * a(), y=a(), nx=a(), ny=a(), w=a() / n, kappa=a(), fx=a(), fy=a(),
+                                           curve_off=np.array([0, n], np.int32)))
+    t = s2d.Targets(100 * rng.uniform(0, 1, 1100), 2.0 + rng.uniform(0, 1, 1100))
+    far, direct = (torch.zeros((2, t.n), dtype=torch.float64, device="cuda") for _ in range(2))
+    s2d.stokes2d_slp_eval(0, src, t, 100.0, -1, 1, 1.0, far[0], far[1])
+    s2d.stokes2d_slp_eval_noalloc(0, src, t, 100.0, -1, 1, 1.0, direct[0], direct[1])
+    torch.cuda.synchronize()
+    assert not torch.equal(far, direct)
+    _close(far, direct)
