@@ -1781,31 +1781,35 @@ __device__ __forceinline__ void mlp_wave_sync() {
 }
 
 // activation columns of a training sample's record
-constexpr int kA_h0 = 0, kA_z1 = kNearFeat, kA_h1 = kA_z1 + 64, kA_z2 = kA_h1 + 64, kA_h2 = kA_z2 + 64,
-              kA_z3 = kA_h2 + 64, kA_h3 = kA_z3 + 64;
+constexpr int kA_h0 = 0, kA_d1 = kNearFeat, kA_h1 = kA_d1 + 64, kA_d2 = kA_h1 + 64, kA_h2 = kA_d2 + 64,
+              kA_d3 = kA_h2 + 64, kA_h3 = kA_d3 + 64;
 
 // one 64-neuron layer of sample's forward pass: lane o; in: the wave's LDS row
-// (n_in values), written over by the layer's activations on return
-__device__ __forceinline__ void mlp_fwd_layer(int n_in, const float *__restrict__ W, const float *__restrict__ b,
-                                              float *row, int o, float *z, float *h) {
+// (n_in values), written over by the layer's activations on return; returns
+// the pre-activation
+__device__ __forceinline__ float mlp_fwd_layer(int n_in, const float *__restrict__ W, const float *__restrict__ b,
+                                               float *row, int o, float *h) {
     float a = b[o];
     for (int k = 0; k < n_in; ++k) a = fmaf(row[k], W[k * 64 + o], a);
     const float hv = gelu_f(a);
-    z[o] = a;
     h[o] = hv;
     mlp_wave_sync();                     // every lane has read the inputs
     row[o] = hv;
     mlp_wave_sync();
+    return a;
 }
 
 // per sample: forward, the head (the 20 outputs dC contracted with the
 // sample's d, times exp(-2 pi b)), the weighted residual e = wt (head - R),
 // its loss term |e|^2 / 2B, the output deltas dY[o] = wt e_out(o) env d[p][in] / B,
-// and the pre-activations z1..z3 and activations h0..h3 for the backward pass
-__global__ __launch_bounds__(256) void mlp_fwd(int32_t B, const int32_t *__restrict__ idx,
-                                               const float *__restrict__ X, const float *__restrict__ T,
-                                               const float *__restrict__ prm, float *__restrict__ act,
-                                               float *__restrict__ dY, float *__restrict__ lossv) {
+// then backward: the deltas of the hidden layers.  The record keeps the
+// activations h0..h3 and the deltas; the pre-activations stay in registers
+// (one kernel instead of a forward and a backward one: 6.9 + 5.7 us apart at
+// 1,024 samples, most of it launch and first-load latency).
+__global__ __launch_bounds__(256) void mlp_sample(int32_t B, const int32_t *__restrict__ idx,
+                                                  const float *__restrict__ X, const float *__restrict__ T,
+                                                  const float *__restrict__ prm, float *__restrict__ act,
+                                                  float *__restrict__ dY, float *__restrict__ lossv) {
     __shared__ float rows[kBlock / kWave][64];
     using O = MlpOffsets;
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
@@ -1820,9 +1824,9 @@ __global__ __launch_bounds__(256) void mlp_fwd(int32_t B, const int32_t *__restr
         row[lane] = v;
     }
     mlp_wave_sync();
-    mlp_fwd_layer(kNearFeat, prm + O::W1, prm + O::b1, row, lane, A + kA_z1, A + kA_h1);
-    mlp_fwd_layer(64, prm + O::W2, prm + O::b2, row, lane, A + kA_z2, A + kA_h2);
-    mlp_fwd_layer(64, prm + O::W3, prm + O::b3, row, lane, A + kA_z3, A + kA_h3);
+    const float z1 = mlp_fwd_layer(kNearFeat, prm + O::W1, prm + O::b1, row, lane, A + kA_h1);
+    const float z2 = mlp_fwd_layer(64, prm + O::W2, prm + O::b2, row, lane, A + kA_h2);
+    const float z3 = mlp_fwd_layer(64, prm + O::W3, prm + O::b3, row, lane, A + kA_h3);
     float yo = 0.f;
     if (lane < kNearOut) {
         float a = prm[O::b4 + lane];
@@ -1841,96 +1845,122 @@ __global__ __launch_bounds__(256) void mlp_fwd(int32_t B, const int32_t *__restr
     }
     const float wt = t[12], env = t[13];
     const float e0 = wt * (env * hd[0] - t[10]), e1 = wt * (env * hd[1] - t[11]);
+    mlp_wave_sync();
     if (lane < kNearOut) {
         const int p = lane / 4, out = (lane % 4) / 2, in = lane % 2;
-        dY[(int64_t)s * kNearOut + lane] = wt * (out ? e1 : e0) * env * t[2 * p + in] / (float)B;
+        const float g = wt * (out ? e1 : e0) * env * t[2 * p + in] / (float)B;
+        dY[(int64_t)s * kNearOut + lane] = g;
+        row[lane] = g;
     }
     if (lane == 0) lossv[s] = 0.5f * (e0 * e0 + e1 * e1) / (float)B;
-}
-
-// per sample: the deltas of the three hidden layers, written over z3, z2, z1
-__global__ __launch_bounds__(256) void mlp_bwd(int32_t B, const float *__restrict__ prm, float *__restrict__ act,
-                                               const float *__restrict__ dY) {
-    __shared__ float rows[kBlock / kWave][64];
-    using O = MlpOffsets;
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const int s = blockIdx.x * (kBlock / kWave) + wv;
-    if (s >= B) return;                  // wave-uniform
-    float *row = rows[wv];
-    float *A = act + (int64_t)s * kActStride;
-    const float *g = dY + (int64_t)s * kNearOut;
+    mlp_wave_sync();
     float a = 0.f;
-    for (int o = 0; o < kNearOut; ++o) a = fmaf(prm[O::W4 + lane * kNearOut + o], g[o], a);
-    const float d3 = a * gelu_grad_f(A[kA_z3 + lane]);
-    A[kA_z3 + lane] = d3;
+    for (int o = 0; o < kNearOut; ++o) a = fmaf(prm[O::W4 + lane * kNearOut + o], row[o], a);
+    const float d3 = a * gelu_grad_f(z3);
+    A[kA_d3 + lane] = d3;
+    mlp_wave_sync();
     row[lane] = d3;
     mlp_wave_sync();
     a = 0.f;
     for (int o = 0; o < 64; ++o) a = fmaf(prm[O::W3 + lane * 64 + o], row[o], a);
-    const float d2 = a * gelu_grad_f(A[kA_z2 + lane]);
-    A[kA_z2 + lane] = d2;
+    const float d2 = a * gelu_grad_f(z2);
+    A[kA_d2 + lane] = d2;
     mlp_wave_sync();
     row[lane] = d2;
     mlp_wave_sync();
     a = 0.f;
     for (int o = 0; o < 64; ++o) a = fmaf(prm[O::W2 + lane * 64 + o], row[o], a);
-    A[kA_z1 + lane] = a * gelu_grad_f(A[kA_z1 + lane]);
+    A[kA_d1 + lane] = a * gelu_grad_f(z1);
 }
 
 // gradient of every parameter: the sum over the batch of (input activation x
 // delta), in kGradChunks contiguous runs of samples, each summed in sample
-// order, then the runs added in order (fixed order: deterministic); a block
-// holds 256 / kGradChunks parameters.  The loss is the sum of lossv.
+// order, then the runs added in order (fixed order: deterministic).  A
+// workgroup owns kGradRows input rows of one layer and all its columns: wave
+// = run, lane = column; a sample costs one coalesced load of the deltas and a
+// scalar load of the rows' activations, 16 samples of loads ahead of their
+// FMAs.  Bound by the latency of those loads (8 rounds of 16 at 1,024 samples).
+// The first row group of a layer also sums its biases; the last workgroup adds
+// the samples' losses in order, from LDS.  12 us at 1,024 samples; one thread
+// per parameter and run, each loading both factors, and one thread adding the
+// losses from memory took 49 us.
 constexpr int kGradChunks = 8;
-__global__ __launch_bounds__(256) void mlp_grad(int32_t B, const float *__restrict__ act,
-                                                const float *__restrict__ dY, const float *__restrict__ lossv,
-                                                float *__restrict__ grad, float *__restrict__ loss) {
-    constexpr int kPer = kBlock / kGradChunks;
-    __shared__ float part[kGradChunks][kPer];
+constexpr int kGradRows = 4;
+constexpr int kGradTiles1 = (kNearFeat + kGradRows - 1) / kGradRows, kGradTiles = 64 / kGradRows;
+constexpr int kGradBlocks = kGradTiles1 + 3 * kGradTiles;        // then one for the loss
+__global__ __launch_bounds__(kGradChunks *kWave) void mlp_grad(int32_t B, const float *__restrict__ act,
+                                                               const float *__restrict__ dY,
+                                                               const float *__restrict__ lossv,
+                                                               float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ float part[kGradChunks][kGradRows + 1][kWave];
     using O = MlpOffsets;
-    const int pp = threadIdx.x % kPer, ch = threadIdx.x / kPer;
-    const int p = blockIdx.x * kPer + pp;
-    int hin = -1, dl = -1, dk = 0;               // activation column, delta column (act) or output (dY)
-    bool outd = false;
-    if (p >= O::W1 && p < O::b1) { const int r = p - O::W1; hin = kA_h0 + r / 64; dl = kA_z1 + r % 64; }
-    else if (p >= O::b1 && p < O::W2) { dl = kA_z1 + (p - O::b1); }
-    else if (p >= O::W2 && p < O::b2) { const int r = p - O::W2; hin = kA_h1 + r / 64; dl = kA_z2 + r % 64; }
-    else if (p >= O::b2 && p < O::W3) { dl = kA_z2 + (p - O::b2); }
-    else if (p >= O::W3 && p < O::b3) { const int r = p - O::W3; hin = kA_h2 + r / 64; dl = kA_z3 + r % 64; }
-    else if (p >= O::b3 && p < O::W4) { dl = kA_z3 + (p - O::b3); }
-    else if (p >= O::W4 && p < O::b4) { const int r = p - O::W4; hin = kA_h3 + r / kNearOut; dk = r % kNearOut; outd = true; }
-    else if (p >= O::b4 && p < O::total) { dk = p - O::b4; outd = true; }
-    float g = 0.f;
-    if (p >= O::W1 && p < O::total) {            // mu_in / sd_in are not trained
-        const int s0 = (int)((int64_t)B * ch / kGradChunks), s1 = (int)((int64_t)B * (ch + 1) / kGradChunks);
-        // the loads of 8 samples are issued before their (ordered) FMAs
-        const float *dsrc = outd ? dY + dk : act + dl;
-        const int64_t dstr = outd ? kNearOut : kActStride;
-        int s = s0;
-        for (; s + 8 <= s1; s += 8) {
-            float dv[8], hv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                dv[u] = dsrc[(int64_t)(s + u) * dstr];
-                hv[u] = hin >= 0 ? act[(int64_t)(s + u) * kActStride + hin] : 1.f;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) g = fmaf(hv[u], dv[u], g);
-        }
-        for (; s < s1; ++s) g = fmaf(hin >= 0 ? act[(int64_t)s * kActStride + hin] : 1.f, dsrc[(int64_t)s * dstr], g);
-    }
-    part[ch][pp] = g;
-    __syncthreads();
-    if (ch == 0 && p < O::total) {
-        float t = 0.f;
-        for (int c = 0; c < kGradChunks; ++c) t += part[c][pp];
-        grad[p] = t;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
+    if (blockIdx.x == kGradBlocks) {
+        if (threadIdx.x < O::W1) grad[threadIdx.x] = 0.f;        // mu_in / sd_in are not trained
+        if (!loss) return;
+        float *buf = &part[0][0][0];
+        constexpr int kBuf = 2048;
+        static_assert(kBuf <= kGradChunks * (kGradRows + 1) * kWave, "the losses' buffer");
         float l = 0.f;
-        for (int s = 0; s < B; ++s) l += lossv[s];
-        *loss = l;
+        for (int s0 = 0; s0 < B; s0 += kBuf) {
+            const int n = min(kBuf, B - s0);
+            for (int k = threadIdx.x; k < n; k += blockDim.x) buf[k] = lossv[s0 + k];
+            __syncthreads();
+            if (threadIdx.x == 0) {
+#pragma unroll 16
+                for (int k = 0; k < n; ++k) l += buf[k];
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = l;
+        return;
     }
+    const int lane = threadIdx.x & (kWave - 1), ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // the layer (0..3), its first row here, its input and delta columns
+    const int b = blockIdx.x, layer = b < kGradTiles1 ? 0 : 1 + (b - kGradTiles1) / kGradTiles;
+    const int row0 = kGradRows * (layer == 0 ? b : (b - kGradTiles1) % kGradTiles);
+    const int n_in = layer == 0 ? kNearFeat : 64, n_out = layer == 3 ? kNearOut : 64;
+    const int hin = (layer == 0 ? kA_h0 : layer == 1 ? kA_h1 : layer == 2 ? kA_h2 : kA_h3) + row0;
+    const int rows = min(kGradRows, n_in - row0), col = min(lane, n_out - 1);
+    const float *dsrc = layer == 3 ? dY + col : act + (layer == 0 ? kA_d1 : layer == 1 ? kA_d2 : kA_d3) + col;
+    const int64_t dstr = layer == 3 ? kNearOut : kActStride;
+    const float *hsrc = act + hin;
+    const int s0 = (int)((int64_t)B * ch / kGradChunks), s1 = (int)((int64_t)B * (ch + 1) / kGradChunks);
+    float g[kGradRows] = {}, gb = 0.f;
+    int s = s0;
+    constexpr int kAhead = 16;
+    for (; s + kAhead <= s1; s += kAhead) {
+        float dv[kAhead], hv[kAhead][kGradRows];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            dv[u] = dsrc[(int64_t)(s + u) * dstr];
+            // rows past n_in read the record's next column and are not written
+#pragma unroll
+            for (int r = 0; r < kGradRows; ++r) hv[u][r] = hsrc[(int64_t)(s + u) * kActStride + r];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+#pragma unroll
+            for (int r = 0; r < kGradRows; ++r) g[r] = fmaf(hv[u][r], dv[u], g[r]);
+            gb = fmaf(1.f, dv[u], gb);
+        }
+    }
+    for (; s < s1; ++s) {
+        const float dv = dsrc[(int64_t)s * dstr];
+#pragma unroll
+        for (int r = 0; r < kGradRows; ++r) g[r] = fmaf(hsrc[(int64_t)s * kActStride + r], dv, g[r]);
+        gb = fmaf(1.f, dv, gb);
+    }
+#pragma unroll
+    for (int r = 0; r < kGradRows; ++r) part[ch][r][lane] = g[r];
+    part[ch][kGradRows][lane] = gb;
+    __syncthreads();
+    const int r = ch;                                // wave r finishes row r, wave kGradRows the biases
+    if (lane >= n_out || r > kGradRows || (r < kGradRows && r >= rows) || (r == kGradRows && row0 > 0)) return;
+    float t = 0.f;
+    for (int c = 0; c < kGradChunks; ++c) t += part[c][r][lane];
+    const int W = layer == 0 ? O::W1 : layer == 1 ? O::W2 : layer == 2 ? O::W3 : O::W4;
+    const int bias = layer == 0 ? O::b1 : layer == 1 ? O::b2 : layer == 2 ? O::b3 : O::b4;
+    grad[r == kGradRows ? bias + lane : W + (row0 + r) * n_out + lane] = t;
 }
 
 __global__ __launch_bounds__(256) void mlp_adam(float *__restrict__ prm, const float *__restrict__ grad,
@@ -2142,10 +2172,9 @@ hipError_t near_launch_train_step(int32_t B, const int32_t *idx, const float *X,
                                   float *lossv, float *loss, int update, hipStream_t st) {
     using O = MlpOffsets;
     const unsigned wave_blocks = (unsigned)((B + kBlock / kWave - 1) / (kBlock / kWave));   // a wave per sample
-    hipLaunchKernelGGL(mlp_fwd, dim3(wave_blocks), dim3(kBlock), 0, st, B, idx, X, T, prm, act, dY, lossv);
-    hipLaunchKernelGGL(mlp_bwd, dim3(wave_blocks), dim3(kBlock), 0, st, B, prm, act, dY);
-    hipLaunchKernelGGL(mlp_grad, dim3((unsigned)((O::total + kBlock / kGradChunks - 1) / (kBlock / kGradChunks))),
-                       dim3(kBlock), 0, st, B, act, dY, lossv, grad, loss);
+    hipLaunchKernelGGL(mlp_sample, dim3(wave_blocks), dim3(kBlock), 0, st, B, idx, X, T, prm, act, dY, lossv);
+    hipLaunchKernelGGL(mlp_grad, dim3(kGradBlocks + 1), dim3(kGradChunks * kWave), 0, st, B, act, dY, lossv, grad,
+                       loss);
     if (update)
         hipLaunchKernelGGL(mlp_adam, dim3(grid_for(O::total)), dim3(256), 0, st, prm, grad, m, v, step, lr, 0.9f,
                            0.999f, 1e-8f);

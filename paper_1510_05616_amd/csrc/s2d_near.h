@@ -19,7 +19,7 @@ constexpr int kNearSBins = 5;                   // bins of |s|: width 1/8, the l
 constexpr int kNearKBins = 8;                   // bins of log10 |kappa h| from -2, width 3/16, both ends open
 constexpr int kNearCell = kNearSBins * kNearKBins;
 constexpr int kNearTable = kNearMaxBins * kNearCell;
-constexpr int kActStride = kNearFeat + 6 * 64;   // h0 z1 h1 z2 h2 z3 h3 per training sample
+constexpr int kActStride = kNearFeat + 6 * 64;   // h0 d1 h1 d2 h2 d3 h3 per training sample
 // training sample record (floats): d[10] (frame, d_pt at 2p, d_pn at 2p + 1),
 // the flat prediction's residual R[2] (frame, units of the layer's scale),
 // the loss weight, exp(-2 pi b)
