@@ -34,14 +34,15 @@
  *   - signed curvature kappa = -(x'' . n) / |x'|^2 (positive on a convex curve
  *     with outward normal);  normals are taken as given.
  *
- * Large sums.  A velocity sum (single or double layer) with at least 2^26
- * (source, target) pairs, 4,096 sources and 1,024 targets takes the far-field
- * route, in FP64 in either mode: sources and targets are sorted along a
- * space-filling curve, near nodes are summed term by term and well separated
- * clusters through expansions truncated below 1e-17 of their terms, in a fixed
- * order.  It needs the workspace stokes2d_workspace_size() gives (about 100
- * bytes per source node and 70 per target); with a smaller one that still
- * holds the direct sum, the call sums directly in its mode's arithmetic.
+ * Large sums.  A sum whose (source, target) pairs times images (at most three
+ * counted) reach 3 * 2^26 in S2D_FP64 or 2^29 in S2D_FP32C, with 2,048 sources
+ * and 1,024 targets at least, takes the far-field route, in FP64 in either
+ * mode: sources and targets are sorted along a space-filling curve, near nodes
+ * are summed term by term and well separated clusters through expansions
+ * truncated below 1e-17 of their terms, in a fixed order.  It needs the
+ * workspace stokes2d_workspace_size() gives (about 100 bytes per source node
+ * and 70 per target); with a smaller one that still holds the direct sum, the
+ * call sums directly in its mode's arithmetic.
  *
  * Memory and ownership.  Every array argument is a DEVICE pointer to
  * caller-owned memory, structure-of-arrays, FP64 (int32 for indices), in

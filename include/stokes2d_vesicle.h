@@ -68,10 +68,10 @@ S2D_API int ves_measure(int64_t n_nodes, int32_t n_curves, const int32_t *curve_
  * row is Eq. (ALC) with L0 [n_curves] the reference perimeters; L0 = NULL
  * gives x_s . u_s = 0.  u_resp_x, u_resp_y: the channel's response velocity
  * at the nodes ([n_nodes] each) or NULL (none, e.g. free space).  mode: the
- * s2d_mode of the single-layer sums in ves_step_apply; from 8,192 nodes on
- * the sums are far-field sums (near nodes term by term, far clusters through
- * expansions truncated below 1e-17), FP64 in either mode, when the workspace
- * has the size ves_step_workspace_size gives.  The solves
+ * s2d_mode of the single-layer sums in ves_step_apply; from about
+ * 5,800 nodes on (three images; 10,000 with one) the sums take the far-field
+ * route of stokes2d.h, FP64 in either mode, when the workspace has the size
+ * ves_step_workspace_size gives.  The solves
  * (ves_step_solve, ves_time_step) with S2D_FP32C refine iteratively: the
  * right-hand side and every residual b - A z in FP64, each correction
  * A dz = r by GMRES with FP32C sums to a relative 1e-4 (FP32C sums alone

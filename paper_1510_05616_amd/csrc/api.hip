@@ -100,6 +100,16 @@ int check_args(int op, int mode, const s2d_curves *s, const s2d_targets *t, doub
     return S2D_OK;
 }
 
+int check_outputs(int op, const s2d_targets *trg, const double *u, const double *v, const double *tnx,
+                  const double *tny) {
+    const bool scalar = op == S2D_OP_SLP_PRESSURE || op == S2D_OP_DLP_PRESSURE;
+    if (trg->n > 0) {
+        if (!u || (!scalar && !v)) return fail(S2D_EINVAL, "output arrays must not be NULL");
+        if (op == S2D_OP_SLP_TRACTION && (!tnx || !tny)) return fail(S2D_EINVAL, "traction needs target normals");
+    }
+    return S2D_OK;
+}
+
 int check_batch_inst(int mode, const s2d_instance &I, int32_t k) {
     const std::string where = "instance " + std::to_string(k) + ": ";
     int rc = check_args(S2D_OP_SLP, mode, &I.ves, &I.trg_ves, I.d, -1, 1, I.mu);
@@ -125,7 +135,7 @@ int hip_fail(hipError_t e, const char *what) {
 }
 
 // The final step's arguments of an evaluation, the partial and self sums
-// (part, self, n_parts) left to the caller.
+// (part, self, kress, n_parts) left to the caller.
 s2d::FinalArgs final_args(int op, const s2d_curves *src, const s2d_targets *trg, bool img0, double mu, double *u,
                           double *v, int accumulate) {
     s2d::FinalArgs f{};
@@ -154,6 +164,8 @@ s2d::FinalArgs final_args(int op, const s2d_curves *src, const s2d_targets *trg,
     f.kappa = src->kappa;
     f.fx = src->fx;
     f.fy = src->fy;
+    f.sx = src->x;
+    f.sy = src->y;
     return f;
 }
 
@@ -182,11 +194,8 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
     using namespace s2d;
     int rc = check_args(op, mode, src, trg, d, img_lo, img_hi, mu);
     if (rc != S2D_OK) return rc;
-    const int ncomp = (op == S2D_OP_SLP_PRESSURE || op == S2D_OP_DLP_PRESSURE) ? 1 : 2;
-    if (trg->n > 0) {
-        if (!u || (ncomp == 2 && !v)) return fail(S2D_EINVAL, "output arrays must not be NULL");
-        if (op == S2D_OP_SLP_TRACTION && (!tnx || !tny)) return fail(S2D_EINVAL, "traction needs target normals");
-    }
+    rc = check_outputs(op, trg, u, v, tnx, tny);
+    if (rc != S2D_OK) return rc;
     int dev = 0;
     rc = current_device(&dev);
     if (rc != S2D_OK) return rc;
@@ -209,10 +218,6 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
         e = launch_prep(p, src, ws, st);
         if (e != hipSuccess) return hip_fail(e, "prep launch");
     }
-    if (p.self) {
-        e = launch_kress(p, src, trg, ws, st);
-        if (e != hipSuccess) return hip_fail(e, "kress launch");
-    }
     PairArgs a{};
     a.rec = (char *)ws + p.off_rec;
     a.sbsum = (const double *)((char *)ws + p.off_sbsum);
@@ -230,6 +235,7 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
     a.n_groups = p.n_groups;
     a.sb_per_split = p.sb_per_split;
     a.n_sb = p.n_sb;
+    a.sbs = p.sbs;
     a.d = d;
     a.img_lo = img_lo;
     a.img_hi = img_hi;
@@ -239,7 +245,7 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
     a.rec64 = (char *)ws + p.off_rec64;
     FinalArgs f = final_args(op, src, trg, img0, mu, u, v, accumulate);
     f.part = a.part;
-    f.self = p.self ? (const double *)((char *)ws + p.off_self) : nullptr;
+    f.kress = p.self ? (const double *)((char *)ws + p.off_kress) : nullptr;
     f.n_parts = p.n_blocks > 0 ? p.n_groups : 0;
     if (p.n_blocks > 0) {
         const ProfEvent pe = prof_begin(op, may_profile, st);
@@ -269,34 +275,35 @@ size_t direct_workspace(int op, int mode, const s2d_curves *src, const s2d_targe
 
 size_t layer_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg) {
     const size_t direct = direct_workspace(op, mode, src, trg);
-    if (direct == 0 || op > S2D_OP_DLP || !far_worth(src->n_nodes, trg->n)) return direct;
+    if (direct == 0 || !far_worth(mode, src->n_nodes, trg->n, 3, false)) return direct;
     return std::max(direct, far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr).total);
 }
 
 int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
                int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
-               void *stream, bool *ready, bool may_profile) {
-    const bool far = trg && src && (op == S2D_OP_SLP || op == S2D_OP_DLP) &&
-                     far_worth(src->n_nodes, trg->n);
+               void *stream, const LayerOpts &o) {
+    const bool far = trg && src && op >= S2D_OP_SLP && op <= S2D_OP_SLP_TRACTION &&
+                     far_worth(mode, src->n_nodes, trg->n, img_hi - img_lo + 1, o.ready != nullptr);
     const FarLayout L = far ? far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr) : FarLayout{};
     if (!far || !ws || ws_bytes < L.total)
-        return eval(op, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream, nullptr,
-                    nullptr, may_profile);
+        return eval(op, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream, o.tnx, o.tny,
+                    o.may_profile);
     int rc = check_args(op, mode, src, trg, d, img_lo, img_hi, mu);
+    if (rc == S2D_OK) rc = check_outputs(op, trg, u, v, o.tnx, o.tny);
     if (rc != S2D_OK) return rc;
-    if (!u || !v) return fail(S2D_EINVAL, "output arrays must not be NULL");
     int dev = 0;
     rc = current_device(&dev);
     if (rc != S2D_OK) return rc;
     if (((uintptr_t)ws & 255) != 0) return fail(S2D_EWORKSPACE, "workspace must be 256-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    if (!ready || !*ready) e = far_setup(op, L, src, trg, ws, st);
+    if (!o.ready || !*o.ready) e = far_setup(op, L, src, trg, ws, st);
     if (e != hipSuccess) return hip_fail(e, "far-field set-up");
-    if (ready) *ready = true;
-    const ProfEvent pe = prof_begin(op, may_profile, st);
+    if (o.ready) *o.ready = true;
+    const ProfEvent pe = prof_begin(op, o.may_profile, st);
     const bool img0 = img_lo <= 0 && img_hi >= 0;
-    e = far_sum(op, L, src, trg, d, img_lo, img_hi, final_args(op, src, trg, img0, mu, u, v, accumulate), ws, st);
+    e = far_sum(op, L, src, trg, o.tnx, o.tny, d, img_lo, img_hi, final_args(op, src, trg, img0, mu, u, v, accumulate),
+                ws, st);
     if (e != hipSuccess) return hip_fail(e, "far-field sum");
     prof_end(pe, st);
     return S2D_OK;
@@ -365,7 +372,7 @@ S2D_API int stokes2d_slp_eval_noalloc(int mode, const s2d_curves *src, const s2d
                                         std::to_string(kScratchBytes) + " (use stokes2d_slp_eval with a workspace)");
     // the far-field sum where the rule asks for it and the scratch holds it
     return s2d::layer_eval(S2D_OP_SLP, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, sp, kScratchBytes,
-                           stream, nullptr, false);
+                           stream, s2d::LayerOpts{nullptr, false, nullptr, nullptr});
 }
 
 S2D_API int stokes2d_dlp_eval(int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
@@ -378,23 +385,23 @@ S2D_API int stokes2d_dlp_eval(int mode, const s2d_curves *src, const s2d_targets
 S2D_API int stokes2d_slp_pressure_eval(int mode, const s2d_curves *src, const s2d_targets *trg, double d,
                                        int32_t img_lo, int32_t img_hi, double *p, int accumulate, void *ws,
                                        size_t ws_bytes, void *stream) {
-    return eval(S2D_OP_SLP_PRESSURE, mode, src, trg, d, img_lo, img_hi, 1.0, p, nullptr, accumulate, ws, ws_bytes,
-                stream);
+    return s2d::layer_eval(S2D_OP_SLP_PRESSURE, mode, src, trg, d, img_lo, img_hi, 1.0, p, nullptr, accumulate, ws,
+                           ws_bytes, stream);
 }
 
 S2D_API int stokes2d_dlp_pressure_eval(int mode, const s2d_curves *src, const s2d_targets *trg, double d,
                                        int32_t img_lo, int32_t img_hi, double mu, double *p, int accumulate,
                                        void *ws, size_t ws_bytes, void *stream) {
-    return eval(S2D_OP_DLP_PRESSURE, mode, src, trg, d, img_lo, img_hi, mu, p, nullptr, accumulate, ws, ws_bytes,
-                stream);
+    return s2d::layer_eval(S2D_OP_DLP_PRESSURE, mode, src, trg, d, img_lo, img_hi, mu, p, nullptr, accumulate, ws,
+                           ws_bytes, stream);
 }
 
 S2D_API int stokes2d_slp_traction_eval(int mode, const s2d_curves *src, const s2d_targets *trg,
                                        const double *trg_nx, const double *trg_ny, double d, int32_t img_lo,
                                        int32_t img_hi, double *tx, double *ty, int accumulate, void *ws,
                                        size_t ws_bytes, void *stream) {
-    return eval(S2D_OP_SLP_TRACTION, mode, src, trg, d, img_lo, img_hi, 1.0, tx, ty, accumulate, ws, ws_bytes,
-                stream, trg_nx, trg_ny);
+    return s2d::layer_eval(S2D_OP_SLP_TRACTION, mode, src, trg, d, img_lo, img_hi, 1.0, tx, ty, accumulate, ws,
+                           ws_bytes, stream, s2d::LayerOpts{nullptr, true, trg_nx, trg_ny});
 }
 
 // ---------------------------------------------------------------------------
@@ -1223,7 +1230,7 @@ NearWallLayout near_wall_layout(int method, const s2d_curves *w, const s2d_targe
     // layouts grow with the target count, so the full one covers AUTO's lists
     if (method != S2D_NEAR_MLP)
         for (const s2d_curves *c : {(const s2d_curves *)&f, w})
-            if (s2d::far_worth(c->n_nodes, t->n))
+            if (s2d::far_worth(S2D_FP64, c->n_nodes, t->n, 3, false))
                 fb = std::max(fb, s2d::far_layout(S2D_OP_DLP, c->n_nodes, t->n, false).total);
     L.pair = o;
     L.need = o + align256(pb);

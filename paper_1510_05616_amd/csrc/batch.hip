@@ -85,12 +85,11 @@ __global__ void batch_reset(unsigned long long *counter) {
     if (threadIdx.x < 2 && blockIdx.x == 0) counter[threadIdx.x] = 0ull;
 }
 
-// FP64: one thread per padded source; FP32C: one thread per sub-block
-// (the prefix sums count padded sources; sub-blocks never straddle instances).
+// One thread per padded source (an instance's sources are padded to whole
+// superblocks, so sub-blocks never straddle instances).
 template <int PREC>
 __global__ __launch_bounds__(256) void batch_prep(BatchTables t, int op) {
-    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t g = PREC == S2D_FP64 ? g0 : g0 * kSubBlock;
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t *off = op == 0 ? t.src_pad_off0 : t.src_pad_off1;
     if (g >= off[t.n_inst]) return;
     const int k = find_inst(off, t.n_inst, g);
@@ -104,9 +103,9 @@ __global__ __launch_bounds__(256) void batch_prep(BatchTables t, int op) {
     } else {
         SubInfo *sub = (SubInfo *)I.pa[op].sub;
         if (op == 0)
-            prep_sub32<S2D_OP_SLP>(j / kSubBlock, s.n_nodes, s.x, s.y, s.nx, s.ny, s.w, s.fx, s.fy, rec, sub);
+            prep_one32<S2D_OP_SLP>(j, s.n_nodes, s.x, s.y, s.nx, s.ny, s.w, s.fx, s.fy, rec, sub);
         else
-            prep_sub32<S2D_OP_DLP>(j / kSubBlock, s.n_nodes, s.x, s.y, s.nx, s.ny, s.w, s.fx, s.fy, rec, sub);
+            prep_one32<S2D_OP_DLP>(j, s.n_nodes, s.x, s.y, s.nx, s.ny, s.w, s.fx, s.fy, rec, sub);
     }
 }
 
@@ -116,7 +115,7 @@ __global__ __launch_bounds__(256) void batch_sbsum(BatchTables t) {
     const int k = find_inst(t.sb_off, t.n_inst, g);
     const BatchInst &I = t.inst[k];
     const s2d_curves &s = I.src[0];
-    sbsum_wave(g - t.sb_off[k], s.n_nodes, s.w, s.fx, s.fy, (double *)I.pa[0].sbsum, threadIdx.x & (kWave - 1));
+    sbsum_wave(g - t.sb_off[k], kSuperBlock, s.n_nodes, s.w, s.fx, s.fy, (double *)I.pa[0].sbsum, threadIdx.x & (kWave - 1));
 }
 
 __global__ __launch_bounds__(256) void batch_kress_table(BatchTables t) {
@@ -423,8 +422,7 @@ hipError_t record_graph(BatchPlan &P, const BatchTables &t, int n_pre_targets, i
         if (prec == S2D_FP64)
             hipLaunchKernelGGL(batch_prep<S2D_FP64>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, t, op);
         else
-            hipLaunchKernelGGL(batch_prep<S2D_FP32C>, dim3((unsigned)((tot / kSubBlock + 255) / 256)), dim3(256), 0,
-                               st, t, op);
+            hipLaunchKernelGGL(batch_prep<S2D_FP32C>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, t, op);
     }
     if (prec == S2D_FP32C && tot_sb > 0)
         hipLaunchKernelGGL(batch_sbsum, dim3((unsigned)((tot_sb + 3) / 4)), dim3(256), 0, st, t);
@@ -520,6 +518,7 @@ int build_plan(BatchPlan &P, int mode, int32_t n_inst, const s2d_instance *inst,
             a.n_splits = (int32_t)g.n_splits[op];
             a.sb_per_split = g.sbps;
             a.n_sb = g.n_sb[op];
+            a.sbs = kSuperBlock;
             a.d = I.d;
             a.img_lo = -1;
             a.img_hi = 1;

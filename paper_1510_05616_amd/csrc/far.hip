@@ -1,4 +1,4 @@
-// Far-field summation of the single and double layer in FP64.
+// Far-field summation of the layers' velocities, pressures and traction in FP64.
 //
 // A direct sum over the 128k channel's 2.8e10 (target, source, image) triples
 // is bound by FP64 issue (15 ms) although all but about 1 % of the triples are
@@ -14,7 +14,11 @@
 //     psi = -1/2 sum conj(g) log r - 1/2 sum conj(w - c) g / r,  const = 1/2 sum g
 //   double layer (a = nu tau, b = 2 Re(conj(nu) tau)):  phi = 1/4 sum a / r,
 //     psi = 1/4 [ sum b / r - sum conj(w - c) a / r^2 ],         const = 0
-// so a cluster is two complex series of kOrder terms.  About a source centre
+// and the other operators follow from the same two functions:
+//   single-layer pressure sum Re(g / r) = -2 Re phi',
+//   double-layer pressure sum Re(a / r^2) = -4 Re phi',
+//   traction (normal m) -m Re phi' + 1/2 conj(m) conj(conj(z - c) phi'' - psi').
+// So a cluster is two complex series of kOrder terms.  About a source centre
 //   phi = a_0 log z + sum_{k>=1} a_k z^-k,  psi likewise (b_0 = conj(a_0));
 // about a target centre at t = c_t - c_s, z = t + x,
 //   alpha_l = (-1)^l t^-l [ sum_k C(l+k-1, l) a_k t^-k - a_0 / l ]
@@ -644,6 +648,8 @@ struct FarArgs {
     const FarBox *info;
     const double *coef, *txy;
     double *part;              // [2][nt], sorted targets
+    const int32_t *tidx;
+    const double *tnx, *tny;   // target normals (traction), caller's order
 };
 
 // One workgroup per target circle; its waves take the far nodes in turn.  Lane
@@ -689,7 +695,7 @@ __global__ __launch_bounds__(64 * kFarWaves) void far_far(FarArgs a) {
                     v.y = __builtin_fma(row[k], b.y, v.y);
                 }
             }
-            if (OP == S2D_OP_SLP) {
+            if (slp_sources(OP)) {
                 const C2 m0 = buf[wid][h][0];
                 const double c = l ? il : __builtin_fma(0.5, log64(q), -logs) - cst;
                 v.x = __builtin_fma(m0.x, c, v.x);
@@ -727,19 +733,38 @@ __global__ __launch_bounds__(64 * kFarWaves) void far_far(FarArgs a) {
     const int64_t p = (int64_t)(circle >> 1) * kTile + lane;
     if (lane < t.lo || lane >= t.hi) return;
     const C2 x{S * (a.txy[p] - t.x), S * (a.txy[a.nt + p] - t.y)};
-    C2 f{0.0, 0.0}, df{0.0, 0.0}, g{0.0, 0.0};
+    // phi, phi', phi'' / 2, psi, psi' by Horner's rule (unused ones drop out)
+    C2 f{0.0, 0.0}, df{0.0, 0.0}, d2{0.0, 0.0}, g{0.0, 0.0}, dg{0.0, 0.0};
+    const auto step = [&](C2 &v, C2 add) {
+        const C2 c = cmul(v, x);
+        v = C2{c.x + add.x, c.y + add.y};
+    };
     for (int k = kOrder - 1; k >= 0; --k) {
-        const C2 al = sum[0][0][k], be = sum[0][0][32 + k];
-        C2 c = cmul(df, x);
-        df = C2{c.x + f.x, c.y + f.y};
-        c = cmul(f, x);
-        f = C2{c.x + al.x, c.y + al.y};
-        c = cmul(g, x);
-        g = C2{c.x + be.x, c.y + be.y};
+        if (OP == S2D_OP_SLP_TRACTION) {
+            step(d2, df);
+            step(dg, g);
+        }
+        step(df, f);
+        step(f, sum[0][0][k]);
+        if (OP <= S2D_OP_DLP || OP == S2D_OP_SLP_TRACTION) step(g, sum[0][0][32 + k]);
     }
-    // phi - x conj(phi') + conj(psi)
-    a.part[p] = f.x - (x.x * df.x + x.y * df.y) + g.x;
-    a.part[a.nt + p] = f.y - (x.y * df.x - x.x * df.y) - g.y;
+    double ox, oy = 0.0;
+    if (OP <= S2D_OP_DLP) {
+        // phi - x conj(phi') + conj(psi)
+        ox = f.x - (x.x * df.x + x.y * df.y) + g.x;
+        oy = f.y - (x.y * df.x - x.x * df.y) - g.y;
+    } else if (OP == S2D_OP_SLP_TRACTION) {
+        const int32_t i = a.tidx[p];
+        const C2 m{a.tnx[i], a.tny[i]}, q = cmul(C2{x.x, -x.y}, d2);
+        // conj(m (conj(x) phi'' - psi')) / 2
+        const C2 v = cmul(m, C2{q.x - 0.5 * dg.x, q.y - 0.5 * dg.y});
+        ox = S * (v.x - m.x * df.x);
+        oy = S * (-v.y - m.y * df.x);
+    } else {
+        ox = (OP == S2D_OP_SLP_PRESSURE ? -2.0 : -4.0) * S * df.x;
+    }
+    a.part[p] = ox;
+    a.part[a.nt + p] = oy;
 }
 
 // ---------------------------------------------------------------------------
@@ -756,6 +781,7 @@ struct NearArgs {
     double *part;                          // planes [2][nt]: the far part, then the groups' when n_groups > 1
     const int32_t *tidx, *spos;
     const int32_t *on_curve, *on_node;     // NULL when no target sits on a source node (or n = 0 is not summed)
+    const double *tnx, *tny;               // target normals (traction)
 };
 
 // n_groups workgroups per target circle; their waves take the near leaves in
@@ -782,6 +808,8 @@ __global__ __launch_bounds__(64 * kNearWaves) void far_near(NearArgs a, FinalArg
         const int j = a.on_node[i];
         if (j >= 0 && j < a.ns) self = a.spos[j];
     }
+    const bool tr = OP == S2D_OP_SLP_TRACTION && act;
+    const double mx = tr ? a.tnx[i] : 0.0, my = tr ? a.tny[i] : 0.0;
     double ux = 0.0, uy = 0.0, lx = 0.0, ly = 0.0;
     far_walk<kNearWaves, false>(
         a.w, t, a.info->dmin, wid, lane, group * kNearWaves + wid, a.n_groups * kNearWaves, sh,
@@ -800,7 +828,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void far_near(NearArgs a, FinalArg
                         if constexpr (OP == S2D_OP_SLP)
                             slp64_src<1>(px, ty, s, ltab, lx, ly, ux, uy);
                         else
-                            dlp64_src<1>(px, ty, s, ux, uy);
+                            rat64<OP>(px[0], ty, s, mx, my, ux, uy);
                     }
                 }
             }
@@ -810,7 +838,7 @@ __global__ __launch_bounds__(64 * kNearWaves) void far_near(NearArgs a, FinalArg
                 if constexpr (OP == S2D_OP_SLP)
                     slp64_src<1>(px, ty, s, ltab, ax, ay, bx, by);
                 else
-                    dlp64_src<1>(px, ty, s, bx, by);
+                    rat64<OP>(px[0], ty, s, mx, my, bx, by);
                 const bool ok = u != own;
                 ux += ok ? bx : 0.0;
                 uy += ok ? by : 0.0;
@@ -951,12 +979,15 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
     return L;
 }
 
-// Both routes measured at vesicle and wall sources, images -1..1, far / direct
-// in FP64 / direct in FP32C, set-up included (ms): 2^25.7 pairs 0.24 / 0.28 /
-// 0.23; 2^27.2 0.21 / 0.31 / 0.25; 2^28.6 0.30 / 0.89 / 0.53; 2^31 0.42 / 3.7 /
-// 1.9; 2^33.5 0.70 / 19.3 / 9.8.
-bool far_worth(int64_t ns, int64_t nt) {
-    return ns >= 4096 && nt >= 1024 && ns * nt >= (int64_t)1 << 26 && ns + nt < (int64_t)1 << 28;
+// Velocities measured at vesicle and wall sources, images -1..1, far (set-up
+// included) / direct FP64 / direct FP32C, ms: 2^25.7 pairs 0.20 / 0.17 / 0.08;
+// 2^26.9 0.23 / 0.30 / 0.15; 2^27.7 0.24 / 0.45 / 0.23; 2^28.6 0.29 / 0.86 /
+// 0.39; 2^30.1 0.36 / 2.05 / 0.98; 2^33.5 0.68 / 18.9 / 8.7.  A direct sum
+// costs as much per image, the far-field one hardly more for three images than
+// for one; without the set-up (0.08 ms) the lines meet at half the size.
+bool far_worth(int mode, int64_t ns, int64_t nt, int n_img, bool reuse) {
+    const int64_t least = reuse ? (int64_t)3 << 25 : mode == S2D_FP64 ? (int64_t)3 << 26 : (int64_t)1 << 29;
+    return ns >= 2048 && nt >= 1024 && ns + nt < (int64_t)1 << 28 && ns * nt * std::min(n_img, 3) >= least;
 }
 
 hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_targets *t, void *ws,
@@ -991,8 +1022,9 @@ hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_
 
 namespace {
 template <int OP>
-hipError_t far_sum_t(const FarLayout &L, const s2d_curves *s, const s2d_targets *t, double d, int32_t img_lo,
-                     int32_t img_hi, FinalArgs f, void *ws, hipStream_t st) {
+hipError_t far_sum_t(const FarLayout &L, const s2d_curves *s, const s2d_targets *t, const double *tnx,
+                     const double *tny, double d, int32_t img_lo, int32_t img_hi, FinalArgs f, void *ws,
+                     hipStream_t st) {
     char *b = (char *)ws;
     const int32_t *idx = (const int32_t *)(b + far_sorted(L));
     const FarNode *node = (const FarNode *)(b + L.node), *tnode = (const FarNode *)(b + L.tnode);
@@ -1009,16 +1041,17 @@ hipError_t far_sum_t(const FarLayout &L, const s2d_curves *s, const s2d_targets 
         f.self = nullptr;
     }
     const P2mArgs pa{L.ns, L.n0, s->x, s->y, s->nx, s->ny, s->w, s->fx, s->fy, idx, node, info, b + L.rec, coef};
-    hipLaunchKernelGGL(far_p2m<OP>, dim3((unsigned)((L.n0 + 3) / 4)), dim3(256), 0, st, pa);
+    constexpr int BASE = slp_sources(OP) ? S2D_OP_SLP : S2D_OP_DLP;
+    hipLaunchKernelGGL(far_p2m<BASE>, dim3((unsigned)((L.n0 + 3) / 4)), dim3(256), 0, st, pa);
     hipLaunchKernelGGL(far_m2m, dim3((unsigned)L.n1), dim3(64 * kFan), 0, st, (int64_t)0, L.n0, kLeafFan, L.n0, node,
                        info, coef);
     hipLaunchKernelGGL(far_m2m, dim3((unsigned)L.n2), dim3(64 * kFan), 0, st, L.n0, L.n1, kFan, L.n0 + L.n1, node,
                        info, coef);
     const WalkArgs w{L.n0, L.n1, L.n2, node, d, img_lo, img_hi - img_lo + 1};
-    const FarArgs fa{w, L.nt, tnode, info, coef, txy, part};
+    const FarArgs fa{w, L.nt, tnode, info, coef, txy, part, idx + L.ns, tnx, tny};
     hipLaunchKernelGGL(far_far<OP>, dim3((unsigned)L.nT), dim3(64 * kFarWaves), 0, st, fa);
     const NearArgs na{w, L.ns, L.nt, L.groups, tnode, info, b + L.rec, txy, part, idx + L.ns,
-                      (const int32_t *)(b + L.spos), img0 ? t->on_curve : nullptr, img0 ? t->on_node : nullptr};
+                      (const int32_t *)(b + L.spos), img0 ? t->on_curve : nullptr, img0 ? t->on_node : nullptr, tnx, tny};
     hipLaunchKernelGGL(far_near<OP>, dim3((unsigned)(L.nT * L.groups)), dim3(64 * kNearWaves), 0, st, na, f);
     if (L.groups > 1)
         hipLaunchKernelGGL(far_final, dim3((unsigned)((L.nt + 255) / 256)), dim3(256), 0, st, L.nt, L.groups + 1, part,
@@ -1027,10 +1060,17 @@ hipError_t far_sum_t(const FarLayout &L, const s2d_curves *s, const s2d_targets 
 }
 }  // namespace
 
-hipError_t far_sum(int op, const FarLayout &L, const s2d_curves *s, const s2d_targets *t, double d, int32_t img_lo,
-                   int32_t img_hi, FinalArgs f, void *ws, hipStream_t st) {
-    return op == S2D_OP_SLP ? far_sum_t<S2D_OP_SLP>(L, s, t, d, img_lo, img_hi, f, ws, st)
-                            : far_sum_t<S2D_OP_DLP>(L, s, t, d, img_lo, img_hi, f, ws, st);
+hipError_t far_sum(int op, const FarLayout &L, const s2d_curves *s, const s2d_targets *t, const double *tnx,
+                   const double *tny, double d, int32_t img_lo, int32_t img_hi, FinalArgs f, void *ws,
+                   hipStream_t st) {
+    switch (op) {
+    case S2D_OP_SLP: return far_sum_t<S2D_OP_SLP>(L, s, t, tnx, tny, d, img_lo, img_hi, f, ws, st);
+    case S2D_OP_DLP: return far_sum_t<S2D_OP_DLP>(L, s, t, tnx, tny, d, img_lo, img_hi, f, ws, st);
+    case S2D_OP_SLP_PRESSURE: return far_sum_t<S2D_OP_SLP_PRESSURE>(L, s, t, tnx, tny, d, img_lo, img_hi, f, ws, st);
+    case S2D_OP_DLP_PRESSURE: return far_sum_t<S2D_OP_DLP_PRESSURE>(L, s, t, tnx, tny, d, img_lo, img_hi, f, ws, st);
+    case S2D_OP_SLP_TRACTION: return far_sum_t<S2D_OP_SLP_TRACTION>(L, s, t, tnx, tny, d, img_lo, img_hi, f, ws, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace s2d

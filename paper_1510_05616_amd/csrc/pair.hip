@@ -1,10 +1,11 @@
 // Single-call pair-sum kernel.  A workgroup of W waves owns one target tile
 // (kWave targets) and W consecutive source splits of one split group; its
 // waves evaluate pair_sum() (pair_impl.h) on their splits, and wave 0 adds the
-// W results in wave order through LDS.  With one split group (every source
-// in the workgroup) wave 0 then finishes the targets itself: the own-curve
-// Kress sums, the double layer's diagonal limit, the prefactor and the
-// accumulate flag, exactly as finalize() does.  With G > 1 groups it writes
+// W results in wave order through LDS.  The waves of the first group also sum
+// Kress's rule on their targets' own curves (single layer).  With one split
+// group (every source in the workgroup) wave 0 then finishes the targets
+// itself: the double layer's diagonal limit, the prefactor and the accumulate
+// flag, exactly as finalize() does.  With G > 1 groups it writes
 // the group's FP64 partial, and finalize() adds the G partials in order.
 //
 // blockIdx -> (tile, group): group = blockIdx % G, tile = blockIdx / G.  The
@@ -24,7 +25,7 @@ __global__ __launch_bounds__(kMaxPairWaves * kWave) __attribute__((amdgpu_waves_
 void pair_kernel(PairArgs a, FinalArgs f) {
     __shared__ __attribute__((aligned(16))) double ltab[kLogTabWords];
     __shared__ double red[2][kMaxPairWaves - 1][kWave];
-    if (PREC == S2D_FP64 && OP == S2D_OP_SLP) fill_log_table(ltab);
+    if (OP == S2D_OP_SLP && (PREC == S2D_FP64 || f.kress)) fill_log_table(ltab);
     const int lane = threadIdx.x & (kWave - 1);
     // wave index made wave-uniform for the compiler: the split, and with it
     // every source record address, must be uniform so records take the scalar path
@@ -35,6 +36,14 @@ void pair_kernel(PairArgs a, FinalArgs f) {
     const int64_t tile = blk / a.n_groups;
     double ox[1], oy[1];
     pair_sum<OP, PREC, 1, NI>(a, tile, group * W + wid, lane, ltab, ox, oy);
+    const int64_t i = tile * kWave + lane;
+    if (OP == S2D_OP_SLP && f.kress && group == 0 && i < a.n_trg) {
+        double sx, sy;
+        kress_self_one(i, f.n_src, f.on_curve, f.on_node, f.curve_off, f.n_curves, f.sx, f.sy, f.nx, f.ny, f.w, f.fx,
+                       f.fy, f.kress, ltab, sx, sy, wid, W);
+        ox[0] += sx;
+        oy[0] += sy;
+    }
     if (wid > 0) {
         red[0][wid - 1][lane] = ox[0];
         red[1][wid - 1][lane] = oy[0];
@@ -46,7 +55,6 @@ void pair_kernel(PairArgs a, FinalArgs f) {
         sx += red[0][w - 1][lane];
         sy += red[1][w - 1][lane];
     }
-    const int64_t i = tile * kWave + lane;
     if (i >= a.n_trg) return;
     if (a.n_groups > 1) {
         a.part[(int64_t)(2 * group) * a.n_trg + i] = sx;

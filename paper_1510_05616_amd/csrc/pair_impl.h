@@ -29,10 +29,12 @@
 // layer skips curve c at n = 0 (Kress's rule covers it elsewhere) and the
 // double layer skips node i at n = 0 (the diagonal limit covers it).  A wave
 // folds its targets' excluded index ranges into one hull; a superblock that
-// meets the hull in a group holding n = 0 takes a masked path that goes
-// image by image with a per-pair select (it also skips the padding records
-// past the last source).  All other superblocks, the ragged last one
-// included, take the unmasked path.
+// meets the hull in a group holding n = 0 takes a masked path: the same
+// grouped terms, with image 0 replaced by a neutral factor where a target
+// excludes the source or the record is padding.  (Going image by image with
+// one select per pair took 2.5 times as long, and small problems consist of
+// such superblocks.)  All other superblocks, the ragged last one included,
+// take the unmasked path.
 //
 // Precision.  FP64 mode evaluates each term in double.  FP32C mode evaluates
 // each term in float with the hardware log2 and reciprocal, sums a sub-block
@@ -195,17 +197,22 @@ constexpr double kHalfLn2 = 0.34657359027997265471;
 // FP64 single layer of one source at the NI target positions px[m] (the
 // target minus image m's shift) and height py: accumulates A += g log q
 // (one log of the product of the NI squared distances) and B += r (r.g)/q.
-template <int NI>
+// MASK: image m0 of the group is left out unless ok.
+template <int NI, bool MASK = false>
 __device__ __forceinline__ void slp64_src(const double (&px)[NI], double py, const RecSlp64 &s, const double *ltab,
-                                          double &ax, double &ay, double &bx, double &by) {
+                                          double &ax, double &ay, double &bx, double &by, bool ok = true,
+                                          int m0 = 0) {
     const double ry = py - s.y;
     const double ry2 = ry * ry, rgy = ry * s.gy;
     double P = 1.0, ts = 0.0;
 #pragma unroll
     for (int m = 0; m < NI; ++m) {
         const double rx = px[m] - s.x;
-        const double q = __builtin_fma(rx, rx, ry2);
-        const double t = __builtin_fma(rx, s.gx, rgy) * rcp64(q);
+        double q = __builtin_fma(rx, rx, ry2);
+        const bool use = !MASK || ok || m != m0;
+        if (MASK) q = use ? q : 1.0;
+        double t = __builtin_fma(rx, s.gx, rgy) * rcp64(q);
+        if (MASK) t = use ? t : 0.0;
         bx = __builtin_fma(rx, t, bx);
         ts = m == 0 ? t : ts + t;
         P = m == 0 ? q : P * q;
@@ -226,16 +233,18 @@ __device__ __forceinline__ void slp64_src(const double (&px)[NI], double py, con
 // accumulators take (-D g_x + C g_y, C g_x + D g_y), and the constant NI g_x
 // of the x component is added per superblock from its FP64 density sum.
 // With NI = 1 the term is taken directly (a[2], a[3] then hold the whole
-// rational term).
-template <int NI>
+// rational term).  MASK: image m0 is left out unless ok (its share of the
+// constant is then the caller's to take back).
+template <int NI, bool MASK = false>
 __device__ __forceinline__ void slp32_src(const float (&rx)[NI], float ry, float gx, float gy, float iqr,
-                                          float (&a)[4]) {
+                                          float (&a)[4], bool ok = true, int m0 = 0) {
     const float ry2 = ry * ry;
     if constexpr (NI == 1) {
         // one image: r (r.g)/q directly (cheaper than the shared form, and
         // no constant to add back)
-        const float q = __builtin_fmaf(rx[0], rx[0], ry2);
-        const float t = __builtin_fmaf(rx[0], gx, ry * gy) * __builtin_amdgcn_rcpf(q);
+        const bool use = !MASK || ok || m0 != 0;
+        const float q = use ? __builtin_fmaf(rx[0], rx[0], ry2) : 1.f;
+        const float t = use ? __builtin_fmaf(rx[0], gx, ry * gy) * __builtin_amdgcn_rcpf(q) : 0.f;
         a[2] = __builtin_fmaf(rx[0], t, a[2]);
         a[3] = __builtin_fmaf(ry, t, a[3]);
         const float lq = __builtin_amdgcn_logf(q * iqr);
@@ -246,8 +255,9 @@ __device__ __forceinline__ void slp32_src(const float (&rx)[NI], float ry, float
     float P = 1.f, s0 = 0.f, s1 = 0.f;
 #pragma unroll
     for (int m = NI - 1; m >= 0; --m) {
-        const float q = __builtin_fmaf(rx[m], rx[m], ry2);
-        const float iq = __builtin_amdgcn_rcpf(q);
+        const bool use = !MASK || ok || m != m0;
+        const float q = use ? __builtin_fmaf(rx[m], rx[m], ry2) : 1.f;
+        const float iq = use ? __builtin_amdgcn_rcpf(q) : 0.f;
         s0 = m == NI - 1 ? iq : s0 + iq;
         s1 = m == NI - 1 ? rx[m] * iq : __builtin_fmaf(rx[m], iq, s1);
         P = m == NI - 1 ? q * iqr : P * q;     // the scaled factor first
@@ -261,9 +271,9 @@ __device__ __forceinline__ void slp32_src(const float (&rx)[NI], float ry, float
 }
 
 // FP64 double layer of one source over NI images: u += r (r.nu)(r.tau)/q^2
-template <int NI>
+template <int NI, bool MASK = false>
 __device__ __forceinline__ void dlp64_src(const double (&px)[NI], double py, const RecDlp64 &s, double &ux,
-                                          double &uy) {
+                                          double &uy, bool ok = true, int m0 = 0) {
     const double ry = py - s.y;
     const double ry2 = ry * ry, rny = ry * s.ny, rty = ry * s.ty;
     double fs = 0.0;
@@ -274,7 +284,8 @@ __device__ __forceinline__ void dlp64_src(const double (&px)[NI], double py, con
         const double iq = rcp64(q);
         const double rn = __builtin_fma(rx, s.nx, rny);
         const double rt = __builtin_fma(rx, s.tx, rty);
-        const double f = (rn * rt) * (iq * iq);
+        double f = (rn * rt) * (iq * iq);
+        if (MASK) f = ok || m != m0 ? f : 0.0;
         ux = __builtin_fma(rx, f, ux);
         fs = m == 0 ? f : fs + f;
     }
@@ -283,8 +294,9 @@ __device__ __forceinline__ void dlp64_src(const double (&px)[NI], double py, con
 
 // FP32 double layer of one source for the differences (rx[m], ry),
 // accumulators a = {x, y}
-template <int NI>
-__device__ __forceinline__ void dlp32_src(const float (&rx)[NI], float ry, const RecDlp32 &s, float (&a)[2]) {
+template <int NI, bool MASK = false>
+__device__ __forceinline__ void dlp32_src(const float (&rx)[NI], float ry, const RecDlp32 &s, float (&a)[2],
+                                          bool ok = true, int m0 = 0) {
     const float ry2 = ry * ry, rny = ry * s.ny, rty = ry * s.ty;
     float fs = 0.f;
 #pragma unroll
@@ -293,7 +305,8 @@ __device__ __forceinline__ void dlp32_src(const float (&rx)[NI], float ry, const
         const float iq = __builtin_amdgcn_rcpf(q);
         const float rn = __builtin_fmaf(rx[m], s.nx, rny);
         const float rt = __builtin_fmaf(rx[m], s.tx, rty);
-        const float f = (rn * rt) * (iq * iq);
+        float f = (rn * rt) * (iq * iq);
+        if (MASK) f = ok || m != m0 ? f : 0.f;
         a[0] = __builtin_fmaf(rx[m], f, a[0]);
         fs = m == 0 ? f : fs + f;
     }
@@ -438,6 +451,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
 
     // superblock range of the split, wave-uniform: the loop runs on the scalar
     // unit and the record addresses it forms stay scalar (n_sb < 2^31)
+    const int sbs = a.sbs;
     const int sb0 = __builtin_amdgcn_readfirstlane((int)min((int64_t)split * a.sb_per_split, a.n_sb));
     const int sb1 = __builtin_amdgcn_readfirstlane((int)min((int64_t)sb0 + a.sb_per_split, a.n_sb));
 
@@ -456,17 +470,44 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
         const bool has0 = n0 <= 0 && 0 < n0 + NI;
 
         for (int sb = sb0; sb < sb1; ++sb) {
-            const int64_t j0 = (int64_t)sb * kSuperBlock;
-            const int64_t j1 = min(j0 + (int64_t)kSuperBlock, a.n_src);
+            const int64_t j0 = (int64_t)sb * sbs;
             // padding records are zero-density copies of the last source: a ragged
             // superblock needs no mask
-            const bool masked = has0 && hlo < hhi && j0 < hhi && (int64_t)hlo < j0 + kSuperBlock;
+            const bool masked = OP <= S2D_OP_DLP && has0 && hlo < hhi && j0 < hhi && (int64_t)hlo < j0 + sbs;
+            const int m0 = -n0;                            // the group's image 0
+            // FP32C single layer: the log reference factor
+            [[maybe_unused]] float iqr[TPT];
+            if constexpr (OP == S2D_OP_SLP && PREC == S2D_FP32C) {
+                const RecSlp32 *rec = (const RecSlp32 *)a.rec + j0;
+                // log reference: the superblock's first source at every image of the group
+                const double gsx = load_ro<double>(a.sbsum, 2 * sb), gsy = load_ro<double>(a.sbsum, 2 * sb + 1);
+                const RecSlp32 r0 = load_ro<RecSlp32>(rec, 0);
+#pragma unroll
+                for (int k = 0; k < TPT; ++k) {
+                    const double ry0 = py[k] - r0.y;
+                    double qp = 1.0;
+#pragma unroll
+                    for (int m = 0; m < NI; ++m) {
+                        const double rx0 = px[k][m] - r0.x;
+                        qp *= __builtin_fma(rx0, rx0, ry0 * ry0);
+                    }
+                    // iqr = 2^-e with qp = m 2^e, m in [1/2, 1): scaling by it is exact in
+                    // float, and -1/2 sum g ln prod q = -(ln2/2) sum g log2(iqr prod q)
+                    // - (ln2/2) e sum g
+                    const int e = min(max(__builtin_amdgcn_frexp_exp(qp), -100), 100);
+                    iqr[k] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
+                    const double c = -kHalfLn2 * (double)e;
+                    // and, for grouped images, the rational term's constant NI g_x (see slp32_src)
+                    ux[k] = __builtin_fma(c, gsx, NI > 1 ? __builtin_fma((double)NI, gsx, ux[k]) : ux[k]);
+                    uy[k] = __builtin_fma(c, gsy, uy[k]);
+                }
+            }
             if (!masked) {
                 // ---------------- unmasked superblock ----------------
                 if (PREC == S2D_FP64) {
                     if (OP == S2D_OP_SLP) {
                         const RecSlp64 *rec = (const RecSlp64 *)a.rec + j0;
-                        for (int u = 0; u < kSuperBlock; u += 4) {
+                        for (int u = 0; u < sbs; u += 4) {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
                                 const RecSlp64 s = load_ro<RecSlp64>(rec, u + q);
@@ -477,7 +518,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                         }
                     } else if (OP == S2D_OP_DLP) {
                         const RecDlp64 *rec = (const RecDlp64 *)a.rec + j0;
-                        for (int u = 0; u < kSuperBlock; u += 4) {
+                        for (int u = 0; u < sbs; u += 4) {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
                                 const RecDlp64 s = load_ro<RecDlp64>(rec, u + q);
@@ -488,7 +529,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                     } else {
                         using R = Rec64Of<OP>;
                         const R *rec = (const R *)a.rec + j0;
-                        for (int u = 0; u < kSuperBlock; u += 4) {
+                        for (int u = 0; u < sbs; u += 4) {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
                                 const R s = load_ro<R>(rec, u + q);
@@ -503,30 +544,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                 } else {
                     if (OP == S2D_OP_SLP) {
                         const RecSlp32 *rec = (const RecSlp32 *)a.rec + j0;
-                        // log reference: the superblock's first source at every image of the group
-                        float iqr[TPT];
-                        const double gsx = load_ro<double>(a.sbsum, 2 * sb), gsy = load_ro<double>(a.sbsum, 2 * sb + 1);
-                        const RecSlp32 r0 = load_ro<RecSlp32>(rec, 0);
-#pragma unroll
-                        for (int k = 0; k < TPT; ++k) {
-                            const double ry0 = py[k] - r0.y;
-                            double qp = 1.0;
-#pragma unroll
-                            for (int m = 0; m < NI; ++m) {
-                                const double rx0 = px[k][m] - r0.x;
-                                qp *= __builtin_fma(rx0, rx0, ry0 * ry0);
-                            }
-                            // iqr = 2^-e with qp = m 2^e, m in [1/2, 1): scaling by it is exact in
-                            // float, and -1/2 sum g ln prod q = -(ln2/2) sum g log2(iqr prod q)
-                            // - (ln2/2) e sum g
-                            const int e = min(max(__builtin_amdgcn_frexp_exp(qp), -100), 100);
-                            iqr[k] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
-                            const double c = -kHalfLn2 * (double)e;
-                            // and, for grouped images, the rational term's constant NI g_x (see slp32_src)
-                            ux[k] = __builtin_fma(c, gsx, NI > 1 ? __builtin_fma((double)NI, gsx, ux[k]) : ux[k]);
-                            uy[k] = __builtin_fma(c, gsy, uy[k]);
-                        }
-                        for (int u = 0; u < kSuperBlock; u += kSubBlock) {
+                        for (int u = 0; u < sbs; u += kSubBlock) {
                             // per target: [source parity][log x, log y, rat x, rat y]
                             float ac[TPT][2][4], dx[TPT][NI], dy[TPT];
 #pragma unroll
@@ -573,7 +591,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                         }
                     } else if (OP == S2D_OP_DLP) {
                         const RecDlp32 *rec = (const RecDlp32 *)a.rec + j0;
-                        for (int u = 0; u < kSuperBlock; u += kSubBlock) {
+                        for (int u = 0; u < sbs; u += kSubBlock) {
                             float ac[TPT][2][2], dx[TPT][NI], dy[TPT];     // [source parity][x, y]
 #pragma unroll
                             for (int k = 0; k < TPT; ++k)
@@ -615,7 +633,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                         // pressures and traction, FP32C
                         using R = Rec32Of<OP>;
                         const R *rec = (const R *)a.rec + j0;
-                        for (int u = 0; u < kSuperBlock; u += kSubBlock) {
+                        for (int u = 0; u < sbs; u += kSubBlock) {
                             float ac[TPT][2][2], dx[TPT][NI], dy[TPT];     // [source parity][x, y]
 #pragma unroll
                             for (int k = 0; k < TPT; ++k)
@@ -656,51 +674,44 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                         }
                     }
                 }
-            } else {
-                // ---------------- masked superblock (rare): image by image ----------------
-                for (int m = 0; m < NI; ++m) {
-                    const int n = n0 + m;
-                    for (int64_t j = j0; j < j0 + kSuperBlock; ++j) {
-                        const bool inrange = j < j1;
+            } else if constexpr (OP <= S2D_OP_DLP) {
+                // ---------------- masked superblock ----------------
+                // FP32C: FP32 terms from FP64 differences, each added in FP64
+#pragma unroll 2
+                for (int u = 0; u < sbs; ++u) {
+                    const int64_t j = j0 + u;
+                    bool ok[TPT];
+#pragma unroll
+                    for (int k = 0; k < TPT; ++k) ok[k] = j < a.n_src && (j < lo[k] || j >= hi[k]);
+                    if constexpr (PREC == S2D_FP64) {
+                        const Rec64Of<OP> s = load_ro<Rec64Of<OP>>(a.rec, j);
 #pragma unroll
                         for (int k = 0; k < TPT; ++k) {
-                            const bool ok = inrange && (n != 0 || j < lo[k] || j >= hi[k]);
-                            const double p1[1] = {px[k][m]};
-                            if (PREC == S2D_FP64) {
-                                if (OP == S2D_OP_SLP) {
-                                    const RecSlp64 s = load_ro<RecSlp64>(a.rec, j);
-                                    double ax = 0, ay = 0, bx = 0, by = 0;
-                                    slp64_src<1>(p1, py[k], s, ltab, ax, ay, bx, by);
-                                    vx[k] += ok ? ax : 0.0; vy[k] += ok ? ay : 0.0;
-                                    ux[k] += ok ? bx : 0.0; uy[k] += ok ? by : 0.0;
-                                } else {
-                                    const Rec64Of<OP> s = load_ro<Rec64Of<OP>>(a.rec, j);
-                                    double ax = 0, ay = 0;
-                                    rat64<OP>(px[k][m], py[k], s, mx[k], my[k], ax, ay);
-                                    ux[k] += ok ? ax : 0.0; uy[k] += ok ? ay : 0.0;
-                                }
+                            if constexpr (OP == S2D_OP_SLP)
+                                slp64_src<NI, true>(px[k], py[k], s, ltab, vx[k], vy[k], ux[k], uy[k], ok[k], m0);
+                            else
+                                dlp64_src<NI, true>(px[k], py[k], s, ux[k], uy[k], ok[k], m0);
+                        }
+                    } else {
+                        const Rec32Of<OP> s = load_ro<Rec32Of<OP>>(a.rec, j);
+#pragma unroll
+                        for (int k = 0; k < TPT; ++k) {
+                            float rx[NI];
+#pragma unroll
+                            for (int m = 0; m < NI; ++m) rx[m] = (float)(px[k][m] - s.x);
+                            const float ry = (float)(py[k] - s.y);
+                            if constexpr (OP == S2D_OP_SLP) {
+                                float t4[4] = {0.f, 0.f, 0.f, 0.f};
+                                slp32_src<NI, true>(rx, ry, s.gx, s.gy, iqr[k], t4, ok[k], m0);
+                                // the constant NI g_x counts image 0 only where it is summed
+                                const double cg = NI > 1 && !ok[k] ? (double)s.gx : 0.0;
+                                ux[k] += __builtin_fma(-kHalfLn2, (double)t4[0], (double)t4[2] - cg);
+                                uy[k] += __builtin_fma(-kHalfLn2, (double)t4[1], (double)t4[3]);
                             } else {
-                                if (OP == S2D_OP_SLP) {
-                                    const RecSlp32 s = load_ro<RecSlp32>(a.rec, j);
-                                    float t4[4] = {0.f, 0.f, 0.f, 0.f};
-                                    const float r1[1] = {(float)(px[k][m] - s.x)};
-                                    slp32_src<1>(r1, (float)(py[k] - s.y), s.gx, s.gy, 1.0f, t4);
-                                    ux[k] += ok ? __builtin_fma(-kHalfLn2, (double)t4[0], (double)t4[2]) : 0.0;
-                                    uy[k] += ok ? __builtin_fma(-kHalfLn2, (double)t4[1], (double)t4[3]) : 0.0;
-                                } else if constexpr (near_fp64(OP)) {
-                                    const Rec64Of<OP> s = load_ro<Rec64Of<OP>>(a.rec64, j);
-                                    double ax = 0, ay = 0;
-                                    rat64<OP>(px[k][m], py[k], s, mx[k], my[k], ax, ay);
-                                    ux[k] += ok ? ax : 0.0;
-                                    uy[k] += ok ? ay : 0.0;
-                                } else {
-                                    const Rec32Of<OP> s = load_ro<Rec32Of<OP>>(a.rec, j);
-                                    float t2[2] = {0.f, 0.f};
-                                    rat32<OP>((float)(px[k][m] - s.x), (float)(py[k] - s.y), s, (float)mx[k],
-                                              (float)my[k], t2);
-                                    ux[k] += ok ? (double)t2[0] : 0.0;
-                                    uy[k] += ok ? (double)t2[1] : 0.0;
-                                }
+                                float t2[2] = {0.f, 0.f};
+                                dlp32_src<NI, true>(rx, ry, s, t2, ok[k], m0);
+                                ux[k] += (double)t2[0];
+                                uy[k] += (double)t2[1];
                             }
                         }
                     }

@@ -43,12 +43,22 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
     constexpr size_t kL2Budget = (size_t)3 << 20;
     p.n_src = s->n_nodes;
     p.n_trg = t->n;
-    p.n_sb = (p.n_src + kSuperBlock - 1) / kSuperBlock;
     p.n_tiles = (p.n_trg + kWave - 1) / kWave;
+    // Superblocks of 256 sources give every wave its split when there are
+    // enough of them to fill the chip; few targets or sources leave waves idle
+    // then, and a split of 64 or 16 sources is shorter (576 targets and 512
+    // wall nodes: 2 waves of 256 sources a tile 126 us, 16 waves of 32 sources
+    // 22 us; 10,496 targets and 4,096 wall nodes 134 and 52 us).
+    const int64_t busy = (int64_t)cus * 16;
+    p.sbs = kSuperBlock;
+    while (p.sbs > kSubBlock && p.n_tiles * ((p.n_src + p.sbs - 1) / p.sbs) < busy) p.sbs /= 4;
+    p.n_sb = (p.n_src + p.sbs - 1) / p.sbs;
     if (p.n_sb > 0 && p.n_tiles > 0) {
-        const bool fits = (size_t)p.n_sb * kSuperBlock * rec_bytes(op, mode) <= kL2Budget;
+        const bool fits = (size_t)p.n_sb * p.sbs * rec_bytes(op, mode) <= kL2Budget;
         const int64_t fill = (int64_t)cus * 4 * 16;
-        const int64_t gmax = std::max<int64_t>(1, (p.n_sb + 7) / 8);
+        // a group's waves keep at least 64 sources each: more groups cost a
+        // partial plane each and the finalize launch
+        const int64_t gmax = std::min<int64_t>(64, std::max<int64_t>(1, p.n_src / (64 * kMaxPairWaves)));
         int64_t G = 1;
         if (!(fits && p.n_tiles * kMaxPairWaves >= fill))
             G = std::min<int64_t>(std::max<int64_t>(1, (fill + p.n_tiles * kMaxPairWaves - 1) /
@@ -74,24 +84,19 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
     p.self = false;    // set by the caller once images are known
     size_t off = 0;
     p.off_rec = off;
-    off = align256(off + (size_t)p.n_sb * kSuperBlock * rec_bytes(op, mode));
+    off = align256(off + (size_t)p.n_sb * p.sbs * rec_bytes(op, mode));
     p.off_rec64 = off;
     if (mode == S2D_FP32C && s2d::near_fp64(op))
-        off = align256(off + (size_t)p.n_sb * kSuperBlock * rec_bytes(op, S2D_FP64));
+        off = align256(off + (size_t)p.n_sb * p.sbs * rec_bytes(op, S2D_FP64));
     p.off_sub = off;
     if (mode == S2D_FP32C)
-        off = align256(off + (size_t)p.n_sb * (kSuperBlock / kSubBlock) * sizeof(s2d::SubInfo));
+        off = align256(off + (size_t)p.n_sb * (p.sbs / kSubBlock) * sizeof(s2d::SubInfo));
     p.off_sbsum = off;
     if (op == S2D_OP_SLP && mode == S2D_FP32C) off = align256(off + (size_t)p.n_sb * 2 * sizeof(double));
     p.off_part = off;
     if (p.n_groups > 1) off = align256(off + (size_t)p.n_groups * 2 * (size_t)p.n_trg * sizeof(double));
-    p.off_self = off;
     p.off_kress = off;
-    if (op == S2D_OP_SLP && t->on_curve && p.n_trg > 0) {
-        off = align256(off + 2 * (size_t)p.n_trg * sizeof(double));
-        p.off_kress = off;
-        off = align256(off + (size_t)p.n_src * sizeof(double));
-    }
+    if (op == S2D_OP_SLP && t->on_curve && p.n_trg > 0) off = align256(off + (size_t)p.n_src * sizeof(double));
     p.total = off;
     return p;
 }

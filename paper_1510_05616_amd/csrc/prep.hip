@@ -1,77 +1,83 @@
-// Source preparation kernels of a single evaluation (device code in
-// prep_impl.h).
+// Source preparation of a single evaluation (device code in prep_impl.h and
+// self_impl.h): records, superblock sums and Kress tables by one launch.  At
+// the sizes the direct sum serves each of these is a few microseconds of work,
+// less than a launch of its own.
 #include "prep_impl.h"
+#include "self_impl.h"
 
 namespace s2d {
 
-template <int OP, int PREC>
-__global__ __launch_bounds__(256) void prep_records(int64_t n_src, int64_t n_pad,
-                                                    const double *__restrict__ x, const double *__restrict__ y,
-                                                    const double *__restrict__ nx, const double *__restrict__ ny,
-                                                    const double *__restrict__ w,
-                                                    const double *__restrict__ fx, const double *__restrict__ fy,
-                                                    void *rec_out, SubInfo *sub) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (PREC == S2D_FP64) {
-        if (j >= n_pad) return;
-        prep_one64<OP>(j, n_src, x, y, nx, ny, w, fx, fy, rec_out);
-    } else {
-        if (j >= n_pad / kSubBlock) return;           // one thread per sub-block
-        prep_sub32<OP>(j, n_src, x, y, nx, ny, w, fx, fy, rec_out, sub);
-    }
-}
+struct PrepArgs {
+    int64_t n_src, n_pad, n_sb;
+    int sbs;
+    int32_t n_curves;
+    int64_t b_rec, b_sum;            // workgroups of records and of superblock sums; then one per curve
+    const int32_t *off;
+    const double *x, *y, *nx, *ny, *w, *fx, *fy;
+    void *rec, *rec64;
+    SubInfo *sub;
+    double *sbsum, *kress;
+};
 
-__global__ __launch_bounds__(256) void prep_sbsum(int64_t n_src, int64_t n_sb,
-                                                  const double *__restrict__ w,
-                                                  const double *__restrict__ fx, const double *__restrict__ fy,
-                                                  double *sbsum) {
-    const int64_t sb = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;   // a wave per superblock
-    if (sb >= n_sb) return;                                                           // wave-uniform
-    sbsum_wave(sb, n_src, w, fx, fy, sbsum, threadIdx.x & (kWave - 1));
+template <int OP, int PREC>
+__global__ __launch_bounds__(256) void prep(PrepArgs a) {
+    __shared__ double ctab[OP == S2D_OP_SLP ? kCosTab : 1];
+    const int64_t b = blockIdx.x;
+    if (b < a.b_rec) {
+        const int64_t j = b * 256 + threadIdx.x;
+        if (j >= a.n_pad) return;
+        if (PREC == S2D_FP64) {
+            prep_one64<OP>(j, a.n_src, a.x, a.y, a.nx, a.ny, a.w, a.fx, a.fy, a.rec);
+        } else {
+            prep_one32<OP>(j, a.n_src, a.x, a.y, a.nx, a.ny, a.w, a.fx, a.fy, a.rec, a.sub);
+            // FP64 records for the near sub-blocks of the pressures and traction
+            if (a.rec64) prep_one64<OP>(j, a.n_src, a.x, a.y, a.nx, a.ny, a.w, a.fx, a.fy, a.rec64);
+        }
+    } else if (b < a.b_rec + a.b_sum) {
+        const int64_t sb = (b - a.b_rec) * 4 + threadIdx.x / kWave;          // a wave per superblock
+        if (sb < a.n_sb)
+            sbsum_wave(sb, a.sbs, a.n_src, a.w, a.fx, a.fy, a.sbsum, threadIdx.x & (kWave - 1));
+    } else if constexpr (OP == S2D_OP_SLP) {
+        kress_table_curve(a.off, (int32_t)(b - a.b_rec - a.b_sum), a.n_src, a.kress, ctab);
+    }
 }
 
 template <int OP, int PREC>
 static hipError_t prep_t(const Plan &p, const s2d_curves *s, void *ws, hipStream_t st) {
-    const int64_t n_pad = p.n_sb * kSuperBlock;
-    if (n_pad == 0) return hipSuccess;
-    void *rec = (char *)ws + p.off_rec;
-    SubInfo *sub = (SubInfo *)((char *)ws + p.off_sub);
-    const int64_t nthr = PREC == S2D_FP64 ? n_pad : n_pad / kSubBlock;
-    hipLaunchKernelGGL((prep_records<OP, PREC>), dim3((unsigned)((nthr + 255) / 256)), dim3(256), 0, st,
-                       p.n_src, n_pad, s->x, s->y, s->nx, s->ny, s->w, s->fx, s->fy, rec, sub);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (OP == S2D_OP_SLP && PREC == S2D_FP32C) {
-        hipLaunchKernelGGL(prep_sbsum, dim3((unsigned)((p.n_sb + 3) / 4)), dim3(256), 0, st,
-                           p.n_src, p.n_sb, s->w, s->fx, s->fy, (double *)((char *)ws + p.off_sbsum));
-        e = hipGetLastError();
-    }
-    return e;
-}
-
-// FP64 records of the sources at p.off_rec64 (FP32C pressures and traction)
-template <int OP>
-static hipError_t prep_rec64(const Plan &p, const s2d_curves *s, void *ws, hipStream_t st) {
-    const int64_t n_pad = p.n_sb * kSuperBlock;
-    if (n_pad == 0) return hipSuccess;
-    hipLaunchKernelGGL((prep_records<OP, S2D_FP64>), dim3((unsigned)((n_pad + 255) / 256)), dim3(256), 0, st,
-                       p.n_src, n_pad, s->x, s->y, s->nx, s->ny, s->w, s->fx, s->fy, (char *)ws + p.off_rec64,
-                       (SubInfo *)nullptr);
+    char *b = (char *)ws;
+    PrepArgs a{};
+    a.n_src = p.n_src;
+    a.sbs = p.sbs;
+    a.n_sb = p.n_sb;
+    a.n_pad = p.n_sb * p.sbs;
+    a.off = s->curve_off;
+    a.x = s->x;
+    a.y = s->y;
+    a.nx = s->nx;
+    a.ny = s->ny;
+    a.w = s->w;
+    a.fx = s->fx;
+    a.fy = s->fy;
+    a.rec = b + p.off_rec;
+    a.rec64 = PREC == S2D_FP32C && near_fp64(p.op) ? b + p.off_rec64 : nullptr;
+    a.sub = (SubInfo *)(b + p.off_sub);
+    a.sbsum = (double *)(b + p.off_sbsum);
+    a.kress = (double *)(b + p.off_kress);
+    a.b_rec = (a.n_pad + 255) / 256;
+    a.b_sum = OP == S2D_OP_SLP && PREC == S2D_FP32C ? (p.n_sb + 3) / 4 : 0;
+    const int64_t blocks = a.b_rec + a.b_sum + (p.self ? s->n_curves : 0);
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL((prep<OP, PREC>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_prep(const Plan &p, const s2d_curves *s, void *ws, hipStream_t st) {
-    if (p.mode == S2D_FP32C && near_fp64(p.op)) {
-        const hipError_t e = slp_sources(p.op) ? prep_rec64<S2D_OP_SLP_PRESSURE>(p, s, ws, st)
-                                               : prep_rec64<S2D_OP_DLP>(p, s, ws, st);
-        if (e != hipSuccess) return e;
-    }
-    if (p.op == S2D_OP_SLP)
-        return p.mode == S2D_FP64 ? prep_t<S2D_OP_SLP, S2D_FP64>(p, s, ws, st) : prep_t<S2D_OP_SLP, S2D_FP32C>(p, s, ws, st);
+    const bool f64 = p.mode == S2D_FP64;
+    if (p.op == S2D_OP_SLP) return f64 ? prep_t<S2D_OP_SLP, S2D_FP64>(p, s, ws, st) : prep_t<S2D_OP_SLP, S2D_FP32C>(p, s, ws, st);
     if (slp_sources(p.op))       // pressure and traction of the single layer: same records, no log sums
-        return p.mode == S2D_FP64 ? prep_t<S2D_OP_SLP_PRESSURE, S2D_FP64>(p, s, ws, st)
-                                  : prep_t<S2D_OP_SLP_PRESSURE, S2D_FP32C>(p, s, ws, st);
-    return p.mode == S2D_FP64 ? prep_t<S2D_OP_DLP, S2D_FP64>(p, s, ws, st) : prep_t<S2D_OP_DLP, S2D_FP32C>(p, s, ws, st);
+        return f64 ? prep_t<S2D_OP_SLP_PRESSURE, S2D_FP64>(p, s, ws, st)
+                   : prep_t<S2D_OP_SLP_PRESSURE, S2D_FP32C>(p, s, ws, st);
+    return f64 ? prep_t<S2D_OP_DLP, S2D_FP64>(p, s, ws, st) : prep_t<S2D_OP_DLP, S2D_FP32C>(p, s, ws, st);
 }
 
 }  // namespace s2d

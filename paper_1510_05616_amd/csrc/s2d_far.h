@@ -1,4 +1,4 @@
-// Far-field summation (far.hip): large velocity sums of the layers by near
+// Far-field summation (far.hip): large sums of the layers by near
 // tiles taken term by term and far clusters through truncated expansions, all
 // in FP64.
 #pragma once
@@ -6,8 +6,7 @@
 
 namespace s2d {
 
-// Sizes and workspace carve-up of one (sources, targets) pair; op S2D_OP_SLP
-// or S2D_OP_DLP.
+// Sizes and workspace carve-up of one (sources, targets) pair.
 struct FarLayout {
     int64_t ns, nt;            // sources, targets
     int64_t n0, n1, n2, nT;    // source nodes of the three levels, target circles
@@ -20,8 +19,9 @@ struct FarLayout {
 
 FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve);
 
-// Whether the far-field sum is the faster route for these sizes.
-bool far_worth(int64_t ns, int64_t nt);
+// Whether the far-field sum is the faster route for these sizes and images;
+// reuse: one set-up serves several densities.
+bool far_worth(int mode, int64_t ns, int64_t nt, int n_img, bool reuse);
 
 // Orders sources and targets along a space-filling curve and boxes their
 // tiles; with Kress's tables when the single layer's targets sit on curves.
@@ -33,7 +33,9 @@ hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *src, const s2
 // The sum over images img_lo..img_hi for the densities in src, finished and
 // written (or added) as `f` says (FinalArgs of the same operator; self and
 // part are set here).
-hipError_t far_sum(int op, const FarLayout &L, const s2d_curves *src, const s2d_targets *trg, double d,
-                   int32_t img_lo, int32_t img_hi, FinalArgs f, void *ws, hipStream_t st);
+// tnx, tny: the targets' normals (traction only).
+hipError_t far_sum(int op, const FarLayout &L, const s2d_curves *src, const s2d_targets *trg, const double *tnx,
+                   const double *tny, double d, int32_t img_lo, int32_t img_hi, FinalArgs f, void *ws,
+                   hipStream_t st);
 
 }  // namespace s2d

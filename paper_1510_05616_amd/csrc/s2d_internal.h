@@ -16,7 +16,8 @@ constexpr int kWave = 64;            // CDNA wavefront width
 constexpr int kWavesPerBlock = 4;    // batched pair kernel: 4 independent waves per workgroup
 constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr int kMaxPairWaves = 16;    // single-call pair kernel: up to 16 waves (splits) per target tile
-constexpr int kSuperBlock = 256;     // sources per superblock (split granularity, FP32 log reference)
+constexpr int kSuperBlock = 256;     // sources per superblock (split granularity, FP32 log reference); small
+                                     // single calls take 64 or 16 (plan.hip)
 constexpr int kSubBlock = 16;        // FP32 sub-block: local origin, merged into the FP64 accumulators
 constexpr double kFarRadii = 4.0;    // a sub-block is far from a target beyond this many radii
 constexpr int kMaxImages = 64;
@@ -36,7 +37,8 @@ struct SubInfo { double ox, oy, r2; };
 struct Plan {
     int op, mode, tpt;
     int64_t n_src, n_trg;
-    int64_t n_sb;            // superblocks (sources padded to kSuperBlock)
+    int sbs;                 // sources per superblock
+    int64_t n_sb;            // superblocks (sources padded to a whole number)
     int64_t n_tiles;         // target tiles of kWave targets
     int waves;               // waves (splits) per workgroup, <= kMaxPairWaves
     int n_groups;            // split groups: workgroups per tile, partial planes when > 1
@@ -45,7 +47,7 @@ struct Plan {
     int64_t n_blocks;        // workgroups of the pair kernel
     bool self;               // targets carry on_curve/on_node and image 0 is in range
     // workspace carve-out (byte offsets)
-    size_t off_rec, off_rec64, off_sub, off_sbsum, off_part, off_self, off_kress, total;
+    size_t off_rec, off_rec64, off_sub, off_sbsum, off_part, off_kress, total;
 };
 
 struct PairArgs {
@@ -62,6 +64,7 @@ struct PairArgs {
     int32_t n_groups;         // single-call kernel: split groups (partial planes when > 1)
     int64_t sb_per_split;
     int64_t n_sb;
+    int32_t sbs;              // sources per superblock
     double d;
     int32_t img_lo, img_hi;
     double *part;             // single call: [n_groups][2][n_trg]; batched: [n_splits][2][n_trg]
@@ -89,7 +92,9 @@ constexpr bool slp_sources(int op) {
 
 struct FinalArgs {
     const double *part;
-    const double *self;       // SLP own-curve Kress sums [2][n_trg] or NULL
+    const double *self;       // own-curve terms [2][n_trg] summed elsewhere (far-field route) or NULL
+    const double *kress;      // Kress table: the pair kernel sums Kress's rule itself; or NULL
+    const double *sx, *sy;    // source nodes
     int32_t n_parts;          // partial planes of part
     int64_t n_trg;
     int64_t n_src;
@@ -107,8 +112,6 @@ struct FinalArgs {
 // launchers (return hipError_t of the launch)
 hipError_t launch_prep(const Plan &p, const s2d_curves *src, void *ws, hipStream_t st);
 hipError_t launch_pair(const Plan &p, const PairArgs &a, const FinalArgs &f, hipStream_t st);
-hipError_t launch_kress(const Plan &p, const s2d_curves *src, const s2d_targets *trg,
-                        void *ws, hipStream_t st);
 hipError_t launch_final(const Plan &p, const FinalArgs &a, hipStream_t st);
 
 // the rocBLAS handle of the current device bound to stream st (a
@@ -117,16 +120,21 @@ hipError_t launch_final(const Plan &p, const FinalArgs &a, hipStream_t st);
 std::mutex &blas_mutex();
 void *blas_handle(hipStream_t st, std::string &err);
 
-// One layer sum (api.hip): the direct one, or for velocities, where the sizes
-// favour it and the workspace holds it, the far-field sum (FP64 in either mode).
-// ready, when given, is false before the first call for a geometry and then
-// lets later calls with the same nodes, targets and workspace keep the set-up.
+// One layer sum (api.hip): the direct one, or where the sizes favour it and the
+// workspace holds it, the far-field sum (FP64 in either mode).
 // direct_workspace: the least a call needs.
+struct LayerOpts {
+    // when given: false before the first call for a geometry, and then lets
+    // later calls with the same nodes, targets and workspace keep the set-up
+    bool *ready = nullptr;
+    bool may_profile = true;
+    const double *tnx = nullptr, *tny = nullptr;      // target normals (traction)
+};
 size_t direct_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg);
 size_t layer_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg);
 int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
                int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
-               void *stream, bool *ready = nullptr, bool may_profile = true);
+               void *stream, const LayerOpts &o = LayerOpts{});
 
 // error state and device checks shared by the entry points (api.hip):
 // set_error records the calling thread's message and returns code;

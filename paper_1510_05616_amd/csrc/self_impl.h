@@ -16,9 +16,11 @@
 //   T_j = -(N / 4 pi) R_j + log(2 |sin(pi j / N)|)   (j != 0),
 //   -(N / 4 pi) R_j = sum_{p=1}^{m-1} cos(2 pi p j / N) / p + (-1)^j / N.
 // The table is built per curve (one workgroup each, cosines staged in LDS);
-// the sum runs one thread per target, in FP64 in every mode, with the pair
-// kernels' table log and one-step reciprocal (absolute error below 1e-15 and
-// about 2e-15 relative).
+// the sum runs in FP64 in every mode, with the pair kernels' table log and
+// one-step reciprocal (absolute error below 1e-15 and about 2e-15 relative):
+// a lane per target, and in the pair kernel the waves of a target tile take
+// the curve's nodes in turn (one thread per target over all nodes, a launch of
+// its own, took 34 us on curves of 64 nodes and 57 us on 128).
 //
 // Double layer: the n = 0 term of a target's own node is the diagonal limit
 // -(kappa / 2 pi) t t^T tau w (Section 2.3), added in the final reduction.
@@ -55,8 +57,8 @@ __device__ __forceinline__ void kress_table_curve(const int32_t *__restrict__ of
     }
 }
 
-// Own-curve Kress sum for target i (0 when the target is free); ltab: the
-// LDS log table (fill_log_table).
+// Own-curve Kress sum for target i (0 when the target is free) over the
+// curve's nodes k0, k0 + step, ...; ltab: the LDS log table (fill_log_table).
 __device__ __forceinline__ void kress_self_one(int64_t i, int64_t n_src, const int32_t *__restrict__ on_curve,
                                                const int32_t *__restrict__ on_node,
                                                const int32_t *__restrict__ off, int32_t n_curves,
@@ -65,7 +67,7 @@ __device__ __forceinline__ void kress_self_one(int64_t i, int64_t n_src, const i
                                                const double *__restrict__ w,
                                                const double *__restrict__ fx, const double *__restrict__ fy,
                                                const double *__restrict__ T, const double *ltab, double &sx,
-                                               double &sy) {
+                                               double &sy, int k0 = 0, int step = 1) {
     const int c = on_curve[i];
     sx = 0.0;
     sy = 0.0;
@@ -82,7 +84,7 @@ __device__ __forceinline__ void kress_self_one(int64_t i, int64_t n_src, const i
     }
     const int ii = gi - lo;
     const double xi = x[gi], yi = y[gi];
-    for (int k = 0; k < N; ++k) {
+    for (int k = k0; k < N; k += step) {
         const int gk = lo + k;
         const double gx = w[gk] * fx[gk], gy = w[gk] * fy[gk];
         double coef, rrx, rry;

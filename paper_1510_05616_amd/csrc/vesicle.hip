@@ -980,7 +980,7 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
     }
     L.need = o;
     L.far = o;
-    if (far_worth(n, n)) {
+    if (far_worth(S2D_FP64, n, n, p->img_hi - p->img_lo + 1, true)) {
         L.far_bytes = far_layout(S2D_OP_SLP, n, n, true).total;
         o += al256(L.far_bytes);
     }
@@ -1149,7 +1149,7 @@ int apply(StepCtx &C, const double *z, double *out, int mode) {
     if (C.far)
         // one geometry for every density of the solve: ordered and boxed once
         S2D_TRY(layer_eval(S2D_OP_SLP, mode, &C.src, &C.trg, C.p->d, C.p->img_lo, C.p->img_hi, C.p->mu, out,
-                           out + C.n, 1, C.ws + C.L.far, C.L.far_bytes, C.st, &C.far_ready));
+                           out + C.n, 1, C.ws + C.L.far, C.L.far_bytes, C.st, LayerOpts{&C.far_ready}));
     else
         S2D_TRY(stokes2d_slp_eval(mode, &C.src, &C.trg, C.p->d, C.p->img_lo, C.p->img_hi, C.p->mu, out, out + C.n, 1,
                                   C.ws + C.L.slp, C.L.slp_bytes, C.st));

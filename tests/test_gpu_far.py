@@ -35,10 +35,10 @@ def _close(a, b):
     assert e < 1e-12
 
 
-# 86 x 96 = 8,256 nodes: just past the rule; ragged sets with a last tile of
-# one node (sizes sum to 64 k + 1 never, all even: of 2); one far image alone
-@pytest.mark.parametrize("nv,sizes,img", [(86, (96,), (-1, 1)), (173, (50, 34, 66), (-1, 1)), (173, (50,), (0, 0)),
-                                          (141, (64, 62), (-2, 1)), (97, (98,), (1, 1)), (300, (96,), (-1, 1))])
+# 61 x 96 = 5,856 nodes: just past the rule for three images; ragged sets, a
+# last tile of two nodes; one image, which needs more nodes; one far image alone
+@pytest.mark.parametrize("nv,sizes,img", [(61, (96,), (-1, 1)), (173, (50, 34, 66), (-1, 1)), (210, (50,), (0, 0)),
+                                          (141, (64, 62), (-2, 1)), (105, (98,), (1, 1)), (300, (96,), (-1, 1))])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_step_operator(nv, sizes, img, mode):
     import torch
@@ -132,9 +132,8 @@ def _mixed(seed, nv, sizes, n_free):
 
 
 @pytest.mark.parametrize("op", [0, 1])
-@pytest.mark.parametrize("mode", [0, 1])
-@pytest.mark.parametrize("nv,sizes,n_free,img", [(200, (58, 64), 1, (-1, 1)), (90, (96, 46), 7400, (0, 0)),
-                                                 (400, (62,), 3001, (0, 2))])
+@pytest.mark.parametrize("mode,nv,sizes,n_free,img", [(0, 200, (58, 64), 1, (-1, 1)), (0, 330, (96, 46), 12001, (0, 0)),
+                                                      (1, 330, (96, 46), 12001, (0, 0)), (1, 400, (62,), 3001, (0, 2))])
 def test_eval_routes(op, mode, nv, sizes, n_free, img):
     import torch
     import oracle
@@ -223,3 +222,46 @@ def test_noalloc_beyond_the_far_scratch():
     torch.cuda.synchronize()
     assert not torch.equal(far, direct)
     _close(far, direct)
+
+
+@pytest.mark.parametrize("mode,nv,sizes,n_free,img", [(0, 120, (62, 64), 9001, (-1, 1)), (1, 300, (96, 50), 9001, (-1, 1)),
+                                                      (0, 200, (96,), 12001, (1, 1))])
+def test_pressure_and_traction_routes(mode, nv, sizes, n_free, img):
+    import torch
+    import oracle
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    cs, tx, ty, oc, on, d = _mixed(nv, nv, sizes, n_free)
+    tx, ty = tx[-n_free:], ty[-n_free:]
+    src, t = s2d.Curves(cs), s2d.Targets(tx, ty)
+    ang = np.random.default_rng(2).uniform(0, 2 * np.pi, n_free)
+    nx, ny = (torch.as_tensor(f(ang), device="cuda") for f in (np.cos, np.sin))
+    idx = np.random.default_rng(3).choice(n_free, 200, replace=False)
+    print(f"mode {mode}: {src.n_nodes} sources, {n_free} targets, images {img}", flush=True)
+
+    def run(op, m, size):
+        o = torch.full((2, t.n), 0.5, dtype=torch.float64, device="cuda")
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        if op == s2d.S2D_OP_SLP_PRESSURE:
+            s2d.stokes2d_slp_pressure_eval(m, src, t, d, img[0], img[1], o[0], 1, ws)
+        elif op == s2d.S2D_OP_DLP_PRESSURE:
+            s2d.stokes2d_dlp_pressure_eval(m, src, t, d, img[0], img[1], 0.7, o[0], 1, ws)
+        else:
+            s2d.stokes2d_slp_traction_eval(m, src, t, nx, ny, d, img[0], img[1], o[0], o[1], 1, ws)
+        torch.cuda.synchronize()
+        return o - 0.5
+
+    refs = {s2d.S2D_OP_SLP_PRESSURE: lambda: (oracle.slp_pressure(cs, tx[idx], ty[idx], d, img[0], img[1]),),
+            s2d.S2D_OP_DLP_PRESSURE: lambda: (oracle.dlp_pressure(cs, tx[idx], ty[idx], d, img[0], img[1], 0.7),),
+            s2d.S2D_OP_SLP_TRACTION: lambda: oracle.slp_traction(cs, tx[idx], ty[idx], np.cos(ang[idx]), np.sin(ang[idx]),
+                                                                 d, img[0], img[1])}
+    for op, ref in refs.items():
+        need = s2d.stokes2d_workspace_size(op, mode, src, t)
+        far, direct = run(op, mode, need), run(op, 0, need - 256)
+        if op != s2d.S2D_OP_SLP_TRACTION:
+            assert torch.equal(far[1], torch.zeros_like(far[1]))
+        _close(far, direct)
+        r = np.array(ref())
+        e = np.abs(far.cpu().numpy()[:len(r), idx] - r).max() / np.abs(r).max()
+        print(f"op {op} against the oracle {e:.1e}", flush=True)
+        assert e < 1e-12
