@@ -252,17 +252,44 @@ __global__ __launch_bounds__(kVesBlock) void ves_measure_kernel(int64_t n, const
     }
 }
 
+// (out_a, out_b) = D_s of (va, vb): the two components side by side over the
+// block's threads, D's antisymmetry (dtab[N - l] = -dtab[l], dtab[N / 2] = 0)
+// pairing the nodes m - l and m + l; a, b distinct from the outputs
+__device__ void dsv2(const double *va, const double *vb, double *oa, double *ob, const double *dtab, const double *sp,
+                     int N) {
+    const int h = N / 2;
+    for (int idx = threadIdx.x; idx < 2 * N; idx += blockDim.x) {
+        const bool second = idx >= N;
+        const int m = second ? idx - N : idx;
+        const double *v = second ? vb : va;
+        double a0 = 0.0, a1 = 0.0;
+        int lo = m == 0 ? N - 1 : m - 1, hi = m == N - 1 ? 0 : m + 1;
+        for (int l = 1; l < h; ++l) {
+            const double t = dtab[l] * (v[lo] - v[hi]);
+            if (l & 1) a0 += t; else a1 += t;
+            lo = lo == 0 ? N - 1 : lo - 1;
+            hi = hi == N - 1 ? 0 : hi + 1;
+        }
+        (second ? ob : oa)[m] = (a0 + a1) / sp[m];
+    }
+}
+
 // Pre-pass of the step operator.  From z = [u_x; u_y; sigma] (OP) or the
 // shape (RHS), per curve:
 //   OP:  density f = dt kappa_B D_s^4 u - D_s(sigma x_s), out rows 1-2 = u,
 //        out row 3 = x_s . D_s u
 //   RHS: density f = -kappa_B D_s^4 x, out rows 1-2 = u_resp (or 0),
 //        out row 3 = (L0 - L) / (dt L) (or 0)
-// The single layer of f is added to rows 1-2 afterwards.
+// The single layer of f is added to rows 1-2 afterwards.  Speeds and tangents
+// come from the call's geometry pass; five derivative passes in LDS are all
+// that is left per application, bound by their LDS reads (one thread a node,
+// full-length sums and the geometry anew took 162 us on 1,000 curves of 96
+// nodes; this takes 22 us).
 struct OpArgs {
     int64_t n;
     const int32_t *off;
     const double *x, *y;
+    const double *geo;               // speed, w, nx, ny, tx, ty ([n] each)
     const double *z;                 // OP input [3n]
     double dt, kb;
     const double *L0, *urx, *ury;    // RHS inputs
@@ -272,8 +299,8 @@ struct OpArgs {
 
 template <bool RHS>
 __global__ __launch_bounds__(kVesBlock) void ves_op_kernel(OpArgs a) {
-    __shared__ double dtab[kVesMaxN], lx[kVesMaxN], ly[kVesMaxN], xa[kVesMaxN], ya[kVesMaxN], sp[kVesMaxN],
-        tx[kVesMaxN], ty[kVesMaxN], ua[kVesMaxN], ub[kVesMaxN], va[kVesMaxN], vb[kVesMaxN];
+    __shared__ double dtab[kVesMaxN], sp[kVesMaxN], tx[kVesMaxN], ty[kVesMaxN], ua[kVesMaxN], ub[kVesMaxN],
+        va[kVesMaxN], vb[kVesMaxN];
     __shared__ double red[kVesBlock];
     const int64_t n = a.n;
     const CurveRange r = curve_range(a.off, n);
@@ -282,25 +309,23 @@ __global__ __launch_bounds__(kVesBlock) void ves_op_kernel(OpArgs a) {
         curve_nan(r, n, a.out, a.out + n, a.out + 2 * n);
         return;
     }
-    fill_dtab(dtab, r.N);
-    __syncthreads();
-    load_geometry(r, a.x, a.y, lx, ly, xa, ya, sp, tx, ty, dtab);
     const int N = r.N;
-    // ua, va <- the field to differentiate four times
+    fill_dtab(dtab, N);
+    // ua, va <- the field to differentiate four times (positions relative to
+    // the curve's first node)
+    const double x0 = a.x[r.lo], y0 = a.y[r.lo];
     for (int m = threadIdx.x; m < N; m += blockDim.x) {
-        if (RHS) {
-            ua[m] = lx[m];
-            va[m] = ly[m];
-        } else {
-            ua[m] = a.z[r.lo + m];
-            va[m] = a.z[n + r.lo + m];
-        }
+        const int64_t i = r.lo + m;
+        sp[m] = a.geo[i];
+        tx[m] = a.geo[4 * n + i];
+        ty[m] = a.geo[5 * n + i];
+        ua[m] = RHS ? a.x[i] - x0 : a.z[i];
+        va[m] = RHS ? a.y[i] - y0 : a.z[n + i];
     }
     __syncthreads();
     double *p = ua, *q = va, *tp = ub, *tq = vb;
     for (int k = 0; k < 4; ++k) {
-        dsv(p, tp, dtab, sp, N);
-        dsv(q, tq, dtab, sp, N);
+        dsv2(p, q, tp, tq, dtab, sp, N);
         __syncthreads();
         if (!RHS && k == 0) {
             // constraint row x_s . D_s u
@@ -325,23 +350,24 @@ __global__ __launch_bounds__(kVesBlock) void ves_op_kernel(OpArgs a) {
             a.out[2 * n + i] = alc;
         }
     } else {
-        // tension part: D_s(sigma x_s)
-        for (int m = threadIdx.x; m < N; m += blockDim.x) {
-            const double s = a.z[2 * n + r.lo + m];
-            xa[m] = s * tx[m];
-            ya[m] = s * ty[m];
-        }
-        __syncthreads();
-        dsv(xa, tp, dtab, sp, N);
-        dsv(ya, tq, dtab, sp, N);
-        __syncthreads();
+        // tension part: D_s(sigma x_s), added to the bending part as it comes
         const double c = a.dt * a.kb;
         for (int m = threadIdx.x; m < N; m += blockDim.x) {
             const int64_t i = r.lo + m;
-            a.fx[i] = c * p[m] - tp[m];
-            a.fy[i] = c * q[m] - tq[m];
+            const double s = a.z[2 * n + i];
+            tp[m] = s * tx[m];
+            tq[m] = s * ty[m];
+            a.fx[i] = c * p[m];
+            a.fy[i] = c * q[m];
             a.out[i] = a.z[i];
             a.out[n + i] = a.z[n + i];
+        }
+        __syncthreads();
+        dsv2(tp, tq, p, q, dtab, sp, N);
+        __syncthreads();
+        for (int m = threadIdx.x; m < N; m += blockDim.x) {
+            a.fx[r.lo + m] -= p[m];
+            a.fy[r.lo + m] -= q[m];
         }
     }
 }
@@ -564,27 +590,34 @@ __global__ __launch_bounds__(kVesBlock) void pc_fill_ds(PcArgs a) {
         if (j < N && k < N && j != k) v = dtab[(j - k + N) % N] / a.sp[r.lo + j];
         Dm[idx] = v;
     }
+    // one (i, k) per thread: the logarithm and quotient serve all four entries
     const int M2 = 2 * Nm;
-    for (int idx = threadIdx.x; idx < M2 * M2; idx += blockDim.x) {
-        const int row = idx % M2, col = idx / M2;
-        const int ra = row / Nm, i = row % Nm, cb = col / Nm, k = col % Nm;
-        double v = 0.0;
+    for (int idx = threadIdx.x; idx < Nm * Nm; idx += blockDim.x) {
+        const int i = idx % Nm, k = idx / Nm;
+        double coef = 0.0, xx = 0.0, xy = 0.0, yy = 0.0, f = 0.0;
         if (i < N && k < N) {
             const int64_t gi = r.lo + i, gk = r.lo + k;
-            double coef, R;
             if (i == k) {
                 coef = a.T[r.lo] - log(a.w[gk] * (double)N * 0.15915494309189535);
-                const double na = ra == 0 ? a.nx[gk] : a.ny[gk], nb = cb == 0 ? a.nx[gk] : a.ny[gk];
-                R = (ra == cb ? 1.0 : 0.0) - na * nb;
+                const double nx = a.nx[gk], ny = a.ny[gk];
+                xx = 1.0 - nx * nx;
+                xy = -nx * ny;
+                yy = 1.0 - ny * ny;
             } else {
                 const double rx = a.x[gi] - a.x[gk], ry = a.y[gi] - a.y[gk];
                 const double q = rx * rx + ry * ry;
                 coef = a.T[r.lo + (i - k + N) % N] - 0.5 * log(q);
-                R = (ra == 0 ? rx : ry) * (cb == 0 ? rx : ry) / q;
+                xx = rx * rx / q;
+                xy = rx * ry / q;
+                yy = ry * ry / q;
             }
-            v = a.pref * a.w[gk] * ((ra == cb ? coef : 0.0) + R);
+            f = a.pref * a.w[gk];
         }
-        Sm[idx] = v;
+        double *o = Sm + i + (int64_t)k * M2;
+        o[0] = f * (coef + xx);
+        o[Nm] = f * xy;
+        o[(int64_t)Nm * M2] = f * xy;
+        o[(int64_t)Nm * M2 + Nm] = f * (coef + yy);
     }
 }
 
@@ -631,28 +664,129 @@ __global__ __launch_bounds__(kVesBlock) void pc_fill_p(PcArgs a) {
     }
 }
 
-// padded per-curve right-hand sides from a [3n] vector, and back
-__global__ __launch_bounds__(256) void pc_gather(int64_t n, const int32_t *off, int Nm, const double *v,
-                                                 double *rhs) {
-    const int c = blockIdx.x;
-    const int64_t lo = off[c];
-    const int N = (int)(off[c + 1] - lo);
-    double *o = rhs + (int64_t)c * 3 * Nm;
-    for (int idx = threadIdx.x; idx < 3 * Nm; idx += blockDim.x) {
-        const int ab = idx / Nm, m = idx % Nm;
-        o[idx] = m < N ? v[ab * n + lo + m] : 0.0;
+// Readies the factored blocks for pc_solve, one workgroup per curve: the row
+// interchanges composed into a permutation (over ipiv: row r of P_c z = v reads
+// v[ipiv[r]]), and each kTri x kTri diagonal block's two triangles replaced by
+// their inverses (L's unit diagonal implied).  A wave inverts a block: lane c
+// column c of L^-1, lane 32 + c column c of U^-1, by substitution in LDS.
+constexpr int kTri = 32;
+__global__ __launch_bounds__(kVesBlock) void pc_invert(int Nm, double *Pm, int32_t *ipiv) {
+    __shared__ int32_t perm[3 * kVesMaxN];
+    __shared__ double blk[kVesBlock / kWave][kTri][kTri + 1], inv[kVesBlock / kWave][2][kTri][kTri + 1];
+    const int n = 3 * Nm, wid = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    double *A = Pm + (int64_t)blockIdx.x * n * n;
+    int32_t *pv = ipiv + (int64_t)blockIdx.x * n;
+    for (int i = threadIdx.x; i < n; i += kVesBlock) perm[i] = i;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int i = 0; i < n; ++i) {
+            const int j = pv[i] - 1;
+            const int32_t t = perm[i];
+            perm[i] = perm[j];
+            perm[j] = t;
+        }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kVesBlock) pv[i] = perm[i];
+    const int c = lane & (kTri - 1);
+    const bool up = lane >= kTri;
+    for (int k0 = wid * kTri; k0 < n; k0 += kTri * (kVesBlock / kWave)) {
+        const int nb = min(kTri, n - k0);
+        for (int e = lane; e < nb * nb; e += kWave)
+            blk[wid][e % nb][e / nb] = A[(int64_t)(k0 + e / nb) * n + k0 + e % nb];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        if (c < nb) {
+            double(*x)[kTri + 1] = inv[wid][up];      // column c of the inverse: x[.][c]
+            if (up) {
+                x[c][c] = 1.0 / blk[wid][c][c];
+                for (int r = c - 1; r >= 0; --r) {
+                    double s = 0.0;
+                    for (int k = r + 1; k <= c; ++k) s = __builtin_fma(blk[wid][r][k], x[k][c], s);
+                    x[r][c] = -s / blk[wid][r][r];
+                }
+            } else {
+                for (int r = c + 1; r < nb; ++r) {
+                    double s = blk[wid][r][c];
+                    for (int k = c + 1; k < r; ++k) s = __builtin_fma(blk[wid][r][k], x[k][c], s);
+                    x[r][c] = -s;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        for (int e = lane; e < nb * nb; e += kWave) {
+            const int r = e % nb, q = e / nb;
+            A[(int64_t)(k0 + q) * n + k0 + r] = inv[wid][r <= q][r][q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-__global__ __launch_bounds__(256) void pc_scatter(int64_t n, const int32_t *off, int Nm, const double *rhs,
-                                                  double *v) {
-    const int c = blockIdx.x;
-    const int64_t lo = off[c];
-    const int N = (int)(off[c + 1] - lo);
-    const double *o = rhs + (int64_t)c * 3 * Nm;
-    for (int idx = threadIdx.x; idx < 3 * Nm; idx += blockDim.x) {
-        const int ab = idx / Nm, m = idx % Nm;
-        if (m < N) v[ab * n + lo + m] = o[idx];
+// out = P^-1 v, one workgroup per curve with the padded vector in LDS: kTri
+// rows at a time, thread (row, part) sums every eighth column of what is
+// already solved and the inverted diagonal triangle finishes the rows.  Reads
+// each block once: 664 MB for 1,000 curves of 96 nodes, bound by HBM (batched
+// library substitution with its gather and scatter took 0.63 ms there in 20
+// launches, this takes 135 us = 4.9 TB/s).
+__global__ __launch_bounds__(kVesBlock) void pc_solve(int64_t n, const int32_t *off, int Nm, const double *Pm,
+                                                      const int32_t *perm, const double *v, double *out) {
+    __shared__ double y[3 * kVesMaxN], red[kVesBlock / kTri][kTri], zk[kTri];
+    const int M = 3 * Nm, r = threadIdx.x & (kTri - 1), part = threadIdx.x / kTri;
+    constexpr int kParts = kVesBlock / kTri;
+    const int64_t lo = off[blockIdx.x];
+    const int N = (int)(off[blockIdx.x + 1] - lo);
+    const double *A = Pm + (int64_t)blockIdx.x * M * M;
+    const int32_t *pv = perm + (int64_t)blockIdx.x * M;
+    for (int i = threadIdx.x; i < M; i += kVesBlock) {
+        const int s = pv[i], ab = s / Nm, m = s - ab * Nm;
+        y[i] = m < N ? v[ab * n + lo + m] : 0.0;
+    }
+    const int last = (M - 1) / kTri * kTri;
+    for (int sweep = 0; sweep < 2; ++sweep) {
+        for (int q = 0; q <= last; q += kTri) {
+            const int k0 = sweep == 0 ? q : last - q;
+            const bool ok = k0 + r < M;
+            const double *row = A + k0 + r;
+            // the diagonal triangle's entries of this thread, loaded ahead
+            double d[kTri / kParts];
+#pragma unroll
+            for (int e = 0; e < kTri / kParts; ++e) {
+                const int c = part * (kTri / kParts) + e;
+                const bool in = ok && k0 + c < M && (sweep == 0 ? c < r : c >= r);
+                d[e] = in ? row[(int64_t)(k0 + c) * M] : 0.0;
+            }
+            __syncthreads();                           // y complete up to here
+            const int j0 = sweep == 0 ? 0 : k0 + kTri, j1 = sweep == 0 ? k0 : M;
+            double s = 0.0;
+            if (ok) {
+#pragma unroll 8
+                for (int j = j0 + part; j < j1; j += kParts) s = __builtin_fma(row[(int64_t)j * M], y[j], s);
+            }
+            red[part][r] = s;
+            __syncthreads();
+            if (part == 0) {
+                double t = ok ? y[k0 + r] : 0.0;
+                for (int e = 0; e < kParts; ++e) t -= red[e][r];
+                zk[r] = t;
+            }
+            __syncthreads();
+            s = 0.0;
+#pragma unroll
+            for (int e = 0; e < kTri / kParts; ++e) s = __builtin_fma(d[e], zk[part * (kTri / kParts) + e], s);
+            red[part][r] = s;
+            __syncthreads();
+            if (part == 0 && ok) {
+                double t = sweep == 0 ? zk[r] : 0.0;
+                for (int e = 0; e < kParts; ++e) t += red[e][r];
+                y[k0 + r] = t;
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < M; i += kVesBlock) {
+        const int ab = i / Nm, m = i - ab * Nm;
+        if (m < N) out[ab * n + lo + m] = y[i];
     }
 }
 
@@ -682,12 +816,27 @@ __global__ __launch_bounds__(256) void vec_dots_kernel(int64_t len, int k1, cons
     }
 }
 
-__global__ void vec_dots_final(int nb, int k1, const double *partial, double *out) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// out[j] = the blocks' partial sums of product j, one wave per j: lane l adds
+// blocks l, l + 64, ... in order, then a fixed butterfly (a thread per j
+// adding 240 loads in turn took 34 us)
+__global__ __launch_bounds__(256) void vec_dots_final(int nb, int k1, const double *partial, double *out) {
+    const int j = blockIdx.x * (256 / kWave) + threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     if (j >= k1) return;
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[(int64_t)b * k1 + j];
-    out[j] = s;
+    for (int b = lane; b < nb; b += kWave) s += partial[(int64_t)b * k1 + j];
+#pragma unroll
+    for (int m = kWave / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, kWave);
+    if (lane == 0) out[j] = s;
+}
+
+// w -= sum_j h_j V_j (j < k1), h on the device
+__global__ __launch_bounds__(256) void vec_project_kernel(int64_t len, int k1, const double *V, int64_t ldv,
+                                                          const double *h, double *w) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= len) return;
+    double acc = w[i];
+    for (int j = 0; j < k1; ++j) acc = __builtin_fma(-h[j], V[j * ldv + i], acc);
+    w[i] = acc;
 }
 
 struct Coefs {
@@ -860,9 +1009,9 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct StepLayout {
     size_t geo, dens, tgt, b, r, w, dz, ri, V, z, part, dots, slp, slp_bytes;
     // preconditioner (precond != 0): Kress table, per-curve D_s, D_s^2, D_s^4,
-    // S_cc, B, S_cc B, P (LU), pivots, info, padded right-hand sides, two
-    // [3n] vectors
-    size_t T, Dm, D2, D4, Sm, Bm, Top, Pm, ipiv, info, rhs, t1, t2;
+    // S_cc, B, S_cc B, P (LU with inverted diagonal triangles), pivots (then the
+    // row permutation), info, two [3n] vectors
+    size_t T, Dm, D2, D4, Sm, Bm, Top, Pm, ipiv, info, t1, t2;
     // close evaluation (near != 0): curve boxes, per-node counts and list
     // offsets, the near pairs (node, curve, shifted coordinates, corrections),
     // the upsampled records
@@ -948,8 +1097,6 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
         o += al256((size_t)nc * 3 * Nm * sizeof(int32_t));
         L.info = o;
         o += al256((size_t)nc * sizeof(int32_t));
-        L.rhs = o;
-        o += al256((size_t)nc * 3 * Nm * d);
         L.t1 = o;
         o += al256(n3 * d);
         L.t2 = o;
@@ -1134,6 +1281,7 @@ int apply(StepCtx &C, const double *z, double *out, int mode) {
     a.off = C.off;
     a.x = C.x;
     a.y = C.y;
+    a.geo = C.geo;
     a.z = z;
     a.dt = C.p->dt;
     a.kb = C.p->kappa_b;
@@ -1176,16 +1324,45 @@ int apply(StepCtx &C, const double *z, double *out, int mode) {
     return S2D_OK;
 }
 
-// dots[j] = V_j . w, j < k1, read back to the host
-int dots(StepCtx &C, int k1, const double *V, const double *w, double *host) {
+// d[j] = V_j . w, j < k1, on the device
+int dots_dev(StepCtx &C, int k1, const double *V, const double *w, double *d) {
     const int64_t len = 3 * C.n;
-    double *part = (double *)(C.ws + C.L.part), *d = (double *)(C.ws + C.L.dots);
+    double *part = (double *)(C.ws + C.L.part);
     hipLaunchKernelGGL(vec_dots_kernel, dim3(kDotBlocks), dim3(256), 0, C.st, len, k1, V, len, w, part);
-    hipLaunchKernelGGL(vec_dots_final, dim3((k1 + 63) / 64), dim3(64), 0, C.st, kDotBlocks, k1, part, d);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(host, d, k1 * sizeof(double), hipMemcpyDeviceToHost, C.st);
+    hipLaunchKernelGGL(vec_dots_final, dim3((k1 + 3) / 4), dim3(256), 0, C.st, kDotBlocks, k1, part, d);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? S2D_OK : hipf(e, "GMRES dot products");
+}
+
+int read_back(StepCtx &C, const double *d, int k, double *host) {
+    hipError_t e = hipMemcpyAsync(host, d, k * sizeof(double), hipMemcpyDeviceToHost, C.st);
     if (e == hipSuccess) e = hipStreamSynchronize(C.st);
     return e == hipSuccess ? S2D_OK : hipf(e, "GMRES dot products");
+}
+
+// the same, read back to the host
+int dots(StepCtx &C, int k1, const double *V, const double *w, double *host) {
+    double *d = (double *)(C.ws + C.L.dots);
+    S2D_TRY(dots_dev(C, k1, V, w, d));
+    return read_back(C, d, k1, host);
+}
+
+// Classical Gram-Schmidt of w against V_0..V_(k1-1), twice, and |w|^2: the
+// coefficients stay on the device between the passes and come to the host
+// together (three read-backs an iteration otherwise).  h: [2 k1 + 1] = first
+// and second pass, |w|^2.
+int orthogonalise(StepCtx &C, int k1, const double *V, double *w, double *h) {
+    const int64_t len = 3 * C.n;
+    // behind the partial sums: their region has room for restart + 2 columns
+    // and at most `restart` are in use here
+    static_assert(2 * kDotBlocks >= 2 * kMaxRestart + 1, "room for both passes and the norm");
+    double *d = (double *)(C.ws + C.L.part) + (size_t)kDotBlocks * C.p->restart;
+    for (int pass = 0; pass < 2; ++pass) {
+        S2D_TRY(dots_dev(C, k1, V, w, d + pass * k1));
+        hipLaunchKernelGGL(vec_project_kernel, dim3(g256(len)), dim3(256), 0, C.st, len, k1, V, len, d + pass * k1, w);
+    }
+    S2D_TRY(dots_dev(C, 1, w, w, d + 2 * k1));
+    return read_back(C, d, 2 * k1 + 1, h);
 }
 
 int combo(StepCtx &C, int k1, const double *V, const double *c, double sw, double *w) {
@@ -1283,24 +1460,17 @@ int pc_build(StepCtx &C) {
             return ves_fail(S2D_EINVAL, "the preconditioner block of curve " + std::to_string(c) +
                                             " is singular (a circular vesicle leaves the tension's constant "
                                             "mode undetermined)");
-    return S2D_OK;
+    hipLaunchKernelGGL(pc_invert, dim3(nc), dim3(kVesBlock), 0, C.st, Nm, a.Pm, ipiv);
+    e = hipGetLastError();
+    return e == hipSuccess ? S2D_OK : hipf(e, "preconditioner inverse launch");
 }
 
 // out = P^-1 v
 int pc_apply(StepCtx &C, const double *v, double *out) {
-    const int nc = C.nc, Nm = C.p->nmax;
-    double *rhs = (double *)(C.ws + C.L.rhs);
-    hipLaunchKernelGGL(pc_gather, dim3(nc), dim3(256), 0, C.st, C.n, C.off, Nm, v, rhs);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hipf(e, "preconditioner gather");
-    const rocblas_stride s1 = (rocblas_stride)Nm * Nm;
-    S2D_TRY(rbf(rocsolver_dgetrs_strided_batched(C.h, rocblas_operation_none, 3 * Nm, 1,
-                                                 (double *)(C.ws + C.L.Pm), 3 * Nm, 9 * s1,
-                                                 (rocblas_int *)(C.ws + C.L.ipiv), 3 * Nm, rhs, 3 * Nm, 3 * Nm, nc),
-                "preconditioner solve"));
-    hipLaunchKernelGGL(pc_scatter, dim3(nc), dim3(256), 0, C.st, C.n, C.off, Nm, rhs, out);
-    e = hipGetLastError();
-    return e == hipSuccess ? S2D_OK : hipf(e, "preconditioner scatter");
+    hipLaunchKernelGGL(pc_solve, dim3(C.nc), dim3(kVesBlock), 0, C.st, C.n, C.off, C.p->nmax,
+                       (const double *)(C.ws + C.L.Pm), (const int32_t *)(C.ws + C.L.ipiv), v, out);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? S2D_OK : hipf(e, "preconditioner solve");
 }
 
 // Restarted GMRES on A x = rhs from x = 0 (single-layer sums in `mode`),
@@ -1319,7 +1489,7 @@ int krylov(StepCtx &C, const double *rhs, double rhs_norm, double *x, double tol
         rel = rhs_norm == 0.0 ? 0.0 : rhs_norm;
         return S2D_OK;
     }
-    std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), hc(m + 2), h2(m + 2), y(m);
+    std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), hc(m + 2), gs(2 * m + 1), y(m);
     S2D_TRY(axpby(C, 1.0, rhs, 0.0, nullptr, r));
     double beta = rhs_norm;
     while (true) {
@@ -1338,17 +1508,9 @@ int krylov(StepCtx &C, const double *rhs, double rhs_norm, double *x, double tol
             } else {
                 S2D_TRY(apply<false>(C, vj, w, mode));
             }
-            // classical Gram-Schmidt, twice
-            S2D_TRY(dots(C, j + 1, V, w, hc.data()));
-            for (int i = 0; i <= j; ++i) h2[i] = -hc[i];
-            S2D_TRY(combo(C, j + 1, V, h2.data(), 1.0, w));
-            S2D_TRY(dots(C, j + 1, V, w, h2.data()));
-            for (int i = 0; i <= j; ++i) hc[i] += h2[i];
-            for (int i = 0; i <= j; ++i) h2[i] = -h2[i];
-            S2D_TRY(combo(C, j + 1, V, h2.data(), 1.0, w));
-            double ww = 0.0;
-            S2D_TRY(dots(C, 1, w, w, &ww));
-            const double hn = std::sqrt(ww);
+            S2D_TRY(orthogonalise(C, j + 1, V, w, gs.data()));
+            for (int i = 0; i <= j; ++i) hc[i] = gs[i] + gs[j + 1 + i];
+            const double hn = std::sqrt(gs[2 * (j + 1)]);
             // Hessenberg column j, previous rotations, a new one
             for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = hc[i];
             for (int i = 0; i < j; ++i) {

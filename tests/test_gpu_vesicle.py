@@ -529,3 +529,19 @@ def test_table4_convergence_orders_on_the_gpu(corrections):
         assert max(out[M][3] for M in Ms) < 1e-12
     else:
         assert all(1.5 < r < 2.5 for r in rL), rL
+
+
+# block sizes 3 nmax around the solve's 32-row steps: one step (24, 30), a
+# remainder of 4 and of 6 rows, whole steps, the largest; padded blocks
+@pytest.mark.parametrize("N,nmax", [(8, 8), (10, 10), (12, 12), (32, 32), (34, 34), (34, 50), (96, 96), (254, 254),
+                                    (512, 512)])
+def test_preconditioner_inverts_a_lone_vesicle(N, nmax):
+    """Without neighbours and images the preconditioner is the matrix, so
+    GMRES is done after one iteration (a second one for rounding)."""
+    from paper_1510_05616_amd import vesicle as pv
+    x, y = synth._ellipse(0.3, -0.2, 0.5, 0.27, 0.4, N)[:2]
+    V = pv.Vesicles(x, y, np.array([0, N], np.int32))
+    p = pv.params(dt=1e-3, tol=1e-8, nmax=nmax, max_iter=10)
+    _, it, res = V.step_solve(p)
+    print(f"N={N} nmax={nmax}: {it} iterations, residual {res:.1e}", flush=True)
+    assert it <= 2 and res <= 1e-8
