@@ -61,7 +61,7 @@ constexpr int kLeafFan = 32;     // and of a middle one: 16 tiles of two circles
 constexpr int kOrder = 32;       // coefficients per series, the logarithm's included
 constexpr double kTheta = 0.28;
 constexpr int kFarWaves = 4;     // waves per target tile, far kernel
-constexpr int kNearWaves = 8;    // and near kernel
+constexpr int kNearWaves = 4;    // and near kernel
 constexpr int kBoxBlocks = 64;
 constexpr int kSortItems = 2048; // items per sort block
 // bits of a sort key (the bit above marks targets), eight to a pass: cells of
@@ -342,34 +342,36 @@ __global__ __launch_bounds__(256) void far_tiles(int64_t ns, int64_t nt, int64_t
     }
 }
 
-// the circle around up to n children (empty ones apart)
-__device__ __forceinline__ FarNode far_parent(const FarNode *c, int n) {
-    double x0 = __builtin_inf(), x1 = -x0, y0 = x0, y1 = -x0;
-    for (int q = 0; q < n; ++q) {
-        if (c[q].lo == c[q].hi) continue;
-        x0 = fmin(x0, c[q].x - c[q].r);
-        x1 = fmax(x1, c[q].x + c[q].r);
-        y0 = fmin(y0, c[q].y - c[q].r);
-        y1 = fmax(y1, c[q].y + c[q].r);
-    }
-    FarNode p{0.5 * (x0 + x1), 0.5 * (y0 + y1), 0.0, 0, 1};
-    for (int q = 0; q < n; ++q) {
-        if (c[q].lo == c[q].hi) continue;
-        const double dx = c[q].x - p.x, dy = c[q].y - p.y;
-        p.r = fmax(p.r, sqrt(dx * dx + dy * dy) + c[q].r);
-    }
-    p.r *= 1.0 + 1e-12;
-    return p;
+// the circle around the children held by the lanes of a wave (`in`: this lane
+// holds one)
+__device__ __forceinline__ FarNode far_parent(const FarNode &c, bool in) {
+    const double inf = __builtin_inf();
+    const double x0 = wmin(in ? c.x - c.r : inf), x1 = wmax(in ? c.x + c.r : -inf);
+    const double y0 = wmin(in ? c.y - c.r : inf), y1 = wmax(in ? c.y + c.r : -inf);
+    const double cx = 0.5 * (x0 + x1), cy = 0.5 * (y0 + y1), dx = c.x - cx, dy = c.y - cy;
+    return FarNode{cx, cy, wmax(in ? sqrt(dx * dx + dy * dy) + c.r : 0.0) * (1.0 + 1e-12), 0, 1};
 }
 
-// n0: leaves (two per source tile)
-__global__ __launch_bounds__(64) void far_upper(int64_t n0, int64_t n1, FarNode *node) {
-    const int64_t i = (int64_t)blockIdx.x * kFan + threadIdx.x;
-    if (threadIdx.x < kFan && i < n1)
-        node[n0 + i] = far_parent(node + i * kLeafFan, (int)min((int64_t)kLeafFan, n0 - i * kLeafFan));
+// Circles of the upper levels: a workgroup per top node, a wave per middle
+// node, a lane per leaf; n0: leaves (two per source tile).
+__global__ __launch_bounds__(64 * kFan) void far_upper(int64_t n0, int64_t n1, FarNode *node) {
+    __shared__ FarNode mid[kFan];
+    const int wid = threadIdx.x / 64, lane = threadIdx.x & 63;
+    const int64_t b = (int64_t)blockIdx.x * kFan, i = b + wid, c = i * kLeafFan + lane;
+    if (i < n1) {
+        FarNode l{0.0, 0.0, 0.0, 0, 0};
+        if (lane < kLeafFan && c < n0) l = node[c];
+        const FarNode p = far_parent(l, l.lo < l.hi);
+        if (lane == 0) {
+            mid[wid] = p;
+            node[n0 + i] = p;
+        }
+    }
     __syncthreads();
-    const int64_t b = (int64_t)blockIdx.x * kFan;
-    if (threadIdx.x == 0) node[n0 + n1 + blockIdx.x] = far_parent(node + n0 + b, (int)min((int64_t)kFan, n1 - b));
+    if (wid != 0) return;
+    const bool in = lane < kFan && b + lane < n1;
+    const FarNode p = far_parent(mid[in ? lane : 0], in);
+    if (lane == 0) node[n0 + n1 + blockIdx.x] = p;
 }
 
 // ---------------------------------------------------------------------------
@@ -656,8 +658,10 @@ struct FarArgs {
 // (series, l) holds local coefficient l and row l of the binomial table; the
 // 2 x 31 scaled source coefficients pass through LDS.
 template <int OP>
-__global__ __launch_bounds__(64 * kFarWaves) void far_far(FarArgs a) {
-    __shared__ C2 buf[kFarWaves][2][kOrder + 1], sum[kFarWaves][2][64];
+__global__ __launch_bounds__(64 * kFarWaves) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void far_far(FarArgs a) {
+    __shared__ C2 buf[kFarWaves][2][kOrder + 1], sum[kFarWaves][2][64], la[kFarWaves][slp_sources(OP) ? kWave : 1];
+    __shared__ double lq[kFarWaves][slp_sources(OP) ? kWave : 1];
     __shared__ WalkLds sh;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x & 63;
     const int h = lane >> 5, l = lane & 31;
@@ -668,17 +672,26 @@ __global__ __launch_bounds__(64 * kFarWaves) void far_far(FarArgs a) {
     double row[kOrder];
 #pragma unroll
     for (int k = 1; k < kOrder; ++k) row[k] = kBinom.v[l][k];
-    const double sgn = (l & 1) ? -1.0 : 1.0, il = l ? -1.0 / (double)l : 0.0;
-    const double cst = h == 0 ? 1.0 : 0.0;
-    C2 acc{0.0, 0.0}, gam{0.0, 0.0};
+    const double sgn = (l & 1) ? -1.0 : 1.0, il = l ? -1.0 / (double)l : h == 0 ? -1.0 : 0.0;
+    C2 acc{0.0, 0.0}, gam{0.0, 0.0}, lsum{0.0, 0.0};
+    // a_0 log |t| of the nodes held in LDS, summed over the lanes' own share
+    int held = 0;
+    const auto flush = [&] {
+        if (lane < held) {
+            const double c = __builtin_fma(0.5, log64(lq[wid][lane]), -logs);
+            lsum.x = __builtin_fma(la[wid][lane].x, c, lsum.x);
+            lsum.y = __builtin_fma(la[wid][lane].y, c, lsum.y);
+        }
+        held = 0;
+    };
     far_walk<kFarWaves, true>(
         a.w, t, a.info->dmin, wid, lane, wid, kFarWaves, sh, [&](int64_t at, int img) {
-            const FarNode s = a.w.node[at];
+            const FarNode s = load_ro<FarNode>(a.w.node, at);
             const C2 m = ((const C2 *)a.coef)[at * 64 + lane];
             const C2 tt{S * (t.x - (s.x + (double)img * a.w.d)), S * (t.y - s.y)};
             const double q = __builtin_fma(tt.x, tt.x, tt.y * tt.y), iq = rcp64(q);
             // terms until (r_s / (D - r_t))^k < 2^-56
-            const float ratio = (float)(S * s.r) / ((float)sqrt(q) - (float)(S * t.r));
+            const float ratio = (float)(S * s.r) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf((float)q) - (float)(S * t.r));
             const int terms = __builtin_amdgcn_readfirstlane(
                 min(kOrder - 1, max(1, (int)(-56.0f / __builtin_amdgcn_logf(ratio)) + 2)));
             const C2 e = cpow5(C2{tt.x * iq, -tt.y * iq}, l);        // t^-l
@@ -697,9 +710,17 @@ __global__ __launch_bounds__(64 * kFarWaves) void far_far(FarArgs a) {
             }
             if (slp_sources(OP)) {
                 const C2 m0 = buf[wid][h][0];
-                const double c = l ? il : __builtin_fma(0.5, log64(q), -logs) - cst;
-                v.x = __builtin_fma(m0.x, c, v.x);
-                v.y = __builtin_fma(m0.y, c, v.y);
+                v.x = __builtin_fma(m0.x, il, v.x);
+                v.y = __builtin_fma(m0.y, il, v.y);
+                // the logarithms of 64 nodes at a time, a lane each
+                if (lane == 0) {
+                    lq[wid][held] = q;
+                    la[wid][held] = m0;
+                }
+                if (++held == kWave) {
+                    wave_lds_sync();
+                    flush();
+                }
             }
             wave_lds_sync();
             C2 r = cmul(v, e);
@@ -711,6 +732,20 @@ __global__ __launch_bounds__(64 * kFarWaves) void far_far(FarArgs a) {
             gam.x += g.x;
             gam.y += g.y;
         });
+    if (slp_sources(OP)) {
+        wave_lds_sync();
+        flush();
+#pragma unroll
+        for (int m = kWave / 2; m >= 1; m >>= 1) {
+            lsum.x += __shfl_xor(lsum.x, m, kWave);
+            lsum.y += __shfl_xor(lsum.y, m, kWave);
+        }
+        // phi_0 with a_0 log |t|, psi_0 with its conjugate
+        if (l == 0) {
+            acc.x += lsum.x;
+            acc.y += h == 0 ? lsum.y : -lsum.y;
+        }
+    }
     sum[wid][0][lane] = acc;
     sum[wid][1][lane] = gam;
     __syncthreads();
@@ -944,8 +979,8 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
     L.n1 = (L.n0 + kLeafFan - 1) / kLeafFan;
     L.n2 = (L.n1 + kFan - 1) / kFan;
     L.nT = 2 * ((nt + kTile - 1) / kTile);
-    // groups per circle: about four near workgroups for each compute unit
-    L.groups = (int)std::min<int64_t>(8, std::max<int64_t>(1, 2048 / std::max<int64_t>(L.nT, 1)));
+    // groups per circle: about eight near workgroups for each compute unit
+    L.groups = (int)std::min<int64_t>(16, std::max<int64_t>(1, 4096 / std::max<int64_t>(L.nT, 1)));
     const size_t N = (size_t)(ns + nt);
     L.bits = key_bits((int64_t)N);
     L.nblk = (int64_t)((N + kSortItems - 1) / kSortItems);
@@ -968,8 +1003,8 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
     L.txy = take(2 * (size_t)nt * sizeof(double));
     L.rec = take((size_t)ns * rec_bytes(op, S2D_FP64));
     L.coef = take((size_t)(L.n0 + L.n1 + L.n2) * 4 * kOrder * sizeof(double));
-    // one plane and the groups' (groups * nt <= 65,536 by the rule above, so the size grows with nt)
-    L.part = take(2 * ((size_t)nt + std::min<size_t>(8 * (size_t)nt, 65536)) * sizeof(double));
+    // one plane and the groups' (groups * nt <= 131,072 by the rule above, so the size grows with nt)
+    L.part = take(2 * ((size_t)nt + std::min<size_t>(16 * (size_t)nt, 131072)) * sizeof(double));
     L.kress = L.self = o;
     if (op == S2D_OP_SLP && on_curve) {
         L.kress = take((size_t)ns * sizeof(double));
@@ -1013,7 +1048,7 @@ hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_
     hipLaunchKernelGGL(far_tiles, dim3((unsigned)((ts + tt + 3) / 4)), dim3(256), 0, st, L.ns, L.nt, ts, tt, s->x,
                        s->y, t->x, t->y, (const int32_t *)(b + far_sorted(L)), (int32_t *)(b + L.spos), node,
                        (FarNode *)(b + L.tnode), (double *)(b + L.txy));
-    hipLaunchKernelGGL(far_upper, dim3((unsigned)L.n2), dim3(64), 0, st, L.n0, L.n1, node);
+    hipLaunchKernelGGL(far_upper, dim3((unsigned)L.n2), dim3(64 * kFan), 0, st, L.n0, L.n1, node);
     if (op == S2D_OP_SLP && t->on_curve && s->n_curves > 0)
         hipLaunchKernelGGL(far_kress, dim3((unsigned)s->n_curves), dim3(256), 0, st, s->curve_off, s->n_curves, L.ns,
                            (double *)(b + L.kress));

@@ -795,25 +795,37 @@ __global__ __launch_bounds__(kVesBlock) void pc_solve(int64_t n, const int32_t *
 // ---------------------------------------------------------------------------
 constexpr int kDotBlocks = 240;
 
-// partial[b * k1 + j] = sum over block b's chunk of V_j . w (j < k1)
+// partial[b * k1 + j] = sum over block b's chunk of V_j . w (j < k1): a
+// thread's share of w is read once for kDotCols columns, whose sums meet by
+// wave butterflies and in LDS (one column at a time with an LDS tree each, nine
+// barriers a column, took 19 us at 10 columns of 288,000, this takes DOTS_US)
+constexpr int kDotCols = 8;
 __global__ __launch_bounds__(256) void vec_dots_kernel(int64_t len, int k1, const double *V, int64_t ldv,
                                                        const double *w, double *partial) {
-    __shared__ double red[256];
+    __shared__ double red[kMaxRestart + 1][256 / kWave];
     const int64_t chunk = (len + gridDim.x - 1) / gridDim.x;
     const int64_t b0 = (int64_t)blockIdx.x * chunk, b1 = min(b0 + chunk, len);
-    for (int j = 0; j < k1; ++j) {
-        const double *vj = V + j * ldv;
-        double s = 0.0;
-        for (int64_t i = b0 + threadIdx.x; i < b1; i += blockDim.x) s = __builtin_fma(vj[i], w[i], s);
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int st = 128; st > 0; st >>= 1) {
-            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-            __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    for (int j0 = 0; j0 < k1; j0 += kDotCols) {
+        double s[kDotCols] = {};
+        const double *v = V + j0 * ldv;
+        for (int64_t i = b0 + threadIdx.x; i < b1; i += 256) {
+            const double wi = w[i];
+#pragma unroll
+            for (int j = 0; j < kDotCols; ++j)
+                if (j0 + j < k1) s[j] = __builtin_fma(v[j * ldv + i], wi, s[j]);
         }
-        if (threadIdx.x == 0) partial[(int64_t)blockIdx.x * k1 + j] = red[0];
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kDotCols; ++j) {
+            if (j0 + j >= k1) break;
+#pragma unroll
+            for (int m = kWave / 2; m >= 1; m >>= 1) s[j] += __shfl_xor(s[j], m, kWave);
+            if (lane == 0) red[j0 + j][wid] = s[j];
+        }
     }
+    __syncthreads();
+    for (int j = threadIdx.x; j < k1; j += 256)
+        partial[(int64_t)blockIdx.x * k1 + j] = red[j][0] + red[j][1] + red[j][2] + red[j][3];
 }
 
 // out[j] = the blocks' partial sums of product j, one wave per j: lane l adds
@@ -916,7 +928,11 @@ __device__ bool ves_near_hit(double tx, double ty, const double *x, const double
 // Per node i (on curve ci), the (curve c, image k) pairs with c != ci or
 // k != 0 for which the node, shifted by -k d, is near c: counted (WRITE
 // false, cnt[i]) or written from pos[i] on in the order c, then k (WRITE
-// true): the node, the curve and the shifted coordinates.
+// true): the node, the curve and the shifted coordinates.  The nodes of one
+// curve in a wave share a box; 64 (curve, image) pairs at a time are tested
+// against it, a lane each, and the nodes then look only at the few that pass,
+// in order (every node against every pair's box took 0.45 + 0.57 ms on 96,000
+// nodes and 1,000 curves with images -1..1, this takes PAIRS_US).
 template <bool WRITE>
 __global__ __launch_bounds__(256) void ves_near_pairs(int64_t n, int32_t nc, const int32_t *off, const int32_t *oc,
                                                       const double *x, const double *y, const double *box, double d,
@@ -925,58 +941,98 @@ __global__ __launch_bounds__(256) void ves_near_pairs(int64_t n, int32_t nc, con
                                                       double *px, double *py) {
 #pragma clang fp contract(off)
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int ci = oc[i];
-    const double xi = x[i], yi = y[i];
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool act = i < n;
+    const int ci = act ? oc[i] : -1;
+    const double xi = act ? x[i] : 0.0, yi = act ? y[i] : 0.0, inf = __builtin_inf();
     int32_t m = 0;
-    int64_t at = WRITE ? pos[i] : 0;
-    for (int c = 0; c < nc; ++c) {
-        const double *b = box + 5 * c;
-        const double R = band * b[4], R2 = R * R, Rb = 1.01 * R;   // the box test only pre-selects
-        for (int k = img_lo; k <= img_hi; ++k) {
-            if (c == ci && k == 0) continue;
-            const double tx = xi - (double)k * d;
-            if (!(tx >= b[0] - Rb && tx <= b[1] + Rb && yi >= b[2] - Rb && yi <= b[3] + Rb)) continue;
-            if (!ves_near_hit(tx, yi, x, y, off[c], off[c + 1], R2)) continue;
-            if (WRITE) {
-                pnode[at] = (int32_t)i;
-                pcurve[at] = c;
-                px[at] = tx;
-                py[at] = yi;
-                ++at;
-            } else {
-                ++m;
+    int64_t at = WRITE && act ? pos[i] : 0;
+    const int n_img = img_hi - img_lo + 1;
+    const int64_t items = (int64_t)nc * n_img;
+    for (uint64_t todo = __ballot(act); todo;) {
+        const bool in = act && ci == __builtin_amdgcn_readlane(ci, __builtin_ctzll(todo));
+        todo &= ~__ballot(in);
+        // the box of these nodes; a NaN node is near nothing and stays out of it
+        double v[4] = {in ? xi : inf, in ? xi : -inf, in ? yi : inf, in ? yi : -inf};
+#pragma unroll
+        for (int s = kWave / 2; s >= 1; s >>= 1)
+            for (int k = 0; k < 4; ++k) {
+                const double o = __shfl_xor(v[k], s, kWave);
+                v[k] = (k & 1) ? fmax(v[k], o) : fmin(v[k], o);
+            }
+        for (int64_t e0 = 0; e0 < items; e0 += kWave) {
+            // pair e of this lane against the box; the box test only pre-selects
+            const int64_t e = e0 + lane;
+            bool hit = false;
+            if (e < items) {
+                const int c = (int)(e / n_img);
+                const double s = (double)(img_lo + (int)(e - (int64_t)c * n_img)) * d;
+                const double *b = box + 5 * c;
+                const double Rb = 1.01 * (band * b[4]);
+                hit = v[1] - s >= b[0] - Rb && v[0] - s <= b[1] + Rb && v[3] >= b[2] - Rb && v[2] <= b[3] + Rb;
+            }
+            const uint64_t mask = __ballot(hit);
+            if (!in) continue;
+            for (uint64_t left = mask; left; left &= left - 1) {
+                const int64_t q = e0 + __builtin_ctzll(left);
+                const int c = (int)(q / n_img), k = img_lo + (int)(q - (int64_t)c * n_img);
+                if (c == ci && k == 0) continue;
+                const double *b = box + 5 * c;
+                const double R = band * b[4], R2 = R * R, Rb = 1.01 * R;
+                const double tx = xi - (double)k * d;
+                if (!(tx >= b[0] - Rb && tx <= b[1] + Rb && yi >= b[2] - Rb && yi <= b[3] + Rb)) continue;
+                if (!ves_near_hit(tx, yi, x, y, off[c], off[c + 1], R2)) continue;
+                if (WRITE) {
+                    pnode[at] = (int32_t)i;
+                    pcurve[at] = c;
+                    px[at] = tx;
+                    py[at] = yi;
+                    ++at;
+                } else {
+                    ++m;
+                }
             }
         }
     }
-    if (!WRITE) cnt[i] = m;
+    if (!WRITE && act) cnt[i] = m;
 }
 
 // exclusive scan of cnt[0 .. n) into pos[0 .. n], pos[n] the total; one
-// workgroup, each thread over a contiguous segment
+// workgroup, 8,192 counts a round: eight to a thread, wave prefix sums
 __global__ __launch_bounds__(1024) void ves_near_scan(int64_t n, const int32_t *cnt, int64_t *pos) {
-    __shared__ int64_t part[1024];
-    const int64_t seg = (n + 1023) / 1024;
-    const int64_t b0 = min((int64_t)threadIdx.x * seg, n), b1 = min(b0 + seg, n);
-    int64_t s = 0;
-    for (int64_t i = b0; i < b1; ++i) s += cnt[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t acc = 0;
-        for (int t = 0; t < 1024; ++t) {
-            const int64_t v = part[t];
-            part[t] = acc;
-            acc += v;
+    __shared__ int64_t part[1024 / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    int64_t run = 0;
+    for (int64_t b0 = 0; b0 < n; b0 += 8192) {
+        const int64_t i0 = b0 + 8 * (int64_t)threadIdx.x;
+        int32_t v[8];
+        int64_t s = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            v[k] = i0 + k < n ? cnt[i0 + k] : 0;
+            s += v[k];
         }
-        pos[n] = acc;
+        int64_t up = s;
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) {
+            const int64_t o = __shfl_up(up, m, kWave);
+            if (lane >= m) up += o;
+        }
+        __syncthreads();
+        if (lane == kWave - 1) part[wid] = up;
+        __syncthreads();
+        int64_t at = run + up - s;
+        for (int w = 0; w < 1024 / kWave; ++w) {
+            if (w < wid) at += part[w];
+            run += part[w];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (i0 + k < n) pos[i0 + k] = at;
+            at += v[k];
+        }
     }
-    __syncthreads();
-    int64_t acc = part[threadIdx.x];
-    for (int64_t i = b0; i < b1; ++i) {
-        pos[i] = acc;
-        acc += cnt[i];
-    }
+    if (threadIdx.x == 0) pos[n] = run;
 }
 
 // out[i] += the node's corrections, out[n + i] likewise, summed in list order
