@@ -28,20 +28,24 @@
 // conj(psi).
 //
 // Acceptance.  A source node of radius r_s and a target tile of radius r_t at
-// distance D are far when r_s < th (D - r_t) and r_t < th (D - r_s), th = 0.28:
-// both truncations are below 0.28^31 = 8e-18 relative to the sum of the terms'
-// magnitudes.  Non-finite boxes never pass and are summed term by term.
+// distance D are far when r_s < th (D - r_t) and r_t < th (D - r_s), th = 0.32:
+// both truncations are below 0.32^31 = 5e-16 relative to the sum of the terms'
+// magnitudes.  Against the direct sums, with the density on one node, errors
+// over |term| stay at rounding (largest 4.0e-15 for velocities, 6.1e-15 for
+// pressures and traction) for th = 0.28 and 0.32 alike, double at 0.34 and are
+// 2e-13 at 0.37; the channel step below takes 0.93, 0.87, 0.84 and 0.81 ms.
+// Non-finite boxes never pass and are summed term by term.
 // Source nodes have three levels (64, 1,024 and 16,384 sources); a target tile
 // walks them from the top.  Coordinates inside the expansions are scaled by a
 // power of two to about the domain's extent, and nodes closer than 1e-8 of it
 // are never far, so no power over- or underflows harmfully.
 //
 // Measured (MI355X): single layer of 1,000 vesicles x 96 nodes at their own
-// nodes, images -1..1: 15.1 ms direct; here 0.21 ms near part, 0.15 ms far
+// nodes, images -1..1: 15.1 ms direct; here 0.18 ms near part, 0.13 ms far
 // part, 0.05 ms own-curve and source expansions, 0.1 ms set-up (once per
 // geometry).  Walls of 2 x 16,000 nodes refined 8 times at 20,000 near-wall
-// points: 8.6 ms direct; near and far parts of both sums 0.35 ms, set-up
-// 0.15 ms each.  Both parts are bound by FP64 issue and the latency of its
+// points: 8.6 ms direct; near and far parts of both sums 0.29 ms, set-up
+// 0.1 ms each.  Both parts are bound by FP64 issue and the latency of its
 // dependent chains at 3-5 waves per SIMD.
 //
 // Every sum runs in a fixed order (stable sort, ballots, no floating-point
@@ -59,7 +63,7 @@ constexpr int kTile = 64;        // sources and targets per tile: one wave
 constexpr int kFan = 16;         // children of a top node
 constexpr int kLeafFan = 32;     // and of a middle one: 16 tiles of two circles
 constexpr int kOrder = 32;       // coefficients per series, the logarithm's included
-constexpr double kTheta = 0.28;
+constexpr double kTheta = 0.32;
 constexpr int kFarWaves = 4;     // waves per target tile, far kernel
 constexpr int kNearWaves = 4;    // and near kernel
 constexpr int kBoxBlocks = 64;

@@ -31,9 +31,9 @@
 // folds its targets' excluded index ranges into one hull; a superblock that
 // meets the hull in a group holding n = 0 takes a masked path: the same
 // grouped terms, with image 0 replaced by a neutral factor where a target
-// excludes the source or the record is padding.  (Going image by image with
-// one select per pair took 2.5 times as long, and small problems consist of
-// such superblocks.)  All other superblocks, the ragged last one included,
+// excludes the source or the record is padding.  (Image by image with one
+// select per pair, the batched single layer of 64 channels with up to 40
+// vesicles took 1.04 ms against 0.74; small problems consist of such superblocks.)  All other superblocks, the ragged last one included,
 // take the unmasked path.
 //
 // Precision.  FP64 mode evaluates each term in double.  FP32C mode evaluates

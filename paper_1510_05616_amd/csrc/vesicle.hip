@@ -798,7 +798,7 @@ constexpr int kDotBlocks = 240;
 // partial[b * k1 + j] = sum over block b's chunk of V_j . w (j < k1): a
 // thread's share of w is read once for kDotCols columns, whose sums meet by
 // wave butterflies and in LDS (one column at a time with an LDS tree each, nine
-// barriers a column, took 19 us at 10 columns of 288,000, this takes DOTS_US)
+// barriers a column, took 19 us at 10 columns of 288,000, this takes 16)
 constexpr int kDotCols = 8;
 __global__ __launch_bounds__(256) void vec_dots_kernel(int64_t len, int k1, const double *V, int64_t ldv,
                                                        const double *w, double *partial) {
@@ -932,7 +932,7 @@ __device__ bool ves_near_hit(double tx, double ty, const double *x, const double
 // curve in a wave share a box; 64 (curve, image) pairs at a time are tested
 // against it, a lane each, and the nodes then look only at the few that pass,
 // in order (every node against every pair's box took 0.45 + 0.57 ms on 96,000
-// nodes and 1,000 curves with images -1..1, this takes PAIRS_US).
+// nodes and 1,000 curves with images -1..1, this takes 0.05 ms each).
 template <bool WRITE>
 __global__ __launch_bounds__(256) void ves_near_pairs(int64_t n, int32_t nc, const int32_t *off, const int32_t *oc,
                                                       const double *x, const double *y, const double *box, double d,
