@@ -6,21 +6,45 @@
 // nodes equispaced in its parameter t in [0, 2 pi), advancing by s d in x
 // (s = +-1, from the first two nodes).  Its periodic parts x - s d t / 2 pi
 // and y and the density are expanded in their discrete Fourier coefficients
-// V_k = sum_j v_j e^{-2 pi i j k / N}, k = 0 .. N/2 (stage 1, a direct sum per
-// coefficient), and evaluated at the P N parameter values 2 pi m / (P N)
-// (stage 2, the trigonometric interpolant with the Nyquist mode split evenly
-// between +-N/2), with spectral derivatives for the speed |x'(t)|, the
-// weights (2 pi / P N) |x'| and the unit normals, oriented like the given
-// normal of the coarse node at or before the fine one.
+// (stage 1) and evaluated at the P N parameter values 2 pi m / (P N) (stage 2,
+// the trigonometric interpolant with the Nyquist mode split evenly between
+// +-N/2), with spectral derivatives for the speed |x'(t)|, the weights
+// (2 pi / P N) |x'| and the unit normals, oriented like the given normal of
+// the coarse node at or before the fine one.
 //
-// Coefficients are stored interleaved, 8 doubles per (curve, k): re and im of
-// the four series.  Both sums are split into chunks (over the nodes in stage
-// 1, over the modes in stage 2) along the grid's y dimension so that the
-// launch fills the device, and the chunks' partial sums are added in chunk
-// order by a second kernel (deterministic results).  A wave whose lanes all
-// lie in one curve reads the coefficients (and in stage 1 the nodes) through
-// the scalar data path; twiddle factors follow a rotation recurrence
-// re-anchored with sincospi every 32 steps.
+// Two routes, chosen per curve on the device (the sizes are known there only)
+// by wall_factor: with N1 the largest divisor of N up to sqrt(N), N2 = N / N1,
+//  * 8 (N1 + N2) < N, factored: the series are the two complex ones
+//    (x - s d t / 2 pi) + i y and fx + i fy; a transform of N points is N2
+//    transforms of N1 points, a twiddle factor each, and N1 of N2 points, the
+//    fine points P shifted inverse transforms: N1 + N2 terms a value;
+//  * otherwise (small N, a large prime factor), direct: coefficients V_k,
+//    k = 0 .. N/2, as sums over the nodes and fine values as sums over the
+//    modes, N/2 terms for four values at a time by symmetry.
+// About 16 FP64 instructions a term on either; N / 4 terms a value (both
+// stages, symmetry counted) on the direct route against 2 (N1 + N2) put the
+// line at N1 + N2 = N / 8.  Two walls refined 8 times, whole call: 500 against
+// 502 (= 2 x 251, direct) nodes 44 us each, the five launches; 2,000 against
+// 2,018 54 and 76 us; 16,000 against 16,022 152 and 928 us.  Each kernel serves
+// both routes, a curve's work-items leaving where the other route has them, so
+// the factored one adds no launch.  At 16,000 nodes its kernels (29, 22, 58 and
+// 68 us) wait for the caches: 500 waves in stage 1, 75 MB of intermediate sums
+// read 64 times over in the last, which takes two outputs from each.
+//
+// Direct route: coefficients are stored interleaved, 8 doubles per (curve, k):
+// re and im of the four series.  Both sums are split into chunks (over the
+// nodes in stage 1, over the modes in stage 2) along the grid's y dimension so
+// that the launch fills the device, and the chunks' partial sums are added in
+// chunk order by a second kernel (deterministic results).  A wave whose lanes
+// all lie in one curve reads the coefficients (and in stage 1 the nodes)
+// through the scalar data path.  Twiddle factors follow a rotation recurrence
+// re-anchored with sincospi every 32 steps on both routes.
+//
+// The factored route keeps its sums inside the curve's own share of the direct
+// one's scratch: stage 1 in the first chunk's records (4 of 8 doubles), the
+// coefficients in the curve's records (4 of 8), stage 2 in the first chunk's
+// six arrays, and N1 in double 4 of the curve's last record, which the direct
+// route (k <= N/2 < N - 1) leaves alone.
 #include "s2d_near.h"
 
 #include <algorithm>
@@ -66,6 +90,160 @@ __device__ __forceinline__ bool curve_ok(int64_t lo, int64_t hi, int64_t n_nodes
     return lo >= 0 && hi <= n_nodes && hi - lo >= 4 && ((hi - lo) & 1) == 0;
 }
 
+// e^{2 pi i num / den}, 0 <= num < den
+struct Cx { double r, i; };
+__device__ __forceinline__ Cx root(int64_t num, int64_t den) {
+    Cx z;
+    sincospi(2.0 * (double)num / (double)den, &z.i, &z.r);
+    return z;
+}
+__device__ __forceinline__ Cx mul(Cx a, Cx b) { return {a.r * b.r - a.i * b.i, a.r * b.i + a.i * b.r}; }
+
+// use(a, e^{2 pi i (base + a step) / den}, load(a)) for a = a0 .. a1-1 (0 <= base,
+// step < den), the loads of eight terms issued together (past the end: zero
+// terms): one term's at a time wait for a cache miss each.  A term's factor is
+// at most six products away from sincospi values (a chain over all of an
+// anchor's terms doubles the error of the derivatives).
+template <class L, class F>
+__device__ __forceinline__ void rotate(int a0, int a1, int64_t base, int64_t step, int64_t den, L &&load, F &&use) {
+    constexpr int kBatch = 8;
+    Cx w[kBatch + 1] = {{1.0, 0.0}, root(step, den), root(2 * step % den, den), {}, root(4 * step % den, den),
+                        {}, {}, {}, root(8 * step % den, den)};
+    w[3] = mul(w[2], w[1]);
+#pragma unroll
+    for (int e = 5; e < kBatch; ++e) w[e] = mul(w[4], w[e - 4]);
+    for (int s0 = a0; s0 < a1; s0 += kAnchor) {
+        Cx z = root((base + s0 * step) % den, den);
+        const int s1 = min(s0 + kAnchor, a1);
+        for (int a = s0; a < s1; a += kBatch) {
+            double4 v[kBatch];
+#pragma unroll
+            for (int e = 0; e < kBatch; ++e) v[e] = load(min(a + e, s1 - 1));
+#pragma unroll
+            for (int e = 0; e < kBatch; ++e)
+                use(a + e, e ? mul(z, w[e]) : z, a + e < s1 ? v[e] : double4{0.0, 0.0, 0.0, 0.0});
+            z = mul(z, w[kBatch]);
+        }
+    }
+}
+
+// N1 of the curve at lo (0: direct route), from wall_factor
+__device__ __forceinline__ int factor_of(const WallArgs &a, int64_t lo, int64_t N) {
+    const int n1 = (int)((const Coef8 *)a.coef)[lo + N - 1].v[4];
+    return n1 >= 2 && N % n1 == 0 ? n1 : 0;
+}
+
+// a wave per curve: N1, and the fine curve's offset where one is asked for
+__global__ __launch_bounds__(256) void wall_factor(WallArgs a) {
+    const int c = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave), lane = threadIdx.x & (kWave - 1);
+    if (c > a.n_curves) return;
+    const int64_t lo = a.off[c];
+    if (a.ooff && lane == 0) a.ooff[c] = (int32_t)lo * a.P;
+    if (c == a.n_curves) return;
+    const int64_t hi = a.off[c + 1];
+    if (!curve_ok(lo, hi, a.n_nodes)) return;
+    const uint32_t N = (uint32_t)(hi - lo);
+    uint32_t best = 1;
+    for (uint64_t t = 2 + lane; t * t <= N; t += kWave)
+        if (N % (uint32_t)t == 0) best = (uint32_t)t;
+#pragma unroll
+    for (int m = kWave / 2; m >= 1; m >>= 1) best = max(best, (uint32_t)__shfl_xor((int)best, m, kWave));
+    const bool fast = 8ull * (best + N / best) < N;
+    if (lane == 0) ((Coef8 *)a.coef)[hi - 1].v[4] = fast ? (double)best : 0.0;
+}
+
+// Z += (v.x + i v.y) z, F += (v.z + i v.w) z
+__device__ __forceinline__ void add_turned(Cx &Z, Cx &F, Cx z, double4 v) {
+    Z.r = __builtin_fma(v.x, z.r, __builtin_fma(-v.y, z.i, Z.r));
+    Z.i = __builtin_fma(v.x, z.i, __builtin_fma(v.y, z.r, Z.i));
+    F.r = __builtin_fma(v.z, z.r, __builtin_fma(-v.w, z.i, F.r));
+    F.i = __builtin_fma(v.z, z.i, __builtin_fma(v.w, z.r, F.i));
+}
+
+// Factored stage 1, item l = b N1 + k1: sum over a of the values at node
+// N2 a + b (positions relative to the first node: y's mean would leave its
+// rounding in x) times e^{-2 pi i a k1 / N1}, and the twiddle factor e^{-2 pi i b k1 / N}
+__device__ __forceinline__ void factored_dft_a(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t l, double s) {
+    const int N2 = (int)(N / N1), k1 = (int)(l % N1), b = (int)(l / N1);
+    const double sd = s * a.d / (double)N, x0 = a.x[lo], y0 = a.y[lo];
+    Cx Z{0, 0}, F{0, 0};
+    rotate(
+        0, N1, 0, (N1 - k1) % N1, N1,
+        [&](int i) {
+            const int64_t j = (int64_t)N2 * i + b, g = lo + j;
+            return double4{(a.x[g] - x0) - sd * (double)j, a.y[g] - y0, a.fx[g], a.fy[g]};
+        },
+        [&](int, Cx z, double4 v) { add_turned(Z, F, z, v); });
+    const Cx t = root((N - (int64_t)b * k1 % N) % N, N);
+    Z = mul(Z, t);
+    F = mul(F, t);
+    double4 *o = (double4 *)(((Coef8 *)a.part1)[lo + l].v);
+    *o = double4{Z.r, Z.i, F.r, F.i};
+}
+
+// and item k = k1 + N1 k2: coefficient k of both complex series
+__device__ __forceinline__ void factored_dft_b(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t k) {
+    const int N2 = (int)(N / N1), k1 = (int)(k % N1), k2 = (int)(k / N1);
+    const Coef8 *T = (const Coef8 *)a.part1 + lo + k1;
+    Cx Z{0, 0}, F{0, 0};
+    rotate(
+        0, N2, 0, (N2 - k2) % N2, N2, [&](int b) { return *(const double4 *)T[(int64_t)b * N1].v; },
+        [&](int, Cx z, double4 v) { add_turned(Z, F, z, v); });
+    *(double4 *)((Coef8 *)a.coef)[lo + k].v = double4{Z.r, Z.i, F.r, F.i};
+}
+
+// Factored stage 2 at the shift r / P of a node spacing, item l = b N1 + k1:
+// sum over a of the coefficients k = N2 a + b (frequency k below N/2, k - N
+// above) of the first series, its derivative and the second, times
+// e^{2 pi i a (P k1 + r) / (P N1)} (less r / P of a turn above N/2), and
+// e^{2 pi i b (P k1 + r) / (P N)}; the Nyquist term by cos(pi r / P), its
+// derivative by -N/2 sin(pi r / P), times (-1)^q at node q
+__device__ __forceinline__ void factored_synth_a(const WallArgs &a, int64_t lo, int64_t N, int N1, int r, int64_t l) {
+    const int N2 = (int)(N / N1), k1 = (int)(l % N1), b = (int)(l / N1), h = (int)(N / 2);
+    const int64_t P = a.P, step = P * k1 + r;
+    const Coef8 *coef = (const Coef8 *)a.coef + lo;
+    Cx Z{0, 0}, D{0, 0}, F{0, 0};
+    const auto load = [&](int i) { return *(const double4 *)coef[N2 * i + b].v; };
+    const auto add = [&](double kd, Cx z, double4 v) {
+        const double pr = __builtin_fma(v.x, z.r, -v.y * z.i), pi = __builtin_fma(v.x, z.i, v.y * z.r);
+        Z.r += pr;
+        Z.i += pi;
+        D.r = __builtin_fma(-kd, pi, D.r);
+        D.i = __builtin_fma(kd, pr, D.i);
+        F.r = __builtin_fma(v.z, z.r, __builtin_fma(-v.w, z.i, F.r));
+        F.i = __builtin_fma(v.z, z.i, __builtin_fma(v.w, z.r, F.i));
+    };
+    // k = N2 i + b < h for i < i0, > h for i >= i1
+    const int i0 = b < h ? (h - b + N2 - 1) / N2 : 0, i1 = b <= h ? (h - b) / N2 + 1 : 0;
+    rotate(0, i0, 0, step, P * N1, load, [&](int i, Cx z, double4 v) { add((double)(N2 * i + b), z, v); });
+    rotate(i1, N1, (P - r) % P * N1, step, P * N1, load,
+           [&](int i, Cx z, double4 v) { add((double)(N2 * i + b) - (double)N, z, v); });
+    const Cx t = root((int64_t)b * step % (P * N), P * N);
+    Z = mul(Z, t);
+    D = mul(D, t);
+    F = mul(F, t);
+    if (i0 < i1) {                                      // h = N2 i0 + b
+        const double4 v = *(const double4 *)coef[h].v;
+        double sn, cs;
+        sincospi((double)r / (double)P, &sn, &cs);
+        const double e = (k1 & 1) ? -1.0 : 1.0, c = e * cs, ds = -e * (double)h * sn;   // e^{2 pi i h k1 / N}
+        Z.r = __builtin_fma(c, v.x, Z.r);
+        Z.i = __builtin_fma(c, v.y, Z.i);
+        D.r = __builtin_fma(ds, v.x, D.r);
+        D.i = __builtin_fma(ds, v.y, D.i);
+        F.r = __builtin_fma(c, v.z, F.r);
+        F.i = __builtin_fma(c, v.w, F.i);
+    }
+    const int64_t nf = P * a.n_nodes;
+    double *o = a.part2 + P * (lo + l) + r;             // shifts side by side: the next step's lanes
+    o[0] = Z.r;
+    o[nf] = Z.i;
+    o[2 * nf] = F.r;
+    o[3 * nf] = F.i;
+    o[4 * nf] = D.r;
+    o[5 * nf] = D.i;
+}
+
 // stage 1 sums for coefficient k of the curve at lo with N nodes, over its
 // nodes jb .. je-1
 template <bool UNI>
@@ -102,10 +280,16 @@ __global__ __launch_bounds__(256) void wall_dft_part(WallArgs a) {
     if (g >= a.n_nodes) return;
     const int c = find_curve(a.off, a.n_curves, g, 1);
     const int64_t lo = a.off[c], hi = a.off[c + 1], N = hi - lo, k = g - lo;
-    if (!curve_ok(lo, hi, a.n_nodes) || k < 0 || k > N / 2) return;
+    if (!curve_ok(lo, hi, a.n_nodes) || k < 0 || k >= N) return;
+    const int N1 = factor_of(a, lo, N);
+    if (N1 ? blockIdx.y > 0 : k > N / 2) return;
+    const double s = a.x[lo + 1] > a.x[lo] ? 1.0 : -1.0;
+    if (N1) {
+        factored_dft_a(a, lo, N, N1, k, s);
+        return;
+    }
     const int64_t S = a.s1, sc = blockIdx.y, len = (N + S - 1) / S;
     const int64_t jb = min(sc * len, N), je = min(jb + len, N);
-    const double s = a.x[lo + 1] > a.x[lo] ? 1.0 : -1.0;
     double re[4] = {0, 0, 0, 0}, im[4] = {0, 0, 0, 0};
     const int lo_u = __builtin_amdgcn_readfirstlane((int)lo);
     if (__all(lo == (int64_t)lo_u)) {
@@ -126,13 +310,20 @@ __global__ __launch_bounds__(256) void wall_dft_part(WallArgs a) {
     ((Coef8 *)a.part1)[sc * a.n_nodes + lo + k] = o;
 }
 
-// the chunks' partial coefficients summed in chunk order
+// the chunks' partial coefficients summed in chunk order; the factored
+// route's second step
 __global__ __launch_bounds__(256) void wall_dft_sum(WallArgs a) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.n_nodes) return;
     const int c = find_curve(a.off, a.n_curves, g, 1);
     const int64_t lo = a.off[c], hi = a.off[c + 1], N = hi - lo, k = g - lo;
-    if (!curve_ok(lo, hi, a.n_nodes) || k < 0 || k > N / 2) return;
+    if (!curve_ok(lo, hi, a.n_nodes) || k < 0 || k >= N) return;
+    const int N1 = factor_of(a, lo, N);
+    if (N1) {
+        factored_dft_b(a, lo, N, N1, k);
+        return;
+    }
+    if (k > N / 2) return;
     const Coef8 *p = (const Coef8 *)a.part1;
     Coef8 o = p[g];
     for (int sc = 1; sc < a.s1; ++sc) {
@@ -195,7 +386,8 @@ __device__ __forceinline__ void synth_sums(const Coef8 *coef, int64_t lo, int64_
 // stage 2, split over the modes 1 .. h-1: work-item g, chunk blockIdx.y.
 // Curve c owns the P N / 2 work-items from ceil(P off[c] / 2); item j <= M / 4
 // of the curve serves the fine points j, M - j, M/2 + j and M/2 - j (the
-// rest return at once).  Six partial sums per fine point and chunk.
+// rest return at once).  Six partial sums per fine point and chunk.  Factored
+// curves: work-item t of chunk y takes item t + y times the curve's work-items.
 __global__ __launch_bounds__(256) void wall_synth_part(WallArgs a) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t P = a.P, nf = P * a.n_nodes;
@@ -203,7 +395,14 @@ __global__ __launch_bounds__(256) void wall_synth_part(WallArgs a) {
     const int c = find_curve(a.off, a.n_curves, 2 * g, P);
     const int64_t lo = a.off[c], hi = a.off[c + 1], N = hi - lo, M = P * N, h = N / 2;
     const int64_t j = g - (P * lo + 1) / 2;
-    if (!curve_ok(lo, hi, a.n_nodes) || j < 0 || j > M / 4) return;
+    if (!curve_ok(lo, hi, a.n_nodes) || j < 0) return;
+    const int N1 = factor_of(a, lo, N);
+    if (N1) {
+        const int64_t m = j + blockIdx.y * h * P;
+        if (j < h * P && m < M) factored_synth_a(a, lo, N, N1, (int)(m % P), m / P);
+        return;
+    }
+    if (j > M / 4 || blockIdx.y >= a.s2) return;
     const int64_t S = a.s2, sc = blockIdx.y, len = (h - 1 + S - 1) / S;
     const int64_t kb = min(1 + sc * len, h), ke = min(kb + len, h);
     const Coef8 *coef = (const Coef8 *)a.coef;
@@ -246,8 +445,84 @@ __global__ __launch_bounds__(256) void wall_synth_part(WallArgs a) {
     }
 }
 
+// node, normal, weight and density of fine point m of the curve at lo from
+// the four series' values and the first two's derivatives
+__device__ __forceinline__ void fine_point(const WallArgs &a, int64_t lo, int64_t M, int64_t m, double s,
+                                           const double val[4], const double der[2]) {
+    const int64_t g = a.P * lo + m, j = lo + m / a.P;
+    const double dX = der[0] + s * a.d / (2.0 * M_PI), dY = der[1];
+    const double sp = sqrt(dX * dX + dY * dY);
+    const double o = (-dY * a.nx[j] + dX * a.ny[j]) > 0.0 ? 1.0 : -1.0;
+    a.ox[g] = val[0] + s * a.d * ((double)m / (double)M);
+    a.oy[g] = val[1];
+    a.onx[g] = -o * dY / sp;
+    a.ony[g] = o * dX / sp;
+    a.ow[g] = (2.0 * M_PI / (double)M) * sp;
+    a.ofx[g] = val[2];
+    a.ofy[g] = val[3];
+}
+
+// Factored stage 2, last step, item t = (g2 N1 + k1) P + r: fine points
+// P (k1 + N1 k2) + r for k2 = 2 g2 and 2 g2 + 1, the sums over b of stage 2's
+// first step times e^{2 pi i b k2 / N2}
+constexpr int kSynthOut = 2;
+__device__ __forceinline__ void factored_synth_b(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t t, double s) {
+    const int64_t P = a.P, M = P * N, nf = P * a.n_nodes;
+    const int N2 = (int)(N / N1), r = (int)(t % P), k1 = (int)(t / P % N1);
+    const int64_t g2 = t / (P * N1);
+    if (kSynthOut * g2 >= N2) return;
+    const double *T = a.part2 + P * (lo + k1) + r;
+    const int64_t row = P * N1;
+    double acc[kSynthOut][6] = {};
+    // factors as in rotate(): four terms from one value, re-anchored every 16
+    constexpr int kBatch = 4, kTurn = 16;
+    Cx w[kSynthOut][kBatch + 1], z[kSynthOut];
+    int k2[kSynthOut];
+#pragma unroll
+    for (int e = 0; e < kSynthOut; ++e) {
+        k2[e] = (int)min(kSynthOut * g2 + e, (int64_t)N2 - 1);
+        w[e][1] = root(k2[e], N2);
+        w[e][2] = root(2 * (int64_t)k2[e] % N2, N2);
+        w[e][3] = mul(w[e][2], w[e][1]);
+        w[e][4] = root(4 * (int64_t)k2[e] % N2, N2);
+    }
+    for (int b0 = 0; b0 < N2; b0 += kBatch) {
+        if (b0 % kTurn == 0) {
+#pragma unroll
+            for (int e = 0; e < kSynthOut; ++e) z[e] = root((int64_t)b0 * k2[e] % N2, N2);
+        }
+#pragma unroll
+        for (int f = 0; f < kBatch; ++f) {
+            double v[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) v[q] = b0 + f < N2 ? T[q * nf + (b0 + f) * row] : 0.0;
+#pragma unroll
+            for (int e = 0; e < kSynthOut; ++e) {
+                const Cx y = f ? mul(z[e], w[e][f]) : z[e];
+#pragma unroll
+                for (int q = 0; q < 6; q += 2) {
+                    acc[e][q] = __builtin_fma(v[q], y.r, __builtin_fma(-v[q + 1], y.i, acc[e][q]));
+                    acc[e][q + 1] = __builtin_fma(v[q], y.i, __builtin_fma(v[q + 1], y.r, acc[e][q + 1]));
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kSynthOut; ++e) z[e] = mul(z[e], w[e][kBatch]);
+    }
+    const double invN = 1.0 / (double)N;
+#pragma unroll
+    for (int e = 0; e < kSynthOut; ++e) {
+        if (kSynthOut * g2 + e >= N2) return;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) acc[e][q] *= invN;
+        acc[e][0] += a.x[lo];
+        acc[e][1] += a.y[lo];
+        fine_point(a, lo, M, P * (k1 + (int64_t)N1 * k2[e]) + r, s, acc[e], acc[e] + 4);
+    }
+}
+
 // stage 2 finish: the chunks' sums in chunk order, the mean and Nyquist
-// terms, then nodes, normals, weights and density of fine point g
+// terms, then fine point g; the factored route's last step
 __global__ __launch_bounds__(256) void wall_synth_fin(WallArgs a) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t P = a.P, nf = P * a.n_nodes;
@@ -259,6 +534,12 @@ __global__ __launch_bounds__(256) void wall_synth_fin(WallArgs a) {
         a.ox[g] = a.oy[g] = a.onx[g] = a.ony[g] = a.ow[g] = a.ofx[g] = a.ofy[g] = nan;
         return;
     }
+    const double s = a.x[lo + 1] > a.x[lo] ? 1.0 : -1.0;
+    const int N1 = factor_of(a, lo, N);
+    if (N1) {
+        factored_synth_b(a, lo, N, N1, m, s);
+        return;
+    }
     double acc[4] = {0, 0, 0, 0}, dac[2] = {0, 0};
     for (int sc = 0; sc < a.s2; ++sc) {
         const double *p = a.part2 + (int64_t)sc * 6 * nf + g;
@@ -267,7 +548,6 @@ __global__ __launch_bounds__(256) void wall_synth_fin(WallArgs a) {
         dac[0] += p[4 * nf];
         dac[1] += p[5 * nf];
     }
-    const double s = a.x[lo + 1] > a.x[lo] ? 1.0 : -1.0;
     const Coef8 *coef = (const Coef8 *)a.coef;
     const Coef8 V0 = coef[lo], Vh = coef[lo + h];
     double sh, ch;
@@ -278,22 +558,7 @@ __global__ __launch_bounds__(256) void wall_synth_fin(WallArgs a) {
     for (int q = 0; q < 4; ++q) val[q] = (V0.v[2 * q] + 2.0 * acc[q] + Vh.v[2 * q] * ch) * invN;
 #pragma unroll
     for (int q = 0; q < 2; ++q) der[q] = (2.0 * dac[q] - (double)h * Vh.v[2 * q] * sh) * invN;
-    const double dX = der[0] + s * a.d / (2.0 * M_PI), dY = der[1];
-    const double sp = sqrt(dX * dX + dY * dY);
-    const int64_t j = lo + m / P;
-    const double o = (-dY * a.nx[j] + dX * a.ny[j]) > 0.0 ? 1.0 : -1.0;
-    a.ox[g] = val[0] + s * a.d * ((double)m / (double)M);
-    a.oy[g] = val[1];
-    a.onx[g] = -o * dY / sp;
-    a.ony[g] = o * dX / sp;
-    a.ow[g] = (2.0 * M_PI / (double)M) * sp;
-    a.ofx[g] = val[2];
-    a.ofy[g] = val[3];
-}
-
-__global__ void wall_fine_offsets(const int32_t *__restrict__ off, int n_curves, int P, int32_t *__restrict__ foff) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i <= n_curves) foff[i] = off[i] * P;
+    fine_point(a, lo, M, m, s, val, der);
 }
 
 // u (+)= uf - uc, v (+)= vf - vc: the difference is rounded first, so an
@@ -369,15 +634,13 @@ WallScratch wall_scratch(int64_t n_nodes, int P) {
 }
 
 hipError_t wall_upsample_launch(const WallArgs &a, hipStream_t st) {
-    if (a.n_curves > 0 && a.off && a.ooff) {
-        hipLaunchKernelGGL(wall_fine_offsets, dim3((unsigned)((a.n_curves + 1 + 255) / 256)), dim3(256), 0, st,
-                           a.off, a.n_curves, a.P, a.ooff);
-    }
+    if (a.n_curves > 0 && a.off)
+        hipLaunchKernelGGL(wall_factor, dim3((unsigned)((a.n_curves + 1 + 3) / 4)), dim3(256), 0, st, a);
     if (a.n_nodes > 0) {
         const unsigned g1 = grid(a.n_nodes), g2 = grid(((int64_t)a.P * a.n_nodes + 1) / 2);
         hipLaunchKernelGGL(wall_dft_part, dim3(g1, (unsigned)a.s1), dim3(256), 0, st, a);
         hipLaunchKernelGGL(wall_dft_sum, dim3(g1), dim3(256), 0, st, a);
-        hipLaunchKernelGGL(wall_synth_part, dim3(g2, (unsigned)a.s2), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(wall_synth_part, dim3(g2, (unsigned)std::max(a.s2, 2)), dim3(256), 0, st, a);
         hipLaunchKernelGGL(wall_synth_fin, dim3(grid((int64_t)a.P * a.n_nodes)), dim3(256), 0, st, a);
     }
     return hipGetLastError();

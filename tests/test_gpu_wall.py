@@ -366,3 +366,61 @@ def test_wall_auto_extremes_and_network_gain():
               flush=True)
         assert E <= rel
     assert used[0] > 0.2
+
+
+def _long_double_upsample(x, y, nx, ny, fx, fy, d, P, m):
+    # the trigonometric interpolants and their derivatives at fine points m,
+    # direct sums in long double
+    L = np.longdouble
+    pi = L("3.14159265358979323846264338327950288")
+    N, M, h = len(x), P * len(x), len(x) // 2
+    s = 1 if x[1] > x[0] else -1
+    j = np.arange(N)
+    ang, fang = 2 * pi * j / L(N), 2 * pi * np.arange(M) / L(M)
+    cs, sn, fc, fs = np.cos(ang), np.sin(ang), np.cos(fang), np.sin(fang)
+    out, der = [], []
+    for v in (x.astype(L) - L(s * d) * j / L(N), y.astype(L), fx.astype(L), fy.astype(L)):
+        f, g = np.zeros(len(m), L), np.zeros(len(m), L)
+        for k in range(h + 1):
+            i, q = j * k % N, m * k % M
+            a, b, w = (v * cs[i]).sum(), -(v * sn[i]).sum(), 2 if 0 < k < h else 1
+            if k == h:
+                b = L(0)
+            f += w * (a * fc[q] - b * fs[q])
+            g -= w * k * (a * fs[q] + b * fc[q])
+        out.append(f / N)
+        der.append(g / N)
+    dx, dy = der[0] + L(s * d) / (2 * pi), der[1]
+    sp = np.hypot(dx, dy)
+    c = m // P
+    o = np.where(-dy * nx[c] + dx * ny[c] > 0, 1, -1)
+    return (out[0] + L(s * d) * m / L(M), out[1], -o * dy / sp, o * dx / sp, 2 * pi / M * sp, out[2], out[3])
+
+
+@pytest.mark.parametrize("P", [1, 2, 7, 8])
+def test_upsample_factored_and_direct_curves(P):
+    # N = N1 N2 with N1 the largest divisor up to sqrt(N); factored when
+    # 8 (N1 + N2) < N: 256 = 16 x 16 lies just outside, 270 = 15 x 18 just
+    # inside; 514 = 2 x 257 is direct at any size; 1,000 = 25 x 40, 4,094 =
+    # 46 x 89 (odd N2, ragged last batches of 8 terms), 2,304 = 48 x 48 (the
+    # Nyquist mode in the first column) factored; both routes in one call.
+    # Against long double at up to 200 fine points a curve, the first and last
+    # ones among them: double FFTs are themselves 1.3e-11 off in the normals
+    # at 4,094 nodes.
+    walls, d = _mixed_walls((256, 270, 514, 1000, 4094, 2304), seed=20 + P)
+    g, off = _gpu_upsample(walls, d, P)
+    assert np.array_equal(off, P * walls.curve_off)
+    rng = np.random.default_rng(P)
+    got, ref = [[] for _ in NAMES], [[] for _ in NAMES]
+    for c in range(walls.n_curves):
+        s = slice(walls.curve_off[c], walls.curve_off[c + 1])
+        M = int(off[c + 1] - off[c])
+        m = np.unique(np.r_[np.arange(4), M - 1 - np.arange(4), rng.integers(0, M, 192)])
+        r = _long_double_upsample(walls.x[s], walls.y[s], walls.nx[s], walls.ny[s], walls.fx[s], walls.fy[s], d, P, m)
+        for e, (a, b) in enumerate(zip(g, r)):
+            got[e].append(a[off[c] + m])
+            ref[e].append(b)
+    for k, a, b in zip(NAMES, got, ref):
+        err = _rel(np.concatenate(a), np.concatenate(b))
+        print(f"factored P={P} {k} {err:.2e}", flush=True)
+        assert err <= (TOL_DER if k in ("nx", "ny", "w") else TOL_VAL), (k, err)
