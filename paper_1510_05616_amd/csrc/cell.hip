@@ -19,7 +19,7 @@
 // operand within 2^30 elements), X = A^-1 B by the triangular sweeps,
 // S = Q - C X (GEMM), SVD of the small S and its truncated pseudo-inverse.
 // Solve: y = A^-1 v (row permutation, forward and backward sweeps),
-// c = S^+ (g - C y), tau = y - X c.
+// c = S^+ (g - C y), tau = y - X c, all by kernels of this file.
 #include "lu_plan.h"
 #include "s2d_cell.h"
 #include "s2d_internal.h"
@@ -342,6 +342,77 @@ __global__ __launch_bounds__(kTriThreads) void tri_step(const double *__restrict
         for (int k = 0; k < 8; ++k) t += red[k * 64 + lane];
         y[r] -= t;
     }
+}
+
+// The solve's three matrix-vector products (column-major): 64 rows per
+// workgroup, a lane each, the columns in eight parts by wave, summed in LDS in
+// wave order.  The library's product of the 128 x 8,000 C took 0.24 ms, as its
+// rows alone fill two workgroups; here the columns are split as well.  Channel
+// response at 8,000 unknowns: 0.28 ms and two copies before, these take 23 us
+// (the sweeps before them 0.42 ms: 64 dependent launches).
+constexpr int kGemvThreads = 512;
+__device__ __forceinline__ double sum_waves(double v, double *red) {
+    red[threadIdx.x] = v;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x < 64)
+#pragma unroll
+        for (int k = 0; k < kGemvThreads / 64; ++k) t += red[64 * k + threadIdx.x];
+    return t;
+}
+// sum of col[j ld] v[j] over j = j0, j0 + step, ... < j1
+__device__ __forceinline__ double dot_strided(const double *col, int64_t ld, const double *v, int64_t j0, int64_t j1,
+                                              int step) {
+    double acc = 0.0;
+#pragma unroll 8
+    for (int64_t j = j0; j < j1; j += step) acc = __builtin_fma(col[j * ld], v[j], acc);
+    return acc;
+}
+
+// part[b m + i] = sum of C[i, j] y[j] over block b's share of the n columns,
+// less g_i in block 0 (the caller's c may be its g: only this kernel reads g)
+__global__ __launch_bounds__(kGemvThreads) void cell_cy(int m, int64_t n, const double *__restrict__ C,
+                                                        const double *__restrict__ y, const double *__restrict__ g,
+                                                        double *__restrict__ part) {
+    __shared__ double red[kGemvThreads];
+    const int i = blockIdx.x * 64 + (threadIdx.x & 63), w = threadIdx.x >> 6;
+    const int64_t len = (n + gridDim.y - 1) / gridDim.y, j0 = blockIdx.y * len, j1 = min(j0 + len, n);
+    const double t = sum_waves(i < m ? dot_strided(C + i, m, y, j0 + w, j1, kGemvThreads / 64) : 0.0, red);
+    if (w == 0 && i < m) part[(int64_t)blockIdx.y * m + i] = blockIdx.y == 0 ? t - g[i] : t;
+}
+
+// c = P (g - C y), C y - g from its nb partial sums, 64 entries at a time
+__global__ __launch_bounds__(kGemvThreads) void cell_coef(int nc, int m, int nb, const double *__restrict__ P,
+                                                          const double *__restrict__ part, double *__restrict__ c) {
+    __shared__ double red[kGemvThreads], rr[64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, row = blockIdx.x * 64 + lane;
+    double acc = 0.0;
+    for (int i0 = 0; i0 < m; i0 += 64) {
+        const int i = i0 + lane;
+        double s = 0.0;
+        if (i < m) {
+#pragma unroll 8
+            for (int b = w; b < nb; b += kGemvThreads / 64) s += part[(int64_t)b * m + i];
+        }
+        const double t = sum_waves(s, red);
+        if (w == 0) rr[lane] = -t;
+        __syncthreads();
+        if (row < nc) acc += dot_strided(P + row + (int64_t)i0 * nc, nc, rr, w, min(64, m - i0), kGemvThreads / 64);
+        __syncthreads();
+    }
+    const double t = sum_waves(acc, red);
+    if (w == 0 && row < nc) c[row] = t;
+}
+
+// tau = y - X c
+__global__ __launch_bounds__(kGemvThreads) void cell_tau(int64_t n, int nc, const double *__restrict__ X,
+                                                         const double *__restrict__ y, const double *__restrict__ c,
+                                                         double *__restrict__ tau) {
+    __shared__ double red[kGemvThreads];
+    const int64_t r = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+    const int w = threadIdx.x >> 6;
+    const double t = sum_waves(r < n ? dot_strided(X + r, n, c, w, nc, kGemvThreads / 64) : 0.0, red);
+    if (w == 0 && r < n) tau[r] = y[r] - t;
 }
 
 unsigned grid(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -692,30 +763,23 @@ std::string cell_solve(const CellArgs &g, const double *v, const double *gv, dou
     const CellLayout L = cell_layout(g);
     char *b = (char *)ws;
     double *A = (double *)(b + L.A), *X = (double *)(b + L.X), *C = (double *)(b + L.C), *P = (double *)(b + L.P);
-    double *y = (double *)(b + L.y), *rr = (double *)(b + L.rr);
+    double *y = (double *)(b + L.y);
     const int32_t *perm = (const int32_t *)(b + L.perm);
     const int64_t n = 2 * g.n_wall;
-    const rocblas_int nc = 2 * g.M, mr = 4 * g.K;
-    hipError_t e = hipMemcpyAsync(rr, gv, (size_t)mr * 8, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = gather_launch(n, 1, v, n, perm, y, n, st);                 // P v
+    const int nc = 2 * g.M, mr = 4 * g.K;
+    hipError_t e = gather_launch(n, 1, v, n, perm, y, n, st);                           // P v
     if (e == hipSuccess)                                                                 // y = A^-1 v
         e = tri_solve(A, (const double *)(b + L.Tf), (const double *)(b + L.Tb), n, y, (double *)(b + L.w), y, st);
     if (e != hipSuccess) return std::string("cell solve: ") + hipGetErrorString(e);
-    std::lock_guard<std::mutex> lk(g_hmu);
-    std::string err;
-    rocblas_handle h = handle_for(st, err);
-    if (!h) return err;
-    const double one = 1.0, minus_one = -1.0, zero = 0.0;
-    rocblas_status s = rocblas_dgemv(h, rocblas_operation_none, mr, (rocblas_int)n, &minus_one, C, mr, y, 1, &one,
-                                     rr, 1);                                             // g - C y
-    if (s != rocblas_status_success) return rb_err("rocblas_dgemv", s);
-    s = rocblas_dgemv(h, rocblas_operation_none, nc, mr, &one, P, nc, rr, 1, &zero, c, 1);         // c = S^+ (.)
-    if (s != rocblas_status_success) return rb_err("rocblas_dgemv", s);
-    e = hipMemcpyAsync(tau, y, (size_t)n * 8, hipMemcpyDeviceToDevice, st);
+    // the partial sums of C y in S, which the factor has done with
+    const int nb = (int)std::min<int64_t>(nc, (n + 63) / 64);
+    double *part = (double *)(b + L.S);
+    hipLaunchKernelGGL(cell_cy, dim3((unsigned)((mr + 63) / 64), (unsigned)nb), dim3(kGemvThreads), 0, st, mr, n, C, y,
+                       gv, part);
+    hipLaunchKernelGGL(cell_coef, dim3((unsigned)((nc + 63) / 64)), dim3(kGemvThreads), 0, st, nc, mr, nb, P, part, c);
+    hipLaunchKernelGGL(cell_tau, dim3((unsigned)((n + 63) / 64)), dim3(kGemvThreads), 0, st, n, nc, X, y, c, tau);
+    e = hipGetLastError();
     if (e != hipSuccess) return std::string("cell solve: ") + hipGetErrorString(e);
-    s = rocblas_dgemv(h, rocblas_operation_none, (rocblas_int)n, nc, &minus_one, X, (rocblas_int)n, c, 1, &one, tau,
-                      1);                                                                // y - X c
-    if (s != rocblas_status_success) return rb_err("rocblas_dgemv", s);
     return "";
 }
 

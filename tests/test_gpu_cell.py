@@ -160,3 +160,42 @@ def test_poiseuille_at_16000_nodes_per_wall():
     assert eu < 1e-9 and ep < 1e-9
     del cell
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("Nw,K,M", [(8, 1, 1), (16, 2, 33), (96, 17, 33), (130, 33, 64), (300, 16, 1)])
+def test_solve_products_at_uneven_sizes(Nw, K, M):
+    # the products of the solve at rows that end inside a 64-row workgroup
+    # (4K = 4, 8, 68, 132; 2M = 2, 66, 128; 4 Nw = 32, 64, 384, 520) and few
+    # column parts (min(2M, n / 64)), against float64 numpy on the assembled blocks.
+    # The cut-off lies in the widest gap of singular values above 1e-4 s_0, so
+    # the truncated inverse amplifies rounding (1e-14 in S) by at most 1e4:
+    # held to 1e-9.  c over g, tau over v: a caller may reuse its inputs.
+    import torch
+    from paper_1510_05616_amd.cell import Cell
+    walls, sy, d = synth.make_channel(Nw, K)
+    cell = Cell(walls, sy, d, M, MU)
+    A, B, C, Q = (q.cpu().numpy() for q in cell.assemble())
+    S = Q - C @ np.linalg.solve(A, B)
+    U, sv, Vt = np.linalg.svd(S, full_matrices=False)
+    kept = np.append(sv[sv > 1e-4 * sv[0]], 1e-4 * sv[0])
+    j = int(np.argmax(kept[:-1] / kept[1:]))
+    rcond = float(np.sqrt(kept[j] * kept[j + 1]) / sv[0])
+    cell.factor(rcond=rcond)
+    rng = np.random.default_rng(Nw + K)
+    v, g = rng.standard_normal(A.shape[0]), rng.standard_normal(4 * K)
+    y = np.linalg.solve(A, v)
+    c = Vt[:j + 1].T @ ((U[:, :j + 1].T @ (g - C @ y)) / sv[:j + 1])
+    tau = y - np.linalg.solve(A, B @ c)
+    f64 = dict(dtype=torch.float64, device="cuda")
+    size = max(4 * K, 2 * M)
+    gc = torch.zeros(size, **f64)
+    gc[:4 * K] = torch.as_tensor(g)
+    vt = torch.as_tensor(v, **f64)
+    t2, c2 = cell.solve(torch.as_tensor(v, **f64), torch.as_tensor(g, **f64))
+    cell.solve(vt, gc, tau=vt, c=gc)
+    torch.cuda.synchronize()
+    assert torch.equal(vt, t2) and torch.equal(gc[:2 * M], c2)
+    for got, ref in ((c2, c), (t2, tau)):
+        e = np.abs(got.cpu().numpy() - ref).max() / np.abs(ref).max()
+        print(f"Nw={Nw} K={K} M={M} rcond={rcond:.1e} kept {j + 1}: {e:.2e}", flush=True)
+        assert e < 1e-9
