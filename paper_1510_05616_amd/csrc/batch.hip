@@ -128,19 +128,38 @@ __global__ __launch_bounds__(256) void batch_kress_table(BatchTables t) {
     kress_table_curve(I.src[0].curve_off, (int32_t)(g - t.curve_pre[k]), I.src[0].n_nodes, I.kress, ctab);
 }
 
-__global__ __launch_bounds__(256) void batch_kress_self(BatchTables t) {
+// Four waves take the same 64 targets and every fourth node of their curves
+// each, and wave 0 adds the parts in order: with one thread per target, 64
+// channels of up to 40 vesicles x 128 nodes waited 152 us for the chains of
+// their longest curves (75 in four parts).
+constexpr int kSelfParts = 4;
+__global__ __launch_bounds__(kSelfParts * kWave) void batch_kress_self(BatchTables t) {
     __shared__ __attribute__((aligned(16))) double ltab[kLogTabWords];
+    __shared__ double red[kSelfParts - 1][2][kWave];
     fill_log_table(ltab);                           // before any thread returns
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= t.trg_off[t.n_inst]) return;
-    const int k = find_inst(t.trg_off, t.n_inst, g);
+    const int lane = threadIdx.x & (kWave - 1), part = threadIdx.x / kWave;
+    const int64_t g = (int64_t)blockIdx.x * kWave + lane;
+    const bool in = g < t.trg_off[t.n_inst];
+    const int k = in ? find_inst(t.trg_off, t.n_inst, g) : 0;
     const BatchInst &I = t.inst[k];
-    if (!I.self) return;
-    const int64_t i = g - t.trg_off[k];
+    const int64_t i = in ? g - t.trg_off[k] : 0;
+    const bool on = in && I.self;
     const s2d_curves &s = I.src[0];
-    double sx, sy;
-    kress_self_one(i, s.n_nodes, I.trg[0].on_curve, I.trg[0].on_node, s.curve_off, s.n_curves, s.x, s.y, s.nx,
-                   s.ny, s.w, s.fx, s.fy, I.kress, ltab, sx, sy);
+    double sx = 0.0, sy = 0.0;
+    if (on)
+        kress_self_one(i, s.n_nodes, I.trg[0].on_curve, I.trg[0].on_node, s.curve_off, s.n_curves, s.x, s.y, s.nx,
+                       s.ny, s.w, s.fx, s.fy, I.kress, ltab, sx, sy, part, kSelfParts);
+    if (part > 0) {
+        red[part - 1][0][lane] = sx;
+        red[part - 1][1][lane] = sy;
+    }
+    __syncthreads();
+    if (part > 0 || !on) return;
+#pragma unroll
+    for (int p = 0; p < kSelfParts - 1; ++p) {
+        sx += red[p][0][lane];
+        sy += red[p][1][lane];
+    }
     I.self[i] = sx;
     I.self[I.trg[0].n + i] = sy;
 }
@@ -428,7 +447,8 @@ hipError_t record_graph(BatchPlan &P, const BatchTables &t, int n_pre_targets, i
         hipLaunchKernelGGL(batch_sbsum, dim3((unsigned)((tot_sb + 3) / 4)), dim3(256), 0, st, t);
     if (any_self && tot_curves > 0) {
         hipLaunchKernelGGL(batch_kress_table, dim3((unsigned)tot_curves), dim3(256), 0, st, t);
-        hipLaunchKernelGGL(batch_kress_self, dim3((unsigned)((tot_trg + 255) / 256)), dim3(256), 0, st, t);
+        hipLaunchKernelGGL(batch_kress_self, dim3((unsigned)((tot_trg + kWave - 1) / kWave)), dim3(kSelfParts * kWave), 0,
+                           st, t);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return done(e);
