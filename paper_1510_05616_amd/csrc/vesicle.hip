@@ -16,6 +16,7 @@
 #include "self_impl.h"
 #include "s2d_far.h"
 #include "s2d_near.h"
+#include "s2d_vesicle_lu.h"
 #include "../../include/stokes2d_vesicle.h"
 
 #include <rocblas/rocblas.h>
@@ -664,12 +665,11 @@ __global__ __launch_bounds__(kVesBlock) void pc_fill_p(PcArgs a) {
     }
 }
 
-// Readies the factored blocks for pc_solve, one workgroup per curve: the row
+// Readies blocks factored by the library for pc_solve, one workgroup per curve: the row
 // interchanges composed into a permutation (over ipiv: row r of P_c z = v reads
 // v[ipiv[r]]), and each kTri x kTri diagonal block's two triangles replaced by
 // their inverses (L's unit diagonal implied).  A wave inverts a block: lane c
 // column c of L^-1, lane 32 + c column c of U^-1, by substitution in LDS.
-constexpr int kTri = 32;
 __global__ __launch_bounds__(kVesBlock) void pc_invert(int Nm, double *Pm, int32_t *ipiv) {
     __shared__ int32_t perm[3 * kVesMaxN];
     __shared__ double blk[kVesBlock / kWave][kTri][kTri + 1], inv[kVesBlock / kWave][2][kTri][kTri + 1];
@@ -1505,8 +1505,15 @@ int pc_build(StepCtx &C) {
     e = hipGetLastError();
     if (e != hipSuccess) return hipf(e, "preconditioner fill");
     rocblas_int *ipiv = (rocblas_int *)(b + C.L.ipiv), *info = (rocblas_int *)(b + C.L.info);
-    S2D_TRY(rbf(rocsolver_dgetrf_strided_batched(C.h, 3 * Nm, 3 * Nm, a.Pm, 3 * Nm, 9 * s1, ipiv, 3 * Nm, info, nc),
-                "preconditioner LU"));
+    // blocks of more rows than a workgroup has threads: the library's
+    const bool own = 3 * Nm <= kLuMax;
+    if (own) {
+        e = pc_lu_launch(3 * Nm, nc, a.Pm, ipiv, info, C.st);
+        if (e != hipSuccess) return hipf(e, "preconditioner LU launch");
+    } else {
+        S2D_TRY(rbf(rocsolver_dgetrf_strided_batched(C.h, 3 * Nm, 3 * Nm, a.Pm, 3 * Nm, 9 * s1, ipiv, 3 * Nm, info, nc),
+                    "preconditioner LU"));
+    }
     std::vector<rocblas_int> inf(nc);
     e = hipMemcpyAsync(inf.data(), info, nc * sizeof(rocblas_int), hipMemcpyDeviceToHost, C.st);
     if (e == hipSuccess) e = hipStreamSynchronize(C.st);
@@ -1516,7 +1523,7 @@ int pc_build(StepCtx &C) {
             return ves_fail(S2D_EINVAL, "the preconditioner block of curve " + std::to_string(c) +
                                             " is singular (a circular vesicle leaves the tension's constant "
                                             "mode undetermined)");
-    hipLaunchKernelGGL(pc_invert, dim3(nc), dim3(kVesBlock), 0, C.st, Nm, a.Pm, ipiv);
+    if (!own) hipLaunchKernelGGL(pc_invert, dim3(nc), dim3(kVesBlock), 0, C.st, Nm, a.Pm, ipiv);
     e = hipGetLastError();
     return e == hipSuccess ? S2D_OK : hipf(e, "preconditioner inverse launch");
 }
