@@ -218,7 +218,8 @@ __device__ __forceinline__ void slp64_src(const double (&px)[NI], double py, con
         P = m == 0 ? q : P * q;
     }
     by = __builtin_fma(ry, ts, by);
-    const double lq = log64_tab(P, ltab);
+    double lq = log64_tab(P, ltab);
+    if (MASK && NI == 1) lq = ok || m0 != 0 ? lq : 0.0;       // log64_tab(1) is zero to rounding only
     ax = __builtin_fma(s.gx, lq, ax);
     ay = __builtin_fma(s.gy, lq, ay);
 }
@@ -494,7 +495,9 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                     // iqr = 2^-e with qp = m 2^e, m in [1/2, 1): scaling by it is exact in
                     // float, and -1/2 sum g ln prod q = -(ln2/2) sum g log2(iqr prod q)
                     // - (ln2/2) e sum g
-                    const int e = min(max(__builtin_amdgcn_frexp_exp(qp), -100), 100);
+                    // (a masked superblock of the image n = 0 alone takes no reference:
+                    // what it excludes then adds an exact zero)
+                    const int e = NI == 1 && masked ? 0 : min(max(__builtin_amdgcn_frexp_exp(qp), -100), 100);
                     iqr[k] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
                     const double c = -kHalfLn2 * (double)e;
                     // and, for grouped images, the rational term's constant NI g_x (see slp32_src)
