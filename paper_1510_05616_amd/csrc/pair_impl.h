@@ -412,6 +412,22 @@ __device__ __forceinline__ bool far_offsets(const SubInfo &si, const double (&px
 template <int OP, int PREC, int TPT, int NI>
 __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int split, int lane, const double *ltab,
                                          double (&ox)[TPT], double (&oy)[TPT]) {
+    // superblock range of the split, wave-uniform: the loop runs on the scalar
+    // unit and the record addresses it forms stay scalar (n_sb < 2^31)
+    const int sbs = a.sbs;
+    const int sb0 = __builtin_amdgcn_readfirstlane((int)min((int64_t)split * a.sb_per_split, a.n_sb));
+    const int sb1 = __builtin_amdgcn_readfirstlane((int)min((int64_t)sb0 + a.sb_per_split, a.n_sb));
+
+    // Short splits are bound by the scalar loads' latency, one after another and
+    // from records that another XCD has just written: one vector load per line
+    // brings a split's records into this XCD's L2 beside the targets' loads.
+    uint32_t touched = 0;
+    if (sbs < kSuperBlock) {
+        constexpr uint32_t rec = PREC == S2D_FP64 ? sizeof(Rec64Of<OP>) : sizeof(Rec32Of<OP>);
+        const uint32_t bytes = (uint32_t)((sb1 - sb0) * sbs) * rec;
+        const char *r = (const char *)a.rec + (int64_t)sb0 * sbs * (int64_t)rec;
+        for (uint32_t o = (uint32_t)lane * 128; o < bytes; o += kWave * 128) touched |= *(const uint32_t *)(r + o);
+    }
 
     double tx[TPT], ty[TPT];
     int lo[TPT], hi[TPT];
@@ -442,6 +458,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
     }
     hlo = __builtin_amdgcn_readfirstlane(wave_min(hlo));
     hhi = __builtin_amdgcn_readfirstlane(wave_max(hhi));
+    asm volatile("" ::"v"(touched));                // keeps the loads; they came before the targets'
     double mx[TPT], my[TPT];                        // target normals (traction only)
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
@@ -449,12 +466,6 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
         mx[k] = tr ? a.tnx[ti[k]] : 0.0;
         my[k] = tr ? a.tny[ti[k]] : 0.0;
     }
-
-    // superblock range of the split, wave-uniform: the loop runs on the scalar
-    // unit and the record addresses it forms stay scalar (n_sb < 2^31)
-    const int sbs = a.sbs;
-    const int sb0 = __builtin_amdgcn_readfirstlane((int)min((int64_t)split * a.sb_per_split, a.n_sb));
-    const int sb1 = __builtin_amdgcn_readfirstlane((int)min((int64_t)sb0 + a.sb_per_split, a.n_sb));
 
     double ux[TPT], uy[TPT], vx[TPT], vy[TPT];     // vx, vy: FP64 single-layer log accumulators
 #pragma unroll

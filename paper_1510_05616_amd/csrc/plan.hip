@@ -63,11 +63,27 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
         if (!(fits && p.n_tiles * kMaxPairWaves >= fill))
             G = std::min<int64_t>(std::max<int64_t>(1, (fill + p.n_tiles * kMaxPairWaves - 1) /
                                                            (p.n_tiles * kMaxPairWaves)), gmax);
+        // Workgroups come a round per CU at a time and a round lasts as long as
+        // its fullest group: of the group counts allowed, the one with the least
+        // rounds x superblocks of the fullest group, where rounds are few.
+        if (G > 1 && p.n_tiles * G < 4 * (int64_t)cus) {
+            const auto cost = [&](int64_t g) {
+                const int64_t w = std::min<int64_t>(kMaxPairWaves, (p.n_sb + g - 1) / g);
+                const int64_t sps = (p.n_sb + w * g - 1) / (w * g);
+                return (double)((p.n_tiles * g + cus - 1) / cus * std::min(w * sps, p.n_sb)) *
+                       (1.0 + 0.005 * (double)g);
+            };
+            int64_t best = G;
+            for (int64_t g = 2; g <= gmax; ++g) best = cost(g) < cost(best) ? g : best;
+            G = best;
+        }
         if (!fits && gmax >= 8) G = std::min<int64_t>((std::max<int64_t>(G, 8) + 7) / 8 * 8, gmax / 8 * 8);
         G = std::min<int64_t>(G, 65536);
         if (env_groups) G = std::min<int64_t>(env_groups, p.n_sb);
         // W: the full width, or fewer when the group has fewer superblocks.
         int W = (int)std::min<int64_t>(kMaxPairWaves, (p.n_sb + G - 1) / G);
+        // Kress's rule is shared by all of a tile's waves, those without sources too
+        if (op == S2D_OP_SLP && t->on_curve && G == 1) W = std::max(W, 16);
         if (env_waves) W = env_waves;
         p.waves = W;
         p.n_groups = (int)G;

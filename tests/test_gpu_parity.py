@@ -276,3 +276,19 @@ def test_side_targets_few_targets_many_sources(cfg3, mode):
         e2 = rel_err(u.cpu().numpy(), v.cpu().numpy(), ou, ov)
         print(f"side targets mode={mode} images={img}: slp {e1:.2e} dlp {e2:.2e}", flush=True)
         assert e1 <= TOL[mode] and e2 <= TOL[mode]
+
+
+# launch shapes of the direct sums: superblocks of 16 sources (the first three),
+# of 64 and of 256 with one and more split groups, groups chosen for full rounds
+# of the chip; counts around the tile (64), the superblocks and their records.
+# One far image alone in FP64 only: the sums of a few float terms at one distance
+# cancel to a tenth of the terms and less.
+@pytest.mark.parametrize("n_ves,ves_nodes,wall_nodes", [(1, 10, 9), (1, 16, 65), (3, 64, 257), (10, 66, 515),
+                                                        (20, 64, 1000), (40, 96, 1025), (60, 64, 1500)])
+@pytest.mark.parametrize("img,mode", [((-1, 1), 0), ((-1, 1), 1), ((0, 0), 0), ((0, 0), 1), ((1, 1), 0)])
+def test_direct_launch_shapes(n_ves, ves_nodes, wall_nodes, img, mode):
+    prob = synth.make_config(2, n_ves=n_ves, ves_nodes=ves_nodes, wall_nodes=wall_nodes)
+    errs = _check(prob, mode, idx=sample_targets(prob, per_class=256, seed=3), img=img)
+    if n_ves == 1 and img == (0, 0):
+        # a lone vesicle's own nodes have Kress's rule only, in FP64 in either mode
+        assert errs["slp/vesicle"] <= 1e-13
