@@ -1873,6 +1873,23 @@ __global__ __launch_bounds__(256) void mlp_sample(int32_t B, const int32_t *__re
     A[kA_d1 + lane] = a * gelu_grad_f(z1);
 }
 
+// Adam's update of parameter p by its gradient g (m == NULL: none)
+struct AdamArgs {
+    float *prm, *m, *v;
+    int32_t step;
+    float lr, b1, b2, eps;
+};
+__device__ __forceinline__ void adam_one(const AdamArgs &a, int p, float g) {
+    if (!a.m) return;
+    const float mm = a.b1 * a.m[p] + (1.f - a.b1) * g;
+    const float vv = a.b2 * a.v[p] + (1.f - a.b2) * g * g;
+    a.m[p] = mm;
+    a.v[p] = vv;
+    const float mh = mm / (1.f - powf(a.b1, (float)a.step));
+    const float vh = vv / (1.f - powf(a.b2, (float)a.step));
+    a.prm[p] -= a.lr * mh / (sqrtf(vh) + a.eps);
+}
+
 // gradient of every parameter: the sum over the batch of (input activation x
 // delta), in kGradChunks contiguous runs of samples, each summed in sample
 // order, then the runs added in order (fixed order: deterministic).  A
@@ -1883,7 +1900,9 @@ __global__ __launch_bounds__(256) void mlp_sample(int32_t B, const int32_t *__re
 // The first row group of a layer also sums its biases; the last workgroup adds
 // the samples' losses in order, from LDS.  12 us at 1,024 samples; one thread
 // per parameter and run, each loading both factors, and one thread adding the
-// losses from memory took 49 us.
+// losses from memory took 49 us.  The thread that finishes a gradient updates
+// its parameter (nothing here reads the parameters): a launch of its own took
+// another 3.6 of the step's 24 us.
 constexpr int kGradChunks = 8;
 constexpr int kGradRows = 4;
 constexpr int kGradTiles1 = (kNearFeat + kGradRows - 1) / kGradRows, kGradTiles = 64 / kGradRows;
@@ -1891,7 +1910,8 @@ constexpr int kGradBlocks = kGradTiles1 + 3 * kGradTiles;        // then one for
 __global__ __launch_bounds__(kGradChunks *kWave) void mlp_grad(int32_t B, const float *__restrict__ act,
                                                                const float *__restrict__ dY,
                                                                const float *__restrict__ lossv,
-                                                               float *__restrict__ grad, float *__restrict__ loss) {
+                                                               float *__restrict__ grad, float *__restrict__ loss,
+                                                               AdamArgs adam) {
     __shared__ float part[kGradChunks][kGradRows + 1][kWave];
     using O = MlpOffsets;
     if (blockIdx.x == kGradBlocks) {
@@ -1960,23 +1980,9 @@ __global__ __launch_bounds__(kGradChunks *kWave) void mlp_grad(int32_t B, const 
     for (int c = 0; c < kGradChunks; ++c) t += part[c][r][lane];
     const int W = layer == 0 ? O::W1 : layer == 1 ? O::W2 : layer == 2 ? O::W3 : O::W4;
     const int bias = layer == 0 ? O::b1 : layer == 1 ? O::b2 : layer == 2 ? O::b3 : O::b4;
-    grad[r == kGradRows ? bias + lane : W + (row0 + r) * n_out + lane] = t;
-}
-
-__global__ __launch_bounds__(256) void mlp_adam(float *__restrict__ prm, const float *__restrict__ grad,
-                                                float *__restrict__ m, float *__restrict__ v, int32_t step, float lr,
-                                                float b1, float b2, float eps) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    using O = MlpOffsets;
-    if (p >= O::total || p < O::W1) return;
-    const float g = grad[p];
-    const float mm = b1 * m[p] + (1.f - b1) * g;
-    const float vv = b2 * v[p] + (1.f - b2) * g * g;
-    m[p] = mm;
-    v[p] = vv;
-    const float mh = mm / (1.f - powf(b1, (float)step));
-    const float vh = vv / (1.f - powf(b2, (float)step));
-    prm[p] -= lr * mh / (sqrtf(vh) + eps);
+    const int p = r == kGradRows ? bias + lane : W + (row0 + r) * n_out + lane;
+    grad[p] = t;
+    adam_one(adam, p, t);
 }
 
 // FP32 forward only: the 20 raw outputs dC (reference-precision inference,
@@ -2170,14 +2176,10 @@ hipError_t near_launch_train_targets(int op, int64_t n, const double *frame, con
 hipError_t near_launch_train_step(int32_t B, const int32_t *idx, const float *X, const float *T, float *prm,
                                   float *m, float *v, int32_t step, float lr, float *grad, float *act, float *dY,
                                   float *lossv, float *loss, int update, hipStream_t st) {
-    using O = MlpOffsets;
     const unsigned wave_blocks = (unsigned)((B + kBlock / kWave - 1) / (kBlock / kWave));   // a wave per sample
     hipLaunchKernelGGL(mlp_sample, dim3(wave_blocks), dim3(kBlock), 0, st, B, idx, X, T, prm, act, dY, lossv);
     hipLaunchKernelGGL(mlp_grad, dim3(kGradBlocks + 1), dim3(kGradChunks * kWave), 0, st, B, act, dY, lossv, grad,
-                       loss);
-    if (update)
-        hipLaunchKernelGGL(mlp_adam, dim3(grid_for(O::total)), dim3(256), 0, st, prm, grad, m, v, step, lr, 0.9f,
-                           0.999f, 1e-8f);
+                       loss, AdamArgs{prm, update ? m : nullptr, v, step, lr, 0.9f, 0.999f, 1e-8f});
     return hipGetLastError();
 }
 

@@ -311,6 +311,39 @@ def test_training_gradient_matches_oracle_and_finite_differences():
         assert abs(fd - gj) <= 2e-2 * max(abs(gj), 1e-3 * abs(L)), (name, fd, gj)
 
 
+# eight runs of samples, loads of 16 ahead, four samples a workgroup: batches of
+# fewer samples than runs, remainders of each, more losses than their buffer
+@pytest.mark.parametrize("B", [1, 3, 7, 9, 129, 1000, 2049])
+def test_training_gradient_at_batch_remainders(B):
+    import torch
+    from paper_1510_05616_amd import near
+    rng = np.random.default_rng(B)
+    X, dd, R, wt, T = _rand_records(rng, B)
+    X32, T32 = X.astype(np.float32), T.astype(np.float32)
+    p32 = near.dict_to_params(_rand_params()).astype(np.float32)
+    T64 = T32.astype(np.float64)
+    L, g = onear.mlp_loss_grad(near.params_to_dict(p32), X32.astype(np.float64), T64[:, :10].reshape(-1, 5, 2),
+                               T64[:, 10:12], T64[:, 12])
+    prm = torch.as_tensor(p32, device="cuda")
+    grad, loss = torch.full_like(prm, np.nan), torch.zeros(1, dtype=torch.float32, device="cuda")
+    ws = torch.empty(near.near_mlp_train_workspace_size(B), dtype=torch.uint8, device="cuda")
+    Xt, Tt = torch.as_tensor(X32, device="cuda"), torch.as_tensor(T32, device="cuda")
+    near.near_mlp_train_step(B, None, Xt, Tt, prm, None, None, 0, 0.0, grad, loss, ws)
+    # the update is the same gradient's: parameters move by -lr sign(g) at step 1
+    m, v, p2 = torch.zeros_like(prm), torch.zeros_like(prm), prm.clone()
+    g2 = torch.full_like(prm, np.nan)
+    near.near_mlp_train_step(B, None, Xt, Tt, p2, m, v, 1, 1e-3, g2, None, ws)
+    torch.cuda.synchronize()
+    gg = near.params_to_dict(grad.cpu().numpy())
+    assert abs(loss.item() - L) <= 1e-5 * abs(L)
+    for k in ("W1", "b1", "W2", "b2", "W3", "b3", "W4", "b4"):
+        assert np.abs(gg[k] - g[k]).max() <= 2e-4 * np.abs(g[k]).max(), k
+    assert torch.equal(grad, g2) and torch.equal(prm, torch.as_tensor(p32, device="cuda"))
+    big = grad.abs() > 1e-4
+    assert float((p2 - prm + 1e-3 * grad.sign())[big].abs().max()) < 1e-6
+    assert torch.equal(p2[grad == 0], prm[grad == 0])
+
+
 def test_adam_step_matches_oracle():
     import torch
     from paper_1510_05616_amd import near
