@@ -39,7 +39,7 @@
  * and 1,024 targets at least, takes the far-field route, in FP64 in either
  * mode: sources and targets are sorted along a space-filling curve, near nodes
  * are summed term by term and well separated clusters through expansions
- * truncated below 1e-17 of their terms, in a fixed order.  It needs the
+ * truncated below 1e-15 of their terms, in a fixed order.  It needs the
  * workspace stokes2d_workspace_size() gives (about 100 bytes per source node
  * and 70 per target); with a smaller one that still holds the direct sum, the
  * call sums directly in its mode's arithmetic.
