@@ -1935,14 +1935,14 @@ __device__ __forceinline__ void adam_one(const AdamArgs &a, int p, float g) {
 // workgroup owns kGradRows input rows of one layer and all its columns: wave
 // = run, lane = column; a sample costs one coalesced load of the deltas and a
 // scalar load of the rows' activations, 16 samples of loads ahead of their
-// FMAs.  Bound by the latency of those loads (8 rounds of 16 at 1,024 samples).
+// FMAs.  Bound by the latency of those loads (4 rounds of 16 at 1,024 samples;
+// in 8 runs, 8 rounds: 12.6 us, in 16 10.2).
 // The first row group of a layer also sums its biases; the last workgroup adds
-// the samples' losses in order, from LDS.  12 us at 1,024 samples; one thread
-// per parameter and run, each loading both factors, and one thread adding the
-// losses from memory took 49 us.  The thread that finishes a gradient updates
-// its parameter (nothing here reads the parameters): a launch of its own took
-// another 3.6 of the step's 24 us.
-constexpr int kGradChunks = 8;
+// the samples' losses in order, from LDS.  One thread per parameter and run,
+// each loading both factors, and one thread adding the losses from memory took
+// 49 us.  The thread that finishes a gradient updates its parameter (nothing
+// here reads the parameters): a launch of its own took another 3.6.
+constexpr int kGradChunks = 16;
 constexpr int kGradRows = 4;
 constexpr int kGradTiles1 = (kNearFeat + kGradRows - 1) / kGradRows, kGradTiles = 64 / kGradRows;
 constexpr int kGradBlocks = kGradTiles1 + 3 * kGradTiles;        // then one for the loss

@@ -311,7 +311,7 @@ def test_training_gradient_matches_oracle_and_finite_differences():
         assert abs(fd - gj) <= 2e-2 * max(abs(gj), 1e-3 * abs(L)), (name, fd, gj)
 
 
-# eight runs of samples, loads of 16 ahead, four samples a workgroup: batches of
+# sixteen runs of samples, loads of 16 ahead, four samples a workgroup: batches of
 # fewer samples than runs, remainders of each, more losses than their buffer
 @pytest.mark.parametrize("B", [1, 3, 7, 9, 129, 1000, 2049])
 def test_training_gradient_at_batch_remainders(B):
