@@ -569,7 +569,7 @@ struct PcArgs {
     int Nm;
     const double *x, *y, *sp, *w, *nx, *ny, *tx, *ty;
     double dtk, pref;
-    double *T, *Dm, *D4, *Sm, *Bm, *Top, *Pm;
+    double *T, *Dm, *D4, *Sm, *Bm, *Pm;
 };
 
 // Kress table, D_s (Nm x Nm) and S_cc (2Nm x 2Nm) of curve blockIdx.x
@@ -622,46 +622,45 @@ __global__ __launch_bounds__(kVesBlock) void pc_fill_ds(PcArgs a) {
     }
 }
 
-// B_c (2Nm x 3Nm) = [ dt kappa_B D_s^4  0  -D_s diag(t_x) ;  0  dt kappa_B D_s^4  -D_s diag(t_y) ]
+// The last Nm columns of B_c (2Nm x 3Nm) = [ dt kappa_B D_s^4  0  -D_s diag(t_x) ;
+// 0  dt kappa_B D_s^4  -D_s diag(t_y) ]; S_cc times the others is S_cc's halves
+// times D_s^4.  A wave per column, a lane per row.
 __global__ __launch_bounds__(kVesBlock) void pc_fill_b(PcArgs a) {
-    const int c = blockIdx.x, Nm = a.Nm, M2 = 2 * Nm;
+    const int c = blockIdx.x, Nm = a.Nm, M2 = 2 * Nm, lane = threadIdx.x & (kWave - 1);
     const CurveRange r = curve_range(a.off, a.n);
     const int N = r.ok ? r.N : 0;
-    const double *Dm = a.Dm + (int64_t)c * Nm * Nm, *D4 = a.D4 + (int64_t)c * Nm * Nm;
-    double *B = a.Bm + (int64_t)c * 6 * Nm * Nm;
-    for (int idx = threadIdx.x; idx < M2 * 3 * Nm; idx += blockDim.x) {
-        const int row = idx % M2, col = idx / M2;
-        const int ra = row / Nm, j = row % Nm, cb = col / Nm, k = col % Nm;
-        double v = 0.0;
-        if (j < N && k < N) {
-            if (cb < 2)
-                v = ra == cb ? a.dtk * D4[j + k * Nm] : 0.0;
-            else
-                v = -Dm[j + k * Nm] * (ra == 0 ? a.tx[r.lo + k] : a.ty[r.lo + k]);
+    const double *Dm = a.Dm + (int64_t)c * Nm * Nm;
+    double *B = a.Bm + (int64_t)c * 2 * Nm * Nm;
+    for (int k = threadIdx.x / kWave; k < Nm; k += kVesBlock / kWave) {
+        const double tx = k < N ? a.tx[r.lo + k] : 0.0, ty = k < N ? a.ty[r.lo + k] : 0.0;
+        for (int j = lane; j < Nm; j += kWave) {
+            const double d = j < N && k < N ? -Dm[j + k * Nm] : 0.0;
+            double *o = B + j + (int64_t)k * M2;
+            o[0] = d * tx;
+            o[Nm] = d * ty;
         }
-        B[idx] = v;
     }
 }
 
-// P_c (3Nm x 3Nm) from Top_c = S_cc B_c
+// P_c (3Nm x 3Nm), whose first 2Nm rows hold S_cc B_c: the identity added to
+// them, and the constraint's rows.  A wave per column, a lane per row.  (S_cc B_c
+// in an array of its own and P_c filled from it by a flat index took 370 us for
+// 1,000 blocks of 288 rows, this takes 130.)
 __global__ __launch_bounds__(kVesBlock) void pc_fill_p(PcArgs a) {
-    const int c = blockIdx.x, Nm = a.Nm, M2 = 2 * Nm, M3 = 3 * Nm;
+    const int c = blockIdx.x, Nm = a.Nm, M2 = 2 * Nm, M3 = 3 * Nm, lane = threadIdx.x & (kWave - 1);
     const CurveRange r = curve_range(a.off, a.n);
     const int N = r.ok ? r.N : 0;
-    const double *Dm = a.Dm + (int64_t)c * Nm * Nm, *Top = a.Top + (int64_t)c * 6 * Nm * Nm;
+    const double *Dm = a.Dm + (int64_t)c * Nm * Nm;
     double *P = a.Pm + (int64_t)c * 9 * Nm * Nm;
-    for (int idx = threadIdx.x; idx < M3 * M3; idx += blockDim.x) {
-        const int row = idx % M3, col = idx / M3;
-        const int ra = row / Nm, i = row % Nm, cb = col / Nm, k = col % Nm;
-        double v;
-        if (i >= N || k >= N) {
-            v = row == col ? 1.0 : 0.0;
-        } else if (ra < 2) {
-            v = Top[row + (int64_t)col * M2] + (row == col ? 1.0 : 0.0);
-        } else {
-            v = cb < 2 ? (cb == 0 ? a.tx[r.lo + i] : a.ty[r.lo + i]) * Dm[i + k * Nm] : 0.0;
+    for (int col = threadIdx.x / kWave; col < M3; col += kVesBlock / kWave) {
+        const int cb = (col >= Nm) + (col >= M2), k = col - cb * Nm;
+        double *o = P + (int64_t)col * M3;
+        if (lane == 0 && cb < 2) o[col] += 1.0;
+        for (int i = lane; i < Nm; i += kWave) {
+            double v = M2 + i == col ? 1.0 : 0.0;
+            if (i < N && k < N) v = cb < 2 ? (cb == 0 ? a.tx[r.lo + i] : a.ty[r.lo + i]) * Dm[i + k * Nm] : 0.0;
+            o[M2 + i] = v;
         }
-        P[idx] = v;
     }
 }
 
@@ -1067,7 +1066,7 @@ struct StepLayout {
     // preconditioner (precond != 0): Kress table, per-curve D_s, D_s^2, D_s^4,
     // S_cc, B, S_cc B, P (LU with inverted diagonal triangles), pivots (then the
     // row permutation), info, two [3n] vectors
-    size_t T, Dm, D2, D4, Sm, Bm, Top, Pm, ipiv, info, t1, t2;
+    size_t T, Dm, D2, D4, Sm, Bm, Pm, ipiv, info, t1, t2;
     // close evaluation (near != 0): curve boxes, per-node counts and list
     // offsets, the near pairs (node, curve, shifted coordinates, corrections),
     // the upsampled records
@@ -1144,9 +1143,7 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
         L.Sm = o;
         o += al256(4 * q);
         L.Bm = o;
-        o += al256(6 * q);
-        L.Top = o;
-        o += al256(6 * q);
+        o += al256(2 * q);
         L.Pm = o;
         o += al256(9 * q);
         L.ipiv = o;
@@ -1479,7 +1476,6 @@ int pc_build(StepCtx &C) {
     a.D4 = (double *)(b + C.L.D4);
     a.Sm = (double *)(b + C.L.Sm);
     a.Bm = (double *)(b + C.L.Bm);
-    a.Top = (double *)(b + C.L.Top);
     a.Pm = (double *)(b + C.L.Pm);
     double *D2 = (double *)(b + C.L.D2);
     hipLaunchKernelGGL(pc_fill_ds, dim3(nc), dim3(kVesBlock), 0, C.st, a);
@@ -1497,9 +1493,16 @@ int pc_build(StepCtx &C) {
     hipLaunchKernelGGL(pc_fill_b, dim3(nc), dim3(kVesBlock), 0, C.st, a);
     e = hipGetLastError();
     if (e != hipSuccess) return hipf(e, "preconditioner fill");
-    S2D_TRY(rbf(rocblas_dgemm_strided_batched(C.h, rocblas_operation_none, rocblas_operation_none, 2 * Nm, 3 * Nm,
-                                              2 * Nm, &one, a.Sm, 2 * Nm, 4 * s1, a.Bm, 2 * Nm, 6 * s1, &zero, a.Top,
-                                              2 * Nm, 6 * s1, nc),
+    // the first 2Nm rows of P = S_cc B: dt kappa_B S_cc's column halves times D_s^4,
+    // then the last columns
+    for (int q = 0; q < 2; ++q)
+        S2D_TRY(rbf(rocblas_dgemm_strided_batched(C.h, rocblas_operation_none, rocblas_operation_none, 2 * Nm, Nm, Nm,
+                                                  &a.dtk, a.Sm + 2 * q * s1, 2 * Nm, 4 * s1, a.D4, Nm, s1, &zero,
+                                                  a.Pm + 3 * q * s1, 3 * Nm, 9 * s1, nc),
+                    "preconditioner S_cc D_s^4"));
+    S2D_TRY(rbf(rocblas_dgemm_strided_batched(C.h, rocblas_operation_none, rocblas_operation_none, 2 * Nm, Nm, 2 * Nm,
+                                              &one, a.Sm, 2 * Nm, 4 * s1, a.Bm, 2 * Nm, 2 * s1, &zero,
+                                              a.Pm + 6 * s1, 3 * Nm, 9 * s1, nc),
                 "preconditioner S_cc B"));
     hipLaunchKernelGGL(pc_fill_p, dim3(nc), dim3(kVesBlock), 0, C.st, a);
     e = hipGetLastError();
