@@ -188,6 +188,14 @@ void prof_end(const ProfEvent &pe, hipStream_t st) {
     g_prof.push_back(pe);
 }
 
+// Whether the n outputs overlap any array that Kress's rule reads.
+bool outputs_over_sources(const s2d_curves *s, int64_t n, const double *u, const double *v) {
+    for (const double *o : {u, v})
+        for (const double *a : {s->x, s->y, s->nx, s->ny, s->w, s->fx, s->fy})
+            if ((uintptr_t)o < (uintptr_t)(a + s->n_nodes) && (uintptr_t)a < (uintptr_t)(o + n)) return true;
+    return false;
+}
+
 int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double d, int32_t img_lo,
          int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
          void *stream, const double *tnx = nullptr, const double *tny = nullptr, bool may_profile = true) {
@@ -233,6 +241,9 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
     a.n_tiles = p.n_tiles;
     a.n_splits = p.n_splits;
     a.n_groups = p.n_groups;
+    // Kress's rule reads the sources in the pair kernel: outputs over them (a
+    // layer applied in place) are written by the kernel after it
+    a.planes = p.n_groups > 1 || (p.self && outputs_over_sources(src, trg->n, u, v));
     a.sb_per_split = p.sb_per_split;
     a.n_sb = p.n_sb;
     a.sbs = p.sbs;
@@ -253,8 +264,8 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
         if (e != hipSuccess) return hip_fail(e, "pair launch");
         prof_end(pe, st);
     }
-    // the pair kernel finishes the targets itself when it has one split group
-    if (p.n_blocks > 0 && p.n_groups == 1) return S2D_OK;
+    // the pair kernel finishes the targets itself when it leaves no planes
+    if (p.n_blocks > 0 && !a.planes) return S2D_OK;
     e = launch_final(p, f, st);
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
     return S2D_OK;

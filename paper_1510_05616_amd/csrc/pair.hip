@@ -5,8 +5,9 @@
 // Kress's rule on their targets' own curves (single layer).  With one split
 // group (every source in the workgroup) wave 0 then finishes the targets
 // itself: the double layer's diagonal limit, the prefactor and the accumulate
-// flag, exactly as finalize() does.  With G > 1 groups it writes
-// the group's FP64 partial, and finalize() adds the G partials in order.
+// flag, exactly as finalize() does.  With G > 1 groups, or outputs that lie
+// over the sources Kress's rule reads, it writes the group's FP64 partial, and
+// finalize() adds the G partials in order.
 //
 // blockIdx -> (tile, group): group = blockIdx % G, tile = blockIdx / G.  The
 // dispatcher assigns workgroups to the 8 XCDs round-robin, so with G a
@@ -56,7 +57,7 @@ void pair_kernel(PairArgs a, FinalArgs f) {
         sy += red[1][w - 1][lane];
     }
     if (i >= a.n_trg) return;
-    if (a.n_groups > 1) {
+    if (a.planes) {
         a.part[(int64_t)(2 * group) * a.n_trg + i] = sx;
         a.part[(int64_t)(2 * group + 1) * a.n_trg + i] = sy;
         return;

@@ -109,10 +109,13 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
         off = align256(off + (size_t)p.n_sb * (p.sbs / kSubBlock) * sizeof(s2d::SubInfo));
     p.off_sbsum = off;
     if (op == S2D_OP_SLP && mode == S2D_FP32C) off = align256(off + (size_t)p.n_sb * 2 * sizeof(double));
+    // Kress's rule reads the sources while other tiles finish: outputs that lie
+    // over them wait in a plane (api.hip)
+    const bool own = op == S2D_OP_SLP && t->on_curve;
     p.off_part = off;
-    if (p.n_groups > 1) off = align256(off + (size_t)p.n_groups * 2 * (size_t)p.n_trg * sizeof(double));
+    if (p.n_groups > 1 || own) off = align256(off + (size_t)p.n_groups * 2 * (size_t)p.n_trg * sizeof(double));
     p.off_kress = off;
-    if (op == S2D_OP_SLP && t->on_curve && p.n_trg > 0) off = align256(off + (size_t)p.n_src * sizeof(double));
+    if (own && p.n_trg > 0) off = align256(off + (size_t)p.n_src * sizeof(double));
     p.total = off;
     return p;
 }

@@ -62,6 +62,7 @@ struct PairArgs {
     int64_t n_tiles;
     int32_t n_splits;
     int32_t n_groups;         // single-call kernel: split groups (partial planes when > 1)
+    int32_t planes;           // write the partial planes with one group too
     int64_t sb_per_split;
     int64_t n_sb;
     int32_t sbs;              // sources per superblock

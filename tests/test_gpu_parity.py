@@ -292,3 +292,24 @@ def test_direct_launch_shapes(n_ves, ves_nodes, wall_nodes, img, mode):
     if n_ves == 1 and img == (0, 0):
         # a lone vesicle's own nodes have Kress's rule only, in FP64 in either mode
         assert errs["slp/vesicle"] <= 1e-13
+
+
+# A layer applied in place: the outputs are the density, so Kress's rule on a
+# curve of many tiles (2,046 nodes: 32, the last one ragged) must not meet
+# another tile's results.  The kernels' order of summation is the same: same bits.
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("sizes", [(2046,), (130, 64, 258), (34,)])
+def test_single_layer_in_place(sizes, mode):
+    import torch
+    import paper_1510_05616_amd as s2d
+    cs = synth.concat_curves([tuple(getattr(c, k) for k in ("x", "y", "nx", "ny", "w", "kappa", "fx", "fy"))
+                              for c in (synth.ellipse_curve(0.3, 0.2, n, (1.1 * i, 0.0), fx=np.cos, fy=np.sin)
+                                        for i, n in enumerate(sizes))])
+    oc = np.repeat(np.arange(len(sizes), dtype=np.int32), sizes)
+    on = np.arange(sum(sizes), dtype=np.int32)
+    src, t = s2d.Curves(cs), s2d.Targets(cs.x, cs.y, oc, on)
+    want = torch.zeros(2, t.n, dtype=torch.float64, device="cuda")
+    s2d.stokes2d_slp_eval(mode, src, t, 9.0, -1, 1, 1.3, want[0], want[1])
+    s2d.stokes2d_slp_eval(mode, src, t, 9.0, -1, 1, 1.3, src.fx, src.fy)
+    torch.cuda.synchronize()
+    assert torch.equal(src.fx, want[0]) and torch.equal(src.fy, want[1])
