@@ -256,7 +256,8 @@ int eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, double
     a.rec64 = (char *)ws + p.off_rec64;
     FinalArgs f = final_args(op, src, trg, img0, mu, u, v, accumulate);
     f.part = a.part;
-    f.kress = p.self ? (const double *)((char *)ws + p.off_kress) : nullptr;
+    f.own_rule = p.self;
+    f.kress = (const double *)((char *)ws + p.off_kress);
     f.n_parts = p.n_blocks > 0 ? p.n_groups : 0;
     if (p.n_blocks > 0) {
         const ProfEvent pe = prof_begin(op, may_profile, st);

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kMaxPairWaves * kWave) __attribute__((amdgpu_waves_
 void pair_kernel(PairArgs a, FinalArgs f) {
     __shared__ __attribute__((aligned(16))) double ltab[kLogTabWords];
     __shared__ double red[2][kMaxPairWaves - 1][kWave];
-    if (OP == S2D_OP_SLP && (PREC == S2D_FP64 || f.kress)) fill_log_table(ltab);
+    if (OP == S2D_OP_SLP && (PREC == S2D_FP64 || f.own_rule)) fill_log_table(ltab);
     const int lane = threadIdx.x & (kWave - 1);
     // wave index made wave-uniform for the compiler: the split, and with it
     // every source record address, must be uniform so records take the scalar path
@@ -38,7 +38,7 @@ void pair_kernel(PairArgs a, FinalArgs f) {
     double ox[1], oy[1];
     pair_sum<OP, PREC, 1, NI>(a, tile, group * W + wid, lane, ltab, ox, oy);
     const int64_t i = tile * kWave + lane;
-    if (OP == S2D_OP_SLP && f.kress && group == 0 && i < a.n_trg) {
+    if (OP == S2D_OP_SLP && f.own_rule && group == 0 && i < a.n_trg) {
         double sx, sy;
         kress_self_one(i, f.n_src, f.on_curve, f.on_node, f.curve_off, f.n_curves, f.sx, f.sy, f.nx, f.ny, f.w, f.fx,
                        f.fy, f.kress, ltab, sx, sy, wid, W);

@@ -94,7 +94,9 @@ constexpr bool slp_sources(int op) {
 struct FinalArgs {
     const double *part;
     const double *self;       // own-curve terms [2][n_trg] summed elsewhere (far-field route) or NULL
-    const double *kress;      // Kress table: the pair kernel sums Kress's rule itself; or NULL
+    int32_t own_rule;         // Kress's rule applies (single layer, on-curve targets, image 0): the pair kernel
+                              // sums it from `kress`
+    const double *kress;      // Kress table
     const double *sx, *sy;    // source nodes
     int32_t n_parts;          // partial planes of part
     int64_t n_trg;

@@ -14,7 +14,7 @@ __global__ __launch_bounds__(256) void finalize(FinalArgs a) {
         sy += a.part[(int64_t)(2 * s + 1) * a.n_trg + i];
     }
     // without sources every on-curve reference is out of range
-    if (a.n_parts == 0 && a.kress && a.on_curve[i] >= 0) sx = sy = __builtin_nan("");
+    if (a.n_parts == 0 && a.own_rule && a.on_curve[i] >= 0) sx = sy = __builtin_nan("");
     final_one(a, i, sx, sy);
 }
 

@@ -313,3 +313,26 @@ def test_single_layer_in_place(sizes, mode):
     s2d.stokes2d_slp_eval(mode, src, t, 9.0, -1, 1, 1.3, src.fx, src.fy)
     torch.cuda.synchronize()
     assert torch.equal(src.fx, want[0]) and torch.equal(src.fy, want[1])
+
+
+# Without sources every on-curve reference is out of range: NaN with the
+# workspace the size query names, and a call without one is refused.
+@pytest.mark.parametrize("mode", MODES)
+def test_no_sources_with_on_curve_targets(mode):
+    import torch
+    import paper_1510_05616_amd as s2d
+    n = 1000
+    oc = np.where(np.arange(n) % 3 == 0, 0, -1).astype(np.int32)
+    src = s2d.Curves(synth.concat_curves([]))
+    t = s2d.Targets(np.linspace(0, 1, n), np.zeros(n), oc, np.zeros(n, np.int32))
+    u = torch.full((2, n), 2.0, dtype=torch.float64, device="cuda")
+    with pytest.raises(s2d.S2DError) as ei:
+        s2d.stokes2d_slp_eval(mode, src, t, 1.0, -1, 1, 1.0, u[0], u[1],
+                              ws=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    assert ei.value.code == s2d.S2D_EWORKSPACE
+    torch.cuda.synchronize()
+    assert torch.all(u == 2.0)
+    s2d.stokes2d_slp_eval(mode, src, t, 1.0, -1, 1, 1.0, u[0], u[1])
+    torch.cuda.synchronize()
+    nan = torch.as_tensor(oc >= 0, device="cuda")
+    assert torch.isnan(u[:, nan]).all() and torch.all(u[:, ~nan] == 0)
