@@ -29,12 +29,15 @@
 // layer skips curve c at n = 0 (Kress's rule covers it elsewhere) and the
 // double layer skips node i at n = 0 (the diagonal limit covers it).  A wave
 // folds its targets' excluded index ranges into one hull; a superblock that
-// meets the hull in a group holding n = 0 takes a masked path: the same
+// meets the hull in a group holding n = 0 takes a masked path.  FP64: the same
 // grouped terms, with image 0 replaced by a neutral factor where a target
-// excludes the source or the record is padding.  (Image by image with one
-// select per pair, the batched single layer of 64 channels with up to 40
-// vesicles took 1.04 ms against 0.74; small problems consist of such superblocks.)  All other superblocks, the ragged last one included,
-// take the unmasked path.
+// excludes the source or the record is padding.  FP32C: each image's term by
+// itself, added in FP64 or left out, over the aligned kSuperBlock sources
+// around the hull whatever the superblock's own size.  (Grouped in float like
+// the unmasked path the step of 50 x 128 nodes took 155 us against 174, the
+// batched call of 64 channels 2.46 ms against 2.57, but two curves of 64 nodes
+// came out with up to 3.6 times the error.)  All other superblocks, the ragged
+// last one included, take the unmasked path.
 //
 // Precision.  FP64 mode evaluates each term in double.  FP32C mode evaluates
 // each term in float with the hardware log2 and reciprocal, sums a sub-block
@@ -234,18 +237,16 @@ __device__ __forceinline__ void slp64_src(const double (&px)[NI], double py, con
 // accumulators take (-D g_x + C g_y, C g_x + D g_y), and the constant NI g_x
 // of the x component is added per superblock from its FP64 density sum.
 // With NI = 1 the term is taken directly (a[2], a[3] then hold the whole
-// rational term).  MASK: image m0 is left out unless ok (its share of the
-// constant is then the caller's to take back).
-template <int NI, bool MASK = false>
+// rational term).
+template <int NI>
 __device__ __forceinline__ void slp32_src(const float (&rx)[NI], float ry, float gx, float gy, float iqr,
-                                          float (&a)[4], bool ok = true, int m0 = 0) {
+                                          float (&a)[4]) {
     const float ry2 = ry * ry;
     if constexpr (NI == 1) {
         // one image: r (r.g)/q directly (cheaper than the shared form, and
         // no constant to add back)
-        const bool use = !MASK || ok || m0 != 0;
-        const float q = use ? __builtin_fmaf(rx[0], rx[0], ry2) : 1.f;
-        const float t = use ? __builtin_fmaf(rx[0], gx, ry * gy) * __builtin_amdgcn_rcpf(q) : 0.f;
+        const float q = __builtin_fmaf(rx[0], rx[0], ry2);
+        const float t = __builtin_fmaf(rx[0], gx, ry * gy) * __builtin_amdgcn_rcpf(q);
         a[2] = __builtin_fmaf(rx[0], t, a[2]);
         a[3] = __builtin_fmaf(ry, t, a[3]);
         const float lq = __builtin_amdgcn_logf(q * iqr);
@@ -256,9 +257,8 @@ __device__ __forceinline__ void slp32_src(const float (&rx)[NI], float ry, float
     float P = 1.f, s0 = 0.f, s1 = 0.f;
 #pragma unroll
     for (int m = NI - 1; m >= 0; --m) {
-        const bool use = !MASK || ok || m != m0;
-        const float q = use ? __builtin_fmaf(rx[m], rx[m], ry2) : 1.f;
-        const float iq = use ? __builtin_amdgcn_rcpf(q) : 0.f;
+        const float q = __builtin_fmaf(rx[m], rx[m], ry2);
+        const float iq = __builtin_amdgcn_rcpf(q);
         s0 = m == NI - 1 ? iq : s0 + iq;
         s1 = m == NI - 1 ? rx[m] * iq : __builtin_fmaf(rx[m], iq, s1);
         P = m == NI - 1 ? q * iqr : P * q;     // the scaled factor first
@@ -295,9 +295,8 @@ __device__ __forceinline__ void dlp64_src(const double (&px)[NI], double py, con
 
 // FP32 double layer of one source for the differences (rx[m], ry),
 // accumulators a = {x, y}
-template <int NI, bool MASK = false>
-__device__ __forceinline__ void dlp32_src(const float (&rx)[NI], float ry, const RecDlp32 &s, float (&a)[2],
-                                          bool ok = true, int m0 = 0) {
+template <int NI>
+__device__ __forceinline__ void dlp32_src(const float (&rx)[NI], float ry, const RecDlp32 &s, float (&a)[2]) {
     const float ry2 = ry * ry, rny = ry * s.ny, rty = ry * s.ty;
     float fs = 0.f;
 #pragma unroll
@@ -306,8 +305,7 @@ __device__ __forceinline__ void dlp32_src(const float (&rx)[NI], float ry, const
         const float iq = __builtin_amdgcn_rcpf(q);
         const float rn = __builtin_fmaf(rx[m], s.nx, rny);
         const float rt = __builtin_fmaf(rx[m], s.tx, rty);
-        float f = (rn * rt) * (iq * iq);
-        if (MASK) f = ok || m != m0 ? f : 0.f;
+        const float f = (rn * rt) * (iq * iq);
         a[0] = __builtin_fmaf(rx[m], f, a[0]);
         fs = m == 0 ? f : fs + f;
     }
@@ -485,37 +483,9 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
             const int64_t j0 = (int64_t)sb * sbs;
             // padding records are zero-density copies of the last source: a ragged
             // superblock needs no mask
-            const bool masked = OP <= S2D_OP_DLP && has0 && hlo < hhi && j0 < hhi && (int64_t)hlo < j0 + sbs;
+            const int64_t m_len = PREC == S2D_FP64 ? sbs : kSuperBlock, m_lo = j0 / m_len * m_len;
+            const bool masked = OP <= S2D_OP_DLP && has0 && hlo < hhi && m_lo < hhi && (int64_t)hlo < m_lo + m_len;
             const int m0 = -n0;                            // the group's image 0
-            // FP32C single layer: the log reference factor
-            [[maybe_unused]] float iqr[TPT];
-            if constexpr (OP == S2D_OP_SLP && PREC == S2D_FP32C) {
-                const RecSlp32 *rec = (const RecSlp32 *)a.rec + j0;
-                // log reference: the superblock's first source at every image of the group
-                const double gsx = load_ro<double>(a.sbsum, 2 * sb), gsy = load_ro<double>(a.sbsum, 2 * sb + 1);
-                const RecSlp32 r0 = load_ro<RecSlp32>(rec, 0);
-#pragma unroll
-                for (int k = 0; k < TPT; ++k) {
-                    const double ry0 = py[k] - r0.y;
-                    double qp = 1.0;
-#pragma unroll
-                    for (int m = 0; m < NI; ++m) {
-                        const double rx0 = px[k][m] - r0.x;
-                        qp *= __builtin_fma(rx0, rx0, ry0 * ry0);
-                    }
-                    // iqr = 2^-e with qp = m 2^e, m in [1/2, 1): scaling by it is exact in
-                    // float, and -1/2 sum g ln prod q = -(ln2/2) sum g log2(iqr prod q)
-                    // - (ln2/2) e sum g
-                    // (a masked superblock of the image n = 0 alone takes no reference:
-                    // what it excludes then adds an exact zero)
-                    const int e = NI == 1 && masked ? 0 : min(max(__builtin_amdgcn_frexp_exp(qp), -100), 100);
-                    iqr[k] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
-                    const double c = -kHalfLn2 * (double)e;
-                    // and, for grouped images, the rational term's constant NI g_x (see slp32_src)
-                    ux[k] = __builtin_fma(c, gsx, NI > 1 ? __builtin_fma((double)NI, gsx, ux[k]) : ux[k]);
-                    uy[k] = __builtin_fma(c, gsy, uy[k]);
-                }
-            }
             if (!masked) {
                 // ---------------- unmasked superblock ----------------
                 if (PREC == S2D_FP64) {
@@ -558,6 +528,29 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                 } else {
                     if (OP == S2D_OP_SLP) {
                         const RecSlp32 *rec = (const RecSlp32 *)a.rec + j0;
+                        // log reference: the superblock's first source at every image of the group
+                        float iqr[TPT];
+                        const double gsx = load_ro<double>(a.sbsum, 2 * sb), gsy = load_ro<double>(a.sbsum, 2 * sb + 1);
+                        const RecSlp32 r0 = load_ro<RecSlp32>(rec, 0);
+#pragma unroll
+                        for (int k = 0; k < TPT; ++k) {
+                            const double ry0 = py[k] - r0.y;
+                            double qp = 1.0;
+#pragma unroll
+                            for (int m = 0; m < NI; ++m) {
+                                const double rx0 = px[k][m] - r0.x;
+                                qp *= __builtin_fma(rx0, rx0, ry0 * ry0);
+                            }
+                            // iqr = 2^-e with qp = m 2^e, m in [1/2, 1): scaling by it is exact in
+                            // float, and -1/2 sum g ln prod q = -(ln2/2) sum g log2(iqr prod q)
+                            // - (ln2/2) e sum g
+                            const int e = min(max(__builtin_amdgcn_frexp_exp(qp), -100), 100);
+                            iqr[k] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
+                            const double c = -kHalfLn2 * (double)e;
+                            // and, for grouped images, the rational term's constant NI g_x (see slp32_src)
+                            ux[k] = __builtin_fma(c, gsx, NI > 1 ? __builtin_fma((double)NI, gsx, ux[k]) : ux[k]);
+                            uy[k] = __builtin_fma(c, gsy, uy[k]);
+                        }
                         for (int u = 0; u < sbs; u += kSubBlock) {
                             // per target: [source parity][log x, log y, rat x, rat y]
                             float ac[TPT][2][4], dx[TPT][NI], dy[TPT];
@@ -690,7 +683,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                 }
             } else if constexpr (OP <= S2D_OP_DLP) {
                 // ---------------- masked superblock ----------------
-                // FP32C: FP32 terms from FP64 differences, each added in FP64
+                // FP32C: every image's FP32 term from its FP64 difference, added in FP64 by itself
 #pragma unroll 2
                 for (int u = 0; u < sbs; ++u) {
                     const int64_t j = j0 + u;
@@ -710,22 +703,28 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
                         const Rec32Of<OP> s = load_ro<Rec32Of<OP>>(a.rec, j);
 #pragma unroll
                         for (int k = 0; k < TPT; ++k) {
-                            float rx[NI];
-#pragma unroll
-                            for (int m = 0; m < NI; ++m) rx[m] = (float)(px[k][m] - s.x);
                             const float ry = (float)(py[k] - s.y);
-                            if constexpr (OP == S2D_OP_SLP) {
-                                float t4[4] = {0.f, 0.f, 0.f, 0.f};
-                                slp32_src<NI, true>(rx, ry, s.gx, s.gy, iqr[k], t4, ok[k], m0);
-                                // the constant NI g_x counts image 0 only where it is summed
-                                const double cg = NI > 1 && !ok[k] ? (double)s.gx : 0.0;
-                                ux[k] += __builtin_fma(-kHalfLn2, (double)t4[0], (double)t4[2] - cg);
-                                uy[k] += __builtin_fma(-kHalfLn2, (double)t4[1], (double)t4[3]);
-                            } else {
-                                float t2[2] = {0.f, 0.f};
-                                dlp32_src<NI, true>(rx, ry, s, t2, ok[k], m0);
-                                ux[k] += (double)t2[0];
-                                uy[k] += (double)t2[1];
+#pragma unroll
+                            for (int m = 0; m < NI; ++m) {
+                                const bool use = ok[k] || (m != m0 && j < a.n_src);
+                                const float rx[1] = {(float)(px[k][m] - s.x)};
+                                if constexpr (OP == S2D_OP_SLP) {
+                                    // the logarithm's integer part apart: its rounding stays below
+                                    // one unit of the fraction's last place
+                                    const float q = __builtin_fmaf(rx[0], rx[0], ry * ry);
+                                    const float t = __builtin_fmaf(rx[0], s.gx, ry * s.gy) * __builtin_amdgcn_rcpf(q);
+                                    const float lm = __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(q));
+                                    const double l = -kHalfLn2 * ((double)__builtin_amdgcn_frexp_expf(q) + (double)lm);
+                                    const double cx = __builtin_fma(l, (double)s.gx, (double)(rx[0] * t));
+                                    const double cy = __builtin_fma(l, (double)s.gy, (double)(ry * t));
+                                    ux[k] += use ? cx : 0.0;
+                                    uy[k] += use ? cy : 0.0;
+                                } else {
+                                    float t2[2] = {0.f, 0.f};
+                                    dlp32_src<1>(rx, ry, s, t2);
+                                    ux[k] += use ? (double)t2[0] : 0.0;
+                                    uy[k] += use ? (double)t2[1] : 0.0;
+                                }
                             }
                         }
                     }

@@ -336,3 +336,52 @@ def test_no_sources_with_on_curve_targets(mode):
     torch.cuda.synchronize()
     nan = torch.as_tensor(oc >= 0, device="cuda")
     assert torch.isnan(u[:, nan]).all() and torch.all(u[:, ~nan] == 0)
+
+
+# FP32C sums over a tile's own neighbourhood add float terms in FP64: the error
+# is that of the terms' own roundings, emulated here (the hardware's reciprocal
+# and logarithm may be off by one unit of the last place where the emulation
+# has half of one, hence the factor; float sums of neighbouring terms or images
+# double the error and more).
+@pytest.mark.parametrize("img,d", [((0, 0), 1.0), ((-1, 1), 0.66)])
+def test_float_terms_near_own_curves_are_added_in_fp64(img, d):
+    import torch
+    import paper_1510_05616_amd as s2d
+    f32 = np.float32
+    got, want = [], []
+    for seed in range(12):
+        rng = np.random.default_rng(seed)
+        parts = []
+        for i in range(2):
+            t = 2 * np.pi * np.arange(64) / 64
+            f = [sum((rng.normal() * np.cos(k * t) + rng.normal() * np.sin(k * t)) / k ** 2 for k in range(1, 7))
+                 for _ in range(2)]
+            c = synth.ellipse_curve(0.25, 0.14, 64, (0.13 * i, 0.68 * i), phi=rng.uniform(1, 2))
+            parts.append((c.x, c.y, c.nx, c.ny, c.w, c.kappa, f[0], f[1]))
+        cs = synth.concat_curves(parts)
+        cur = np.repeat(np.arange(2, dtype=np.int32), 64)
+        src, trg = s2d.Curves(cs), s2d.Targets(cs.x, cs.y, cur, np.arange(128, dtype=np.int32))
+        r = []
+        for mode in MODES:
+            u = torch.zeros(2, 128, dtype=torch.float64, device="cuda")
+            s2d.stokes2d_slp_eval(mode, src, trg, d, img[0], img[1], 1.0, u[0], u[1])
+            r.append(u.cpu().numpy())
+        got.append(r[1] - r[0])
+        e = np.zeros((2, 128))
+        gx, gy = cs.w * cs.fx, cs.w * cs.fy
+        for n in range(img[0], img[1] + 1):
+            rx, ry = cs.x[:, None] - n * d - cs.x[None], cs.y[:, None] - cs.y[None]
+            on = (cur[:, None] != cur[None]) | (n != 0)
+            q = np.where(on, rx * rx + ry * ry, 1.0)
+            a, b, hx, hy = rx.astype(f32), ry.astype(f32), gx.astype(f32), gy.astype(f32)
+            p = np.where(on, (a.astype(float) ** 2 + (b * b).astype(float)).astype(f32), f32(1))
+            t = ((a.astype(float) * hx + (b * hy).astype(float)).astype(f32) * (f32(1) / p)).astype(f32)
+            m, ex = np.frexp(p)
+            l = -0.5 * np.log(2.0) * (ex + np.log2(m.astype(float)).astype(f32).astype(float))
+            L, T = -0.5 * np.log(q), (rx * gx + ry * gy) / q
+            e[0] += np.where(on, l * hx + (a * t).astype(float) - L * gx - rx * T, 0.0).sum(1)
+            e[1] += np.where(on, l * hy + (b * t).astype(float) - L * gy - ry * T, 0.0).sum(1)
+        want.append(e / (4 * np.pi))
+    g, w = np.sqrt(np.mean(np.square(got))), np.sqrt(np.mean(np.square(want)))
+    print(f"images {img}: FP32C error {g:.2e}, of the terms {w:.2e}", flush=True)
+    assert 0 < g < 1.4 * w
