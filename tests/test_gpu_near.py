@@ -718,3 +718,26 @@ def test_auto_meets_1e5_on_held_out_targets(trained, held_out):
     frac = [(fb == k).double().mean().item() for k in range(3)]
     print(f"AUTO at 1e-5 per curve: E = {E:.2e}, learned/quadrature/none {frac}", flush=True)
     assert E <= 1e-5 and frac[0] > 0.5
+
+
+def test_training_gradient_adds_its_runs_without_rounding():
+    """Sixteen samples are sixteen runs of one: the batch's gradient is the sum
+    of the samples' own (scaled by 1/16, exact in float), rounded once."""
+    import torch
+    from paper_1510_05616_amd import near
+    B = 16
+    X, _, _, _, T = _rand_records(np.random.default_rng(3), B)
+    Xt, Tt = (torch.as_tensor(a.astype(np.float32), device="cuda") for a in (X, T))
+    prm = torch.as_tensor(near.dict_to_params(_rand_params()).astype(np.float32), device="cuda")
+    ws = torch.empty(near.near_mlp_train_workspace_size(B), dtype=torch.uint8, device="cuda")
+    g = torch.zeros_like(prm)
+    near.near_mlp_train_step(B, None, Xt, Tt, prm, None, None, 0, 0.0, g, None, ws)
+    parts = torch.zeros((B,) + prm.shape, dtype=torch.float32, device="cuda")
+    for i in range(B):
+        near.near_mlp_train_step(1, None, Xt[i:i + 1], Tt[i:i + 1], prm, None, None, 0, 0.0, parts[i], None, ws)
+    torch.cuda.synchronize()
+    want = parts.double().sum(0) / B
+    off = (g.double() - want).abs()
+    # half a unit of the last place (and the rounding of `want`); below the normal range no claim
+    assert int((off > 2.0 ** -24 * 1.0001 * want.abs() + 1e-36).sum()) == 0
+    assert float(g.abs().max()) > 0
