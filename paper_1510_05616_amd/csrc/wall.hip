@@ -15,7 +15,8 @@
 // Two routes, chosen per curve on the device (the sizes are known there only)
 // by wall_factor: with N1 the largest divisor of N up to sqrt(N), N2 = N / N1,
 //  * 8 (N1 + N2) < N, factored: the series are the two complex ones
-//    (x - s d t / 2 pi) + i y and fx + i fy; a transform of N points is N2
+//    (x - s d t / 2 pi) + i y and fx + i fy, the second components scaled to
+//    the size of the first; a transform of N points is N2
 //    transforms of N1 points, a twiddle factor each, and N1 of N2 points, the
 //    fine points P shifted inverse transforms: N1 + N2 terms a value;
 //  * otherwise (small N, a large prime factor), direct: coefficients V_k,
@@ -43,8 +44,8 @@
 // The factored route keeps its sums inside the curve's own share of the direct
 // one's scratch: stage 1 in the first chunk's records (4 of 8 doubles), the
 // coefficients in the curve's records (4 of 8), stage 2 in the first chunk's
-// six arrays, and N1 in double 4 of the curve's last record, which the direct
-// route (k <= N/2 < N - 1) leaves alone.
+// six arrays, and N1 and the components' factors in doubles 4 .. 7 of the
+// curve's last record, which the direct route (k <= N/2 < N - 1) leaves alone.
 #include "s2d_near.h"
 
 #include <algorithm>
@@ -127,18 +128,41 @@ __device__ __forceinline__ void rotate(int a0, int a1, int64_t base, int64_t ste
     }
 }
 
-// N1 of the curve at lo (0: direct route), from wall_factor
+// What wall_factor leaves in doubles 4 .. 7 of the curve's last record: N1 (0:
+// direct route), the factors that bring y to x's size and fy to fx's (powers
+// of two; 0: the component is zero throughout), and whether x (1) and fx (2)
+// are not.
+struct Factored { double n1, ry, rf, bits; };
+__device__ __forceinline__ Factored factored(const WallArgs &a, int64_t lo, int64_t N) {
+    const double *v = ((const Coef8 *)a.coef)[lo + N - 1].v + 4;
+    return Factored{v[0], v[1], v[2], v[3]};
+}
 __device__ __forceinline__ int factor_of(const WallArgs &a, int64_t lo, int64_t N) {
     const int n1 = (int)((const Coef8 *)a.coef)[lo + N - 1].v[4];
     return n1 >= 2 && N % n1 == 0 ? n1 : 0;
 }
 
-// a wave per curve: N1, and the fine curve's offset where one is asked for
-__global__ __launch_bounds__(256) void wall_factor(WallArgs a) {
-    const int c = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave), lane = threadIdx.x & (kWave - 1);
-    if (c > a.n_curves) return;
+// node g = lo + j relative to the curve's first node, x without its advance
+__device__ __forceinline__ double4 wall_series(const WallArgs &a, int64_t lo, int64_t j, double sd) {
+    const int64_t g = lo + j;
+    return double4{(a.x[g] - a.x[lo]) - sd * (double)j, a.y[g] - a.y[lo], a.fx[g], a.fy[g]};
+}
+
+// orders magnitudes; 0 for zero, 0x7ff00000 and above for what is not finite
+__device__ __forceinline__ uint32_t size_key(double v) {
+    return ((uint32_t)__double2hiint(v) & 0x7fffffffu) | (__double2loint(v) != 0 ? 1u : 0u);
+}
+
+// A workgroup per curve: N1, the components' factors, and the fine curve's
+// offset where one is asked for.  A complex series leaves rounding of its
+// larger component in the smaller one and a value that is not finite in both:
+// components come in at one size, and curves with such values, or with sizes
+// 2^500 apart, take the direct route.
+__global__ __launch_bounds__(1024) void wall_factor(WallArgs a) {
+    __shared__ uint32_t top[4];
+    const int c = blockIdx.x, lane = threadIdx.x & (kWave - 1);
     const int64_t lo = a.off[c];
-    if (a.ooff && lane == 0) a.ooff[c] = (int32_t)lo * a.P;
+    if (a.ooff && threadIdx.x == 0) a.ooff[c] = (int32_t)lo * a.P;
     if (c == a.n_curves) return;
     const int64_t hi = a.off[c + 1];
     if (!curve_ok(lo, hi, a.n_nodes)) return;
@@ -148,8 +172,42 @@ __global__ __launch_bounds__(256) void wall_factor(WallArgs a) {
         if (N % (uint32_t)t == 0) best = (uint32_t)t;
 #pragma unroll
     for (int m = kWave / 2; m >= 1; m >>= 1) best = max(best, (uint32_t)__shfl_xor((int)best, m, kWave));
-    const bool fast = 8ull * (best + N / best) < N;
-    if (lane == 0) ((Coef8 *)a.coef)[hi - 1].v[4] = fast ? (double)best : 0.0;
+    double *o = ((Coef8 *)a.coef)[hi - 1].v + 4;
+    if (8ull * (best + N / best) >= N) {                // the same for all threads
+        if (threadIdx.x == 0) o[0] = 0.0;
+        return;
+    }
+    if (threadIdx.x < 4) top[threadIdx.x] = 0;
+    __syncthreads();
+    const double sd = (a.x[lo + 1] > a.x[lo] ? 1.0 : -1.0) * a.d / (double)N;
+    uint32_t k[4] = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int64_t j = threadIdx.x; j < N; j += 1024) {
+        const double4 v = wall_series(a, lo, j, sd);
+        k[0] = max(k[0], size_key(v.x));
+        k[1] = max(k[1], size_key(v.y));
+        k[2] = max(k[2], size_key(v.z));
+        k[3] = max(k[3], size_key(v.w));
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int m = kWave / 2; m >= 1; m >>= 1) k[q] = max(k[q], (uint32_t)__shfl_xor((int)k[q], m, kWave));
+        if (lane == 0) atomicMax(&top[q], k[q]);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    bool fit = true;
+    const auto ratio = [&](uint32_t x, uint32_t y) {     // y's factor
+        const int e = (int)(x >> 20) - (int)(y >> 20);
+        fit = fit && max(x, y) < 0x7ff00000u && (x == 0 || y == 0 || abs(e) <= 500);
+        return y == 0 ? 0.0 : x == 0 ? 1.0 : ldexp(1.0, e);
+    };
+    const double ry = ratio(top[0], top[1]), rf = ratio(top[2], top[3]);
+    o[0] = fit ? (double)best : 0.0;
+    o[1] = ry;
+    o[2] = rf;
+    o[3] = (double)((top[0] ? 1 : 0) | (top[2] ? 2 : 0));
 }
 
 // Z += (v.x + i v.y) z, F += (v.z + i v.w) z
@@ -165,13 +223,16 @@ __device__ __forceinline__ void add_turned(Cx &Z, Cx &F, Cx z, double4 v) {
 // rounding in x) times e^{-2 pi i a k1 / N1}, and the twiddle factor e^{-2 pi i b k1 / N}
 __device__ __forceinline__ void factored_dft_a(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t l, double s) {
     const int N2 = (int)(N / N1), k1 = (int)(l % N1), b = (int)(l / N1);
-    const double sd = s * a.d / (double)N, x0 = a.x[lo], y0 = a.y[lo];
+    const double sd = s * a.d / (double)N;
+    const Factored fac = factored(a, lo, N);
     Cx Z{0, 0}, F{0, 0};
     rotate(
         0, N1, 0, (N1 - k1) % N1, N1,
         [&](int i) {
-            const int64_t j = (int64_t)N2 * i + b, g = lo + j;
-            return double4{(a.x[g] - x0) - sd * (double)j, a.y[g] - y0, a.fx[g], a.fy[g]};
+            double4 v = wall_series(a, lo, (int64_t)N2 * i + b, sd);
+            v.y *= fac.ry;
+            v.w *= fac.rf;
+            return v;
         },
         [&](int, Cx z, double4 v) { add_turned(Z, F, z, v); });
     const Cx t = root((N - (int64_t)b * k1 % N) % N, N);
@@ -510,11 +571,18 @@ __device__ __forceinline__ void factored_synth_b(const WallArgs &a, int64_t lo, 
         for (int e = 0; e < kSynthOut; ++e) z[e] = mul(z[e], w[e][kBatch]);
     }
     const double invN = 1.0 / (double)N;
+    const Factored fac = factored(a, lo, N);
+    const int bits = (int)fac.bits;
+    double out[6];                                  // a zero component stays an exact zero
+    out[0] = out[4] = (bits & 1) ? invN : 0.0;
+    out[1] = out[5] = fac.ry != 0.0 ? invN * (1.0 / fac.ry) : 0.0;
+    out[2] = (bits & 2) ? invN : 0.0;
+    out[3] = fac.rf != 0.0 ? invN * (1.0 / fac.rf) : 0.0;
 #pragma unroll
     for (int e = 0; e < kSynthOut; ++e) {
         if (kSynthOut * g2 + e >= N2) return;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) acc[e][q] *= invN;
+        for (int q = 0; q < 6; ++q) acc[e][q] *= out[q];
         acc[e][0] += a.x[lo];
         acc[e][1] += a.y[lo];
         fine_point(a, lo, M, P * (k1 + (int64_t)N1 * k2[e]) + r, s, acc[e], acc[e] + 4);
@@ -635,7 +703,7 @@ WallScratch wall_scratch(int64_t n_nodes, int P) {
 
 hipError_t wall_upsample_launch(const WallArgs &a, hipStream_t st) {
     if (a.n_curves > 0 && a.off)
-        hipLaunchKernelGGL(wall_factor, dim3((unsigned)((a.n_curves + 1 + 3) / 4)), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(wall_factor, dim3((unsigned)a.n_curves + 1), dim3(1024), 0, st, a);
     if (a.n_nodes > 0) {
         const unsigned g1 = grid(a.n_nodes), g2 = grid(((int64_t)a.P * a.n_nodes + 1) / 2);
         hipLaunchKernelGGL(wall_dft_part, dim3(g1, (unsigned)a.s1), dim3(256), 0, st, a);

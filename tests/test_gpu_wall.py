@@ -424,3 +424,39 @@ def test_upsample_factored_and_direct_curves(P):
         err = _rel(np.concatenate(a), np.concatenate(b))
         print(f"factored P={P} {k} {err:.2e}", flush=True)
         assert err <= (TOL_DER if k in ("nx", "ny", "w") else TOL_VAL), (k, err)
+
+
+# A factored transform carries two components as one complex series: each must
+# keep its own accuracy (bar: the one of the other tests, per component), zero
+# components stay zero and a NaN stays in its own.
+@pytest.mark.parametrize("scale", [1e9, 2.0 ** -600, 0.0])
+def test_upsample_components_keep_their_accuracy(scale):
+    walls, d = _mixed_walls((2000, 4006), seed=31)
+    P = 4
+    full, off = _gpu_upsample(walls, d, P)
+    for which in ("fx", "fy"):
+        w = synth.concat_curves([tuple(getattr(walls, k)[walls.curve_off[c]:walls.curve_off[c + 1]] for k in
+                                       ("x", "y", "nx", "ny", "w", "kappa", "fx", "fy")) for c in range(4)])
+        setattr(w, which, getattr(walls, which) * scale)
+        g, _ = _gpu_upsample(w, d, P)
+        for k, a, b in zip(NAMES, g, full):
+            # the other arrays, and this one up to its scale
+            err = _rel(a, b * scale) if k == which and scale else np.abs(a).max() if k == which else _rel(a, b)
+            print(f"{which} scaled by {scale:.1e}: {k} {err:.2e}", flush=True)
+            tol = TOL_DER if k in ("nx", "ny", "w") else TOL_VAL if scale or k != which else 0.0
+            assert err <= tol, (which, k, err)
+
+
+def test_upsample_nan_density_stays_in_its_component():
+    walls, d = _mixed_walls((2000,), seed=32)
+    P = 4
+    full, off = _gpu_upsample(walls, d, P)
+    walls.fx[7] = np.nan
+    g, _ = _gpu_upsample(walls, d, P)
+    M = off[1]
+    for k, a, b in zip(NAMES, g, full):
+        if k == "fx":
+            assert np.isnan(a[:M]).all() and _rel(a[M:], b[M:]) <= TOL_VAL
+        else:
+            # the curve of the NaN takes the direct sums
+            assert _rel(a, b) <= (TOL_DER if k in ("nx", "ny", "w") else TOL_VAL), k
