@@ -14,23 +14,29 @@
 //
 // Two routes, chosen per curve on the device (the sizes are known there only)
 // by wall_factor: with N1 the largest divisor of N up to sqrt(N), N2 = N / N1,
-//  * 8 (N1 + N2) < N, factored: the series are the two complex ones
-//    (x - s d t / 2 pi) + i y and fx + i fy, the second components scaled to
-//    the size of the first; a transform of N points is N2
-//    transforms of N1 points, a twiddle factor each, and N1 of N2 points, the
-//    fine points P shifted inverse transforms: N1 + N2 terms a value;
+//  * 8 (N1 + N2) < N and 20 (N1 + N2) < N + 500 + N^2 / 48,000, factored: the
+//    series are the two complex ones (x - s d t / 2 pi) + i y and fx + i fy, fy
+//    scaled to the size of fx; a transform of N points is N2 transforms of N1
+//    points, a twiddle factor each, and N1 of N2 points, the fine points P shifted inverse transforms: N1 + N2 terms a value;
 //  * otherwise (small N, a large prime factor), direct: coefficients V_k,
 //    k = 0 .. N/2, as sums over the nodes and fine values as sums over the
 //    modes, N/2 terms for four values at a time by symmetry.
-// About 16 FP64 instructions a term on either; N / 4 terms a value (both
-// stages, symmetry counted) on the direct route against 2 (N1 + N2) put the
-// line at N1 + N2 = N / 8.  Two walls refined 8 times, whole call: 500 against
-// 502 (= 2 x 251, direct) nodes 44 us each, the five launches; 2,000 against
-// 2,018 54 and 76 us; 16,000 against 16,022 152 and 928 us.  Each kernel serves
-// both routes, a curve's work-items leaving where the other route has them, so
-// the factored one adds no launch.  At 16,000 nodes its kernels (29, 22, 58 and
-// 68 us) wait for the caches: 500 waves in stage 1, 75 MB of intermediate sums
-// read 64 times over in the last, which takes two outputs from each.
+// Both are chains of loads and multiply-adds: a factored value takes N1 + N2
+// terms in turn, the direct route N^2 / 4 terms over the chip.  Kernel times of
+// two walls refined 8 times, factored against direct at the same N, us: 300
+// nodes (15 x 20) 37 / 35, 500 (20 x 25) 41 / 39, 1,000 (25 x 40) 47 / 46, 1,500
+// (30 x 50) 53 / 58, 2,000 (40 x 50) 58 / 65, 2,500 (50 x 50) 63 / 72, 3,014 (22
+// x 137) 86 / 84, 4,000 (50 x 80) 78 / 117, 7,940 (20 x 397) 250 / 290, 7,984 (16
+// x 499) 300 / 294, 16,000 (125 x 128) 187 / 943.  Hence the second line; below
+// 1,500 nodes the times are alike and the factored route's normals are three to
+// ten times closer to the exact ones (4e-13 against 2e-12 at 2,352 nodes).
+// Each kernel serves both routes, a curve's work-items leaving where the other
+// route has them, so the factored one adds no launch; its loops are kept to the
+// registers of the direct route's (124 and 126 in the first and third kernel:
+// with 211 and 192 the direct route took 1.2-1.45 times as long).
+// At 16,000 nodes its kernels (12, 26, 24, 58 and 68 us) wait for the caches:
+// 500 waves in stage 1, 75 MB of intermediate sums read 64 times over in the
+// last, which takes two outputs from each.
 //
 // Direct route: coefficients are stored interleaved, 8 doubles per (curve, k):
 // re and im of the four series.  Both sums are split into chunks (over the
@@ -39,13 +45,13 @@
 // chunk order by a second kernel (deterministic results).  A wave whose lanes
 // all lie in one curve reads the coefficients (and in stage 1 the nodes)
 // through the scalar data path.  Twiddle factors follow a rotation recurrence
-// re-anchored with sincospi every 32 steps on both routes.
+// re-anchored with sincospi every 32 steps (16 on the factored route).
 //
 // The factored route keeps its sums inside the curve's own share of the direct
 // one's scratch: stage 1 in the first chunk's records (4 of 8 doubles), the
 // coefficients in the curve's records (4 of 8), stage 2 in the first chunk's
-// six arrays, and N1 and the components' factors in doubles 4 .. 7 of the
-// curve's last record, which the direct route (k <= N/2 < N - 1) leaves alone.
+// six arrays, and N1 and fy's factor in doubles 4 .. 6 of the curve's
+// last record, which the direct route (k <= N/2 < N - 1) leaves alone.
 #include "s2d_near.h"
 
 #include <algorithm>
@@ -55,6 +61,7 @@ namespace s2d {
 namespace {
 
 constexpr int kAnchor = 32;
+constexpr int kTurn = 16;
 
 struct alignas(16) Coef8 { double v[8]; };        // (re, im) of x~, y, fx, fy
 
@@ -93,7 +100,8 @@ __device__ __forceinline__ bool curve_ok(int64_t lo, int64_t hi, int64_t n_nodes
 
 // e^{2 pi i num / den}, 0 <= num < den
 struct Cx { double r, i; };
-__device__ __forceinline__ Cx root(int64_t num, int64_t den) {
+// a call of its own: sincospi inlined for every factor keeps them all in registers
+__device__ __noinline__ Cx root(uint32_t num, uint32_t den) {
     Cx z;
     sincospi(2.0 * (double)num / (double)den, &z.i, &z.r);
     return z;
@@ -101,43 +109,52 @@ __device__ __forceinline__ Cx root(int64_t num, int64_t den) {
 __device__ __forceinline__ Cx mul(Cx a, Cx b) { return {a.r * b.r - a.i * b.i, a.r * b.i + a.i * b.r}; }
 
 // use(a, e^{2 pi i (base + a step) / den}, load(a)) for a = a0 .. a1-1 (0 <= base,
-// step < den), the loads of eight terms issued together (past the end: zero
-// terms): one term's at a time wait for a cache miss each.  A term's factor is
-// at most six products away from sincospi values (a chain over all of an
-// anchor's terms doubles the error of the derivatives).
+// step < den), the loads of four terms issued together (past the end: zero
+// terms): one term's at a time wait for a cache miss each, and eight terms' at a
+// time take registers that the direct route's kernels pay for (two waves a SIMD
+// instead of four: 1.24-1.33 times their time).  A term's factor is at most
+// five products away from sincospi values (a chain over 32 terms doubles the
+// error of the derivatives).
 template <class L, class F>
-__device__ __forceinline__ void rotate(int a0, int a1, int64_t base, int64_t step, int64_t den, L &&load, F &&use) {
-    constexpr int kBatch = 8;
-    Cx w[kBatch + 1] = {{1.0, 0.0}, root(step, den), root(2 * step % den, den), {}, root(4 * step % den, den),
-                        {}, {}, {}, root(8 * step % den, den)};
-    w[3] = mul(w[2], w[1]);
+__device__ __forceinline__ void rotate(int a0, int a1, uint32_t base, uint32_t step, uint32_t den, L &&load, F &&use) {
+    if (a0 >= a1) return;
+    Cx w1 = root(step, den), w2 = root((uint32_t)(2ull * step % den), den), w4 = root((uint32_t)(4ull * step % den), den);
+    for (int s0 = a0; s0 < a1; s0 += kTurn) {
+        Cx z = root((uint32_t)((base + (uint64_t)s0 * step) % den), den);
+        const int s1 = min(s0 + kTurn, a1);
+        for (int a = s0; a < s1; a += 4) {
+            double4 v[4];
 #pragma unroll
-    for (int e = 5; e < kBatch; ++e) w[e] = mul(w[4], w[e - 4]);
-    for (int s0 = a0; s0 < a1; s0 += kAnchor) {
-        Cx z = root((base + s0 * step) % den, den);
-        const int s1 = min(s0 + kAnchor, a1);
-        for (int a = s0; a < s1; a += kBatch) {
-            double4 v[kBatch];
-#pragma unroll
-            for (int e = 0; e < kBatch; ++e) v[e] = load(min(a + e, s1 - 1));
-#pragma unroll
-            for (int e = 0; e < kBatch; ++e)
-                use(a + e, e ? mul(z, w[e]) : z, a + e < s1 ? v[e] : double4{0.0, 0.0, 0.0, 0.0});
-            z = mul(z, w[kBatch]);
+            for (int e = 0; e < 4; ++e) v[e] = load(min(a + e, s1 - 1));
+            const double4 none{0.0, 0.0, 0.0, 0.0};
+            use(a, z, v[0]);
+            use(a + 1, mul(z, w1), a + 1 < s1 ? v[1] : none);
+            const Cx y = mul(z, w2);
+            use(a + 2, y, a + 2 < s1 ? v[2] : none);
+            use(a + 3, mul(y, w1), a + 3 < s1 ? v[3] : none);
+            z = mul(z, w4);
         }
     }
 }
 
-// What wall_factor leaves in doubles 4 .. 7 of the curve's last record: N1 (0:
-// direct route), the factors that bring y to x's size and fy to fx's (powers
-// of two; 0: the component is zero throughout), and whether x (1) and fx (2)
-// are not.
-struct Factored { double n1, ry, rf, bits; };
+// Whether N = N1 N2 nodes are factored: never up to kFactorMin, as
+// N1 + N2 >= 2 sqrt(N).
+constexpr int64_t kFactorMin = 256;
+__device__ __forceinline__ bool pays(uint64_t N1, uint64_t N) {
+    const uint64_t s = N1 + N / N1;
+    return 8 * s < N && 20 * s < N + 500 + N * N / 48000;
+}
+
+// What wall_factor leaves in doubles 4 .. 6 of the curve's last record: N1 (0:
+// direct route), the factor that brings fy to fx's size (a power of two; 0: fy
+// is zero throughout), and 0 where fx is zero throughout, else 1.
+struct Factored { double n1, rf, on; };
 __device__ __forceinline__ Factored factored(const WallArgs &a, int64_t lo, int64_t N) {
     const double *v = ((const Coef8 *)a.coef)[lo + N - 1].v + 4;
-    return Factored{v[0], v[1], v[2], v[3]};
+    return Factored{v[0], v[1], v[2]};
 }
 __device__ __forceinline__ int factor_of(const WallArgs &a, int64_t lo, int64_t N) {
+    if (a.n_nodes <= kFactorMin) return 0;              // no curve can be factored
     const int n1 = (int)((const Coef8 *)a.coef)[lo + N - 1].v[4];
     return n1 >= 2 && N % n1 == 0 ? n1 : 0;
 }
@@ -153,11 +170,13 @@ __device__ __forceinline__ uint32_t size_key(double v) {
     return ((uint32_t)__double2hiint(v) & 0x7fffffffu) | (__double2loint(v) != 0 ? 1u : 0u);
 }
 
-// A workgroup per curve: N1, the components' factors, and the fine curve's
-// offset where one is asked for.  A complex series leaves rounding of its
-// larger component in the smaller one and a value that is not finite in both:
-// components come in at one size, and curves with such values, or with sizes
-// 2^500 apart, take the direct route.
+// A workgroup per curve: N1, fy's factor, and the fine curve's offset where one
+// is asked for.  A complex series leaves rounding of its larger component in
+// the smaller one and a value that is not finite in both: fy comes in at fx's
+// size, and curves with such values, or with sizes 2^500 apart, take the direct
+// route.  (x and y stay as they are: their errors meet in one length, and x's
+// periodic part may be mere rounding, white up to the modes that a derivative
+// magnifies; brought to one size with y it trebles the normals' error.)
 __global__ __launch_bounds__(1024) void wall_factor(WallArgs a) {
     __shared__ uint32_t top[4];
     const int c = blockIdx.x, lane = threadIdx.x & (kWave - 1);
@@ -165,7 +184,7 @@ __global__ __launch_bounds__(1024) void wall_factor(WallArgs a) {
     if (a.ooff && threadIdx.x == 0) a.ooff[c] = (int32_t)lo * a.P;
     if (c == a.n_curves) return;
     const int64_t hi = a.off[c + 1];
-    if (!curve_ok(lo, hi, a.n_nodes)) return;
+    if (a.n_nodes <= kFactorMin || !curve_ok(lo, hi, a.n_nodes)) return;
     const uint32_t N = (uint32_t)(hi - lo);
     uint32_t best = 1;
     for (uint64_t t = 2 + lane; t * t <= N; t += kWave)
@@ -173,7 +192,7 @@ __global__ __launch_bounds__(1024) void wall_factor(WallArgs a) {
 #pragma unroll
     for (int m = kWave / 2; m >= 1; m >>= 1) best = max(best, (uint32_t)__shfl_xor((int)best, m, kWave));
     double *o = ((Coef8 *)a.coef)[hi - 1].v + 4;
-    if (8ull * (best + N / best) >= N) {                // the same for all threads
+    if (!pays(best, N)) {                               // the same for all threads
         if (threadIdx.x == 0) o[0] = 0.0;
         return;
     }
@@ -197,17 +216,12 @@ __global__ __launch_bounds__(1024) void wall_factor(WallArgs a) {
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    bool fit = true;
-    const auto ratio = [&](uint32_t x, uint32_t y) {     // y's factor
-        const int e = (int)(x >> 20) - (int)(y >> 20);
-        fit = fit && max(x, y) < 0x7ff00000u && (x == 0 || y == 0 || abs(e) <= 500);
-        return y == 0 ? 0.0 : x == 0 ? 1.0 : ldexp(1.0, e);
-    };
-    const double ry = ratio(top[0], top[1]), rf = ratio(top[2], top[3]);
+    const int e = (int)(top[2] >> 20) - (int)(top[3] >> 20);
+    const bool fit = max(max(top[0], top[1]), max(top[2], top[3])) < 0x7ff00000u &&
+                     (top[2] == 0 || top[3] == 0 || abs(e) <= 500);
     o[0] = fit ? (double)best : 0.0;
-    o[1] = ry;
-    o[2] = rf;
-    o[3] = (double)((top[0] ? 1 : 0) | (top[2] ? 2 : 0));
+    o[1] = top[3] == 0 ? 0.0 : top[2] == 0 ? 1.0 : ldexp(1.0, e);
+    o[2] = top[2] == 0 ? 0.0 : 1.0;
 }
 
 // Z += (v.x + i v.y) z, F += (v.z + i v.w) z
@@ -222,20 +236,20 @@ __device__ __forceinline__ void add_turned(Cx &Z, Cx &F, Cx z, double4 v) {
 // N2 a + b (positions relative to the first node: y's mean would leave its
 // rounding in x) times e^{-2 pi i a k1 / N1}, and the twiddle factor e^{-2 pi i b k1 / N}
 __device__ __forceinline__ void factored_dft_a(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t l, double s) {
-    const int N2 = (int)(N / N1), k1 = (int)(l % N1), b = (int)(l / N1);
+    const int N2 = (int)((uint32_t)N / (uint32_t)N1), b = (int)((uint32_t)l / (uint32_t)N1), k1 = (int)l - b * N1;
     const double sd = s * a.d / (double)N;
-    const Factored fac = factored(a, lo, N);
+    const double rf = factored(a, lo, N).rf;
     Cx Z{0, 0}, F{0, 0};
     rotate(
         0, N1, 0, (N1 - k1) % N1, N1,
         [&](int i) {
             double4 v = wall_series(a, lo, (int64_t)N2 * i + b, sd);
-            v.y *= fac.ry;
-            v.w *= fac.rf;
+            v.w *= rf;
             return v;
         },
         [&](int, Cx z, double4 v) { add_turned(Z, F, z, v); });
-    const Cx t = root((N - (int64_t)b * k1 % N) % N, N);
+    const uint32_t n = (uint32_t)N, turn = (uint32_t)b * (uint32_t)k1;      // b k1 < N
+    const Cx t = root(turn ? n - turn : 0, n);
     Z = mul(Z, t);
     F = mul(F, t);
     double4 *o = (double4 *)(((Coef8 *)a.part1)[lo + l].v);
@@ -244,7 +258,7 @@ __device__ __forceinline__ void factored_dft_a(const WallArgs &a, int64_t lo, in
 
 // and item k = k1 + N1 k2: coefficient k of both complex series
 __device__ __forceinline__ void factored_dft_b(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t k) {
-    const int N2 = (int)(N / N1), k1 = (int)(k % N1), k2 = (int)(k / N1);
+    const int N2 = (int)((uint32_t)N / (uint32_t)N1), k2 = (int)((uint32_t)k / (uint32_t)N1), k1 = (int)k - k2 * N1;
     const Coef8 *T = (const Coef8 *)a.part1 + lo + k1;
     Cx Z{0, 0}, F{0, 0};
     rotate(
@@ -260,7 +274,8 @@ __device__ __forceinline__ void factored_dft_b(const WallArgs &a, int64_t lo, in
 // e^{2 pi i b (P k1 + r) / (P N)}; the Nyquist term by cos(pi r / P), its
 // derivative by -N/2 sin(pi r / P), times (-1)^q at node q
 __device__ __forceinline__ void factored_synth_a(const WallArgs &a, int64_t lo, int64_t N, int N1, int r, int64_t l) {
-    const int N2 = (int)(N / N1), k1 = (int)(l % N1), b = (int)(l / N1), h = (int)(N / 2);
+    const int N2 = (int)((uint32_t)N / (uint32_t)N1), b = (int)((uint32_t)l / (uint32_t)N1), k1 = (int)l - b * N1;
+    const int h = (int)(N / 2);
     const int64_t P = a.P, step = P * k1 + r;
     const Coef8 *coef = (const Coef8 *)a.coef + lo;
     Cx Z{0, 0}, D{0, 0}, F{0, 0};
@@ -460,7 +475,7 @@ __global__ __launch_bounds__(256) void wall_synth_part(WallArgs a) {
     const int N1 = factor_of(a, lo, N);
     if (N1) {
         const int64_t m = j + blockIdx.y * h * P;
-        if (j < h * P && m < M) factored_synth_a(a, lo, N, N1, (int)(m % P), m / P);
+        if (j < h * P && m < M) factored_synth_a(a, lo, N, N1, (int)((uint32_t)m % (uint32_t)P), (uint32_t)m / (uint32_t)P);
         return;
     }
     if (j > M / 4 || blockIdx.y >= a.s2) return;
@@ -523,66 +538,73 @@ __device__ __forceinline__ void fine_point(const WallArgs &a, int64_t lo, int64_
     a.ofy[g] = val[3];
 }
 
-// Factored stage 2, last step, item t = (g2 N1 + k1) P + r: fine points
-// P (k1 + N1 k2) + r for k2 = 2 g2 and 2 g2 + 1, the sums over b of stage 2's
-// first step times e^{2 pi i b k2 / N2}
-constexpr int kSynthOut = 2;
+// Factored stage 2, last step, item t = (g N1 + k1) P + r: fine points
+// P (k1 + N1 k2) + r for k2 = OUT g .. OUT g + OUT - 1, the sums over b of stage
+// 2's first step times e^{2 pi i b k2 / N2}, BATCH terms' loads at a time.  Two
+// outputs share each load; one in eights halves the chain of loads where the
+// launch leaves the chip room (up to kRound fine points: two waves a SIMD).
+constexpr int64_t kRound = 131072;
+template <int OUT, int BATCH>
 __device__ __forceinline__ void factored_synth_b(const WallArgs &a, int64_t lo, int64_t N, int N1, int64_t t, double s) {
     const int64_t P = a.P, M = P * N, nf = P * a.n_nodes;
-    const int N2 = (int)(N / N1), r = (int)(t % P), k1 = (int)(t / P % N1);
-    const int64_t g2 = t / (P * N1);
-    if (kSynthOut * g2 >= N2) return;
+    const uint32_t N2 = (uint32_t)N / (uint32_t)N1, P32 = (uint32_t)P, tp = (uint32_t)t / P32;
+    const uint32_t r = (uint32_t)t - tp * P32, g = tp / (uint32_t)N1, k1 = tp - g * (uint32_t)N1;
+    if (OUT * g >= N2) return;
     const double *T = a.part2 + P * (lo + k1) + r;
     const int64_t row = P * N1;
-    double acc[kSynthOut][6] = {};
-    // factors as in rotate(): four terms from one value, re-anchored every 16
-    constexpr int kBatch = 4, kTurn = 16;
-    Cx w[kSynthOut][kBatch + 1], z[kSynthOut];
-    int k2[kSynthOut];
+    double acc[OUT][6] = {};
+    // factors as in rotate()
+    const auto turned = [&](uint64_t num) { return root((uint32_t)(num % N2), N2); };
+    Cx w1[OUT], w2[OUT], w4[OUT], wb[OUT], z[OUT];
+    uint32_t k2[OUT];
 #pragma unroll
-    for (int e = 0; e < kSynthOut; ++e) {
-        k2[e] = (int)min(kSynthOut * g2 + e, (int64_t)N2 - 1);
-        w[e][1] = root(k2[e], N2);
-        w[e][2] = root(2 * (int64_t)k2[e] % N2, N2);
-        w[e][3] = mul(w[e][2], w[e][1]);
-        w[e][4] = root(4 * (int64_t)k2[e] % N2, N2);
+    for (int e = 0; e < OUT; ++e) {
+        k2[e] = min(OUT * g + e, N2 - 1);
+        w1[e] = turned(k2[e]);
+        w2[e] = turned(2ull * k2[e]);
+        w4[e] = turned(4ull * k2[e]);
+        wb[e] = BATCH == 4 ? w4[e] : turned((uint64_t)BATCH * k2[e]);
     }
-    for (int b0 = 0; b0 < N2; b0 += kBatch) {
+    for (uint32_t b0 = 0; b0 < N2; b0 += BATCH) {
         if (b0 % kTurn == 0) {
 #pragma unroll
-            for (int e = 0; e < kSynthOut; ++e) z[e] = root((int64_t)b0 * k2[e] % N2, N2);
+            for (int e = 0; e < OUT; ++e) z[e] = turned((uint64_t)b0 * k2[e]);
+        }
+        double v[BATCH][6];
+#pragma unroll
+        for (int f = 0; f < BATCH; ++f) {
+            const double *p = T + (int64_t)min(b0 + f, N2 - 1) * row;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) v[f][q] = p[q * nf];
         }
 #pragma unroll
-        for (int f = 0; f < kBatch; ++f) {
-            double v[6];
+        for (int e = 0; e < OUT; ++e) {
+            Cx y[BATCH];
+            y[0] = z[e];
 #pragma unroll
-            for (int q = 0; q < 6; ++q) v[q] = b0 + f < N2 ? T[q * nf + (b0 + f) * row] : 0.0;
+            for (int f = 1; f < BATCH; ++f) y[f] = f == 4 ? mul(z[e], w4[e]) : (f & 1) ? mul(y[f - 1], w1[e]) : mul(y[f - 2], w2[e]);
 #pragma unroll
-            for (int e = 0; e < kSynthOut; ++e) {
-                const Cx y = f ? mul(z[e], w[e][f]) : z[e];
+            for (int f = 0; f < BATCH; ++f) {
+                const bool in = b0 + f < N2;
+                const double yr = in ? y[f].r : 0.0, yi = in ? y[f].i : 0.0;
 #pragma unroll
                 for (int q = 0; q < 6; q += 2) {
-                    acc[e][q] = __builtin_fma(v[q], y.r, __builtin_fma(-v[q + 1], y.i, acc[e][q]));
-                    acc[e][q + 1] = __builtin_fma(v[q], y.i, __builtin_fma(v[q + 1], y.r, acc[e][q + 1]));
+                    acc[e][q] = __builtin_fma(v[f][q], yr, __builtin_fma(-v[f][q + 1], yi, acc[e][q]));
+                    acc[e][q + 1] = __builtin_fma(v[f][q], yi, __builtin_fma(v[f][q + 1], yr, acc[e][q + 1]));
                 }
             }
+            z[e] = mul(z[e], wb[e]);
         }
-#pragma unroll
-        for (int e = 0; e < kSynthOut; ++e) z[e] = mul(z[e], w[e][kBatch]);
     }
     const double invN = 1.0 / (double)N;
     const Factored fac = factored(a, lo, N);
-    const int bits = (int)fac.bits;
-    double out[6];                                  // a zero component stays an exact zero
-    out[0] = out[4] = (bits & 1) ? invN : 0.0;
-    out[1] = out[5] = fac.ry != 0.0 ? invN * (1.0 / fac.ry) : 0.0;
-    out[2] = (bits & 2) ? invN : 0.0;
-    out[3] = fac.rf != 0.0 ? invN * (1.0 / fac.rf) : 0.0;
+    // a component that is zero stays an exact zero
+    const double outx = fac.on * invN, outy = fac.rf != 0.0 ? invN * (1.0 / fac.rf) : 0.0;
 #pragma unroll
-    for (int e = 0; e < kSynthOut; ++e) {
-        if (kSynthOut * g2 + e >= N2) return;
+    for (int e = 0; e < OUT; ++e) {
+        if (OUT * g + e >= N2) return;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) acc[e][q] *= out[q];
+        for (int q = 0; q < 6; ++q) acc[e][q] *= q == 2 ? outx : q == 3 ? outy : invN;
         acc[e][0] += a.x[lo];
         acc[e][1] += a.y[lo];
         fine_point(a, lo, M, P * (k1 + (int64_t)N1 * k2[e]) + r, s, acc[e], acc[e] + 4);
@@ -605,7 +627,10 @@ __global__ __launch_bounds__(256) void wall_synth_fin(WallArgs a) {
     const double s = a.x[lo + 1] > a.x[lo] ? 1.0 : -1.0;
     const int N1 = factor_of(a, lo, N);
     if (N1) {
-        factored_synth_b(a, lo, N, N1, m, s);
+        if (nf <= kRound)
+            factored_synth_b<1, 8>(a, lo, N, N1, m, s);
+        else
+            factored_synth_b<2, 4>(a, lo, N, N1, m, s);
         return;
     }
     double acc[4] = {0, 0, 0, 0}, dac[2] = {0, 0};
@@ -703,7 +728,8 @@ WallScratch wall_scratch(int64_t n_nodes, int P) {
 
 hipError_t wall_upsample_launch(const WallArgs &a, hipStream_t st) {
     if (a.n_curves > 0 && a.off)
-        hipLaunchKernelGGL(wall_factor, dim3((unsigned)a.n_curves + 1), dim3(1024), 0, st, a);
+        hipLaunchKernelGGL(wall_factor, dim3((unsigned)a.n_curves + 1),
+                           dim3(a.n_nodes <= kFactorMin ? kWave : 1024), 0, st, a);
     if (a.n_nodes > 0) {
         const unsigned g1 = grid(a.n_nodes), g2 = grid(((int64_t)a.P * a.n_nodes + 1) / 2);
         hipLaunchKernelGGL(wall_dft_part, dim3(g1, (unsigned)a.s1), dim3(256), 0, st, a);

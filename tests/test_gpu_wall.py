@@ -460,3 +460,28 @@ def test_upsample_nan_density_stays_in_its_component():
         else:
             # the curve of the NaN takes the direct sums
             assert _rel(a, b) <= (TOL_DER if k in ("nx", "ny", "w") else TOL_VAL), k
+
+
+@pytest.mark.parametrize("P", [1, 4, 8])
+def test_upsample_routes_at_the_line(P):
+    # beyond 8 (N1 + N2) < N a factored size must satisfy
+    # 20 (N1 + N2) < N + 500 + N^2 / 48,000: 1,022 = 14 x 73 and 1,956 = 12 x 163
+    # are direct, 3,014 = 22 x 137 and 7,940 = 20 x 397 (ragged batches of four
+    # and eight, the last turn of 13 terms) factored; at P = 8 all with two outputs
+    # a work-item in the last step (a call of more than 131,072 fine points), else one
+    walls, d = _mixed_walls((1022, 1956, 3014, 7940), seed=40 + P)
+    g, off = _gpu_upsample(walls, d, P)
+    rng = np.random.default_rng(P)
+    got, ref = [[] for _ in NAMES], [[] for _ in NAMES]
+    for c in range(walls.n_curves):
+        s = slice(walls.curve_off[c], walls.curve_off[c + 1])
+        M = int(off[c + 1] - off[c])
+        m = np.unique(np.r_[np.arange(4), M - 1 - np.arange(4), rng.integers(0, M, 56)])
+        r = _long_double_upsample(walls.x[s], walls.y[s], walls.nx[s], walls.ny[s], walls.fx[s], walls.fy[s], d, P, m)
+        for e, (a, b) in enumerate(zip(g, r)):
+            got[e].append(a[off[c] + m])
+            ref[e].append(b)
+    for k, a, b in zip(NAMES, got, ref):
+        err = _rel(np.concatenate(a), np.concatenate(b))
+        print(f"routes P={P} {k} {err:.2e}", flush=True)
+        assert err <= (TOL_DER if k in ("nx", "ny", "w") else TOL_VAL), (k, err)
