@@ -56,28 +56,40 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
     if (p.n_sb > 0 && p.n_tiles > 0) {
         const bool fits = (size_t)p.n_sb * p.sbs * rec_bytes(op, mode) <= kL2Budget;
         const int64_t fill = (int64_t)cus * 4 * 16;
-        // a group's waves keep at least 64 sources each: more groups cost a
-        // partial plane each and the finalize launch
-        const int64_t gmax = std::min<int64_t>(64, std::max<int64_t>(1, p.n_src / (64 * kMaxPairWaves)));
+        // a group's waves keep at least 64 sources each, and of more than 64
+        // groups there are no more than give each CU eight workgroups
+        const int64_t gmax = std::min<int64_t>(std::max<int64_t>(1, p.n_src / (64 * kMaxPairWaves)),
+                                               std::max<int64_t>(64, (8 * (int64_t)cus + p.n_tiles - 1) / p.n_tiles));
+        const bool by8 = !fits && gmax >= 8 && cus >= 8;
         int64_t G = 1;
         if (!(fits && p.n_tiles * kMaxPairWaves >= fill))
             G = std::min<int64_t>(std::max<int64_t>(1, (fill + p.n_tiles * kMaxPairWaves - 1) /
                                                            (p.n_tiles * kMaxPairWaves)), gmax);
-        // Workgroups come a round per CU at a time and a round lasts as long as
-        // its fullest group: of the group counts allowed, the one with the least
-        // rounds x superblocks of the fullest group, where rounds are few.
-        if (G > 1 && p.n_tiles * G < 4 * (int64_t)cus) {
+        // Few workgroups: the group count with the least expected time.  A wave's
+        // superblock of 256 sources takes a time unit (FP64 with three images
+        // 121 us) with 16 waves on its CU, 1.8 with 32 and about 0.6 with 8; a
+        // CU has as many workgroups as the fullest one of its XCD (groups go
+        // round the XCDs where G is a multiple of 8), groups past the last source
+        // are empty, and a plane costs about 1/500 unit.  1e6 sources, at most 64
+        // groups: 64 targets 495 us, 640 targets 1.68 ms; by this rule 207 us and
+        // 1.08 ms.
+        if (G > 1 && p.n_tiles * std::min<int64_t>(G, 64) < 4 * (int64_t)cus) {
             const auto cost = [&](int64_t g) {
                 const int64_t w = std::min<int64_t>(kMaxPairWaves, (p.n_sb + g - 1) / g);
                 const int64_t sps = (p.n_sb + w * g - 1) / (w * g);
-                return (double)((p.n_tiles * g + cus - 1) / cus * std::min(w * sps, p.n_sb)) *
-                       (1.0 + 0.005 * (double)g);
+                const int64_t full = ((p.n_sb + sps - 1) / sps + w - 1) / w;         // groups that have sources
+                const int64_t k = by8 ? (p.n_tiles * ((full + 7) / 8) + cus / 8 - 1) / (cus / 8)
+                                      : (p.n_tiles * full + cus - 1) / cus;
+                const double v = (double)(k * w) / kMaxPairWaves;
+                return (double)(sps * p.sbs) / kSuperBlock * (v <= 1.0 ? 0.25 + 0.75 * v : 0.9 * v + 0.1) +
+                       0.002 * (double)g;
             };
-            int64_t best = G;
-            for (int64_t g = 2; g <= gmax; ++g) best = cost(g) < cost(best) ? g : best;
+            const int64_t step = by8 ? 8 : 1;
+            int64_t best = by8 ? 8 : 2;
+            for (int64_t g = best; g <= gmax; g += step) best = cost(g) < cost(best) ? g : best;
             G = best;
         }
-        if (!fits && gmax >= 8) G = std::min<int64_t>((std::max<int64_t>(G, 8) + 7) / 8 * 8, gmax / 8 * 8);
+        if (by8) G = std::min<int64_t>((std::max<int64_t>(G, 8) + 7) / 8 * 8, gmax / 8 * 8);
         G = std::min<int64_t>(G, 65536);
         if (env_groups) G = std::min<int64_t>(env_groups, p.n_sb);
         // W: the full width, or fewer when the group has fewer superblocks.

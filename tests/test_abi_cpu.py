@@ -97,6 +97,17 @@ def test_workspace_grows_with_problem(L):
             assert 0 < a < b
 
 
+def test_few_targets_split_many_sources_over_the_chip(L):
+    # a split group is a workgroup; its plane of partial sums (16 bytes a
+    # target of the tile) shows in the workspace: one target tile against a
+    # million sources needs about one group per CU, 128 at the least
+    import paper_1510_05616_amd as s2d
+    for op, mode in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        size = [L.stokes2d_workspace_size(op, mode, ctypes.byref(c), ctypes.byref(t))
+                for c, t in (_structs(1000000, 1), _structs(1000000, 64))]
+        assert size[1] - size[0] >= 128 * 16 * 63 - 256
+
+
 def test_batch_tuned_is_host_only_and_reports_the_default(L, tmp_path, monkeypatch):
     import paper_1510_05616_amd as s2d
     monkeypatch.setenv("S2D_TUNE_CACHE", str(tmp_path / "absent.json"))

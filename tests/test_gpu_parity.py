@@ -385,3 +385,27 @@ def test_float_terms_near_own_curves_are_added_in_fp64(img, d):
     g, w = np.sqrt(np.mean(np.square(got))), np.sqrt(np.mean(np.square(want)))
     print(f"images {img}: FP32C error {g:.2e}, of the terms {w:.2e}", flush=True)
     assert 0 < g < 1.4 * w
+
+
+# Few targets against sources that more than 64 split groups share (one and
+# three target tiles, the last ragged; superblocks of 16 and of 64)
+@pytest.mark.parametrize("n_trg,nodes", [(1, 150016), (64, 262145), (150, 300000)])
+@pytest.mark.parametrize("mode", MODES)
+def test_few_targets_many_split_groups(n_trg, nodes, mode):
+    import torch
+    import oracle
+    import paper_1510_05616_amd as s2d
+    c = synth.ellipse_curve(1.0, 0.6, nodes, fx=np.cos, fy=lambda t: np.sin(2 * t) + 0.3)
+    rng = np.random.default_rng(n_trg)
+    x, y = rng.uniform(-2, 2, n_trg), rng.uniform(0.8, 2, n_trg)
+    src, t = s2d.Curves(c), s2d.Targets(x, y)
+    u = torch.zeros(4, n_trg, dtype=torch.float64, device="cuda")
+    s2d.stokes2d_slp_eval(mode, src, t, 5.0, -1, 1, 0.8, u[0], u[1])
+    s2d.stokes2d_dlp_eval(mode, src, t, 5.0, -1, 1, u[2], u[3])
+    torch.cuda.synchronize()
+    g = u.cpu().numpy()
+    o = *oracle.slp(c, x, y, d=5.0, img_lo=-1, img_hi=1, mu=0.8), *oracle.dlp(c, x, y, d=5.0, img_lo=-1, img_hi=1)
+    for i in (0, 2):
+        e = rel_err(g[i], g[i + 1], o[i], o[i + 1])
+        print(f"{n_trg} targets, {nodes} sources, mode {mode}: {e:.2e}", flush=True)
+        assert e <= TOL[mode]
