@@ -19,14 +19,19 @@
 
 namespace s2d {
 
-template <int OP, int PREC, int NI>
+// OWN: Kress's rule too.  Without it the FP32C kernels hold no table of
+// logarithms in LDS, and without SHORT no code for short superblocks: a million
+// targets at 64 sources, workgroups of a wave, 173 us (228 with both in one
+// kernel).
+template <int OP, int PREC, int NI, bool OWN, bool SHORT>
 // register allocation held to 8 waves per SIMD (64 VGPRs): every pair kernel
 // fits without spills, and two 16-wave workgroups then share a CU
 __global__ __launch_bounds__(kMaxPairWaves * kWave) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void pair_kernel(PairArgs a, FinalArgs f) {
-    __shared__ __attribute__((aligned(16))) double ltab[kLogTabWords];
+    constexpr bool kTab = OP == S2D_OP_SLP && (PREC == S2D_FP64 || OWN);
+    __shared__ __attribute__((aligned(16))) double ltab[kTab ? kLogTabWords : 2];
     __shared__ double red[2][kMaxPairWaves - 1][kWave];
-    if (OP == S2D_OP_SLP && (PREC == S2D_FP64 || f.own_rule)) fill_log_table(ltab);
+    if constexpr (kTab) fill_log_table(ltab);
     const int lane = threadIdx.x & (kWave - 1);
     // wave index made wave-uniform for the compiler: the split, and with it
     // every source record address, must be uniform so records take the scalar path
@@ -36,9 +41,9 @@ void pair_kernel(PairArgs a, FinalArgs f) {
     const int group = (int)(blk % a.n_groups);
     const int64_t tile = blk / a.n_groups;
     double ox[1], oy[1];
-    pair_sum<OP, PREC, 1, NI>(a, tile, group * W + wid, lane, ltab, ox, oy);
+    pair_sum<OP, PREC, 1, NI, SHORT>(a, tile, group * W + wid, lane, ltab, ox, oy);
     const int64_t i = tile * kWave + lane;
-    if (OP == S2D_OP_SLP && f.own_rule && group == 0 && i < a.n_trg) {
+    if (OWN && group == 0 && i < a.n_trg) {
         double sx, sy;
         kress_self_one(i, f.n_src, f.on_curve, f.on_node, f.curve_off, f.n_curves, f.sx, f.sy, f.nx, f.ny, f.w, f.fx,
                        f.fy, f.kress, ltab, sx, sy, wid, W);
@@ -65,31 +70,28 @@ void pair_kernel(PairArgs a, FinalArgs f) {
     final_one(f, i, sx, sy);
 }
 
-template <int OP, int PREC, int NI>
+template <int OP, int PREC, int NI, bool OWN>
 static hipError_t launch_t(const Plan &p, const PairArgs &a, const FinalArgs &f, hipStream_t st) {
-    hipLaunchKernelGGL((pair_kernel<OP, PREC, NI>), dim3((unsigned)p.n_blocks), dim3(p.waves * kWave), 0, st, a, f);
+    if (p.sbs < kSuperBlock)
+        hipLaunchKernelGGL((pair_kernel<OP, PREC, NI, OWN, true>), dim3((unsigned)p.n_blocks), dim3(p.waves * kWave), 0,
+                           st, a, f);
+    else
+        hipLaunchKernelGGL((pair_kernel<OP, PREC, NI, OWN, false>), dim3((unsigned)p.n_blocks), dim3(p.waves * kWave), 0,
+                           st, a, f);
     return hipGetLastError();
 }
 
-template <int NI>
+template <int PREC, int NI>
 static hipError_t launch_ni(const Plan &p, const PairArgs &a, const FinalArgs &f, hipStream_t st) {
-    const bool f64 = p.mode == S2D_FP64;
     switch (p.op) {
     case S2D_OP_SLP:
-        return f64 ? launch_t<S2D_OP_SLP, S2D_FP64, NI>(p, a, f, st) : launch_t<S2D_OP_SLP, S2D_FP32C, NI>(p, a, f, st);
-    case S2D_OP_DLP:
-        return f64 ? launch_t<S2D_OP_DLP, S2D_FP64, NI>(p, a, f, st) : launch_t<S2D_OP_DLP, S2D_FP32C, NI>(p, a, f, st);
-    case S2D_OP_SLP_PRESSURE:
-        return f64 ? launch_t<S2D_OP_SLP_PRESSURE, S2D_FP64, NI>(p, a, f, st)
-                   : launch_t<S2D_OP_SLP_PRESSURE, S2D_FP32C, NI>(p, a, f, st);
-    case S2D_OP_DLP_PRESSURE:
-        return f64 ? launch_t<S2D_OP_DLP_PRESSURE, S2D_FP64, NI>(p, a, f, st)
-                   : launch_t<S2D_OP_DLP_PRESSURE, S2D_FP32C, NI>(p, a, f, st);
-    case S2D_OP_SLP_TRACTION:
-        return f64 ? launch_t<S2D_OP_SLP_TRACTION, S2D_FP64, NI>(p, a, f, st)
-                   : launch_t<S2D_OP_SLP_TRACTION, S2D_FP32C, NI>(p, a, f, st);
-    default:
-        return hipErrorInvalidValue;
+        return f.own_rule ? launch_t<S2D_OP_SLP, PREC, NI, true>(p, a, f, st)
+                          : launch_t<S2D_OP_SLP, PREC, NI, false>(p, a, f, st);
+    case S2D_OP_DLP: return launch_t<S2D_OP_DLP, PREC, NI, false>(p, a, f, st);
+    case S2D_OP_SLP_PRESSURE: return launch_t<S2D_OP_SLP_PRESSURE, PREC, NI, false>(p, a, f, st);
+    case S2D_OP_DLP_PRESSURE: return launch_t<S2D_OP_DLP_PRESSURE, PREC, NI, false>(p, a, f, st);
+    case S2D_OP_SLP_TRACTION: return launch_t<S2D_OP_SLP_TRACTION, PREC, NI, false>(p, a, f, st);
+    default: return hipErrorInvalidValue;
     }
 }
 
@@ -98,8 +100,9 @@ hipError_t launch_pair(const Plan &p, const PairArgs &a, const FinalArgs &f, hip
     if (p.waves < 1 || p.waves > kMaxPairWaves || a.n_groups < 1) return hipErrorInvalidValue;
     // images three at a time when the count allows it
     const int n_img = a.img_hi - a.img_lo + 1;
-    if (n_img % 3 == 0) return launch_ni<3>(p, a, f, st);
-    return launch_ni<1>(p, a, f, st);
+    const bool f64 = p.mode == S2D_FP64;
+    if (n_img % 3 == 0) return f64 ? launch_ni<S2D_FP64, 3>(p, a, f, st) : launch_ni<S2D_FP32C, 3>(p, a, f, st);
+    return f64 ? launch_ni<S2D_FP64, 1>(p, a, f, st) : launch_ni<S2D_FP32C, 1>(p, a, f, st);
 }
 
 }  // namespace s2d

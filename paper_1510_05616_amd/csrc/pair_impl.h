@@ -405,14 +405,15 @@ __device__ __forceinline__ bool far_offsets(const SubInfo &si, const double (&px
 // one wave: targets [tile * kWave * TPT, +kWave * TPT) against source split
 // `split` (empty past the last superblock), images img_lo..img_hi in groups
 // of NI (the image count must be a multiple of NI); returns the FP64 sums
-// (ox, oy) of its targets, without the operator's prefactor
+// (ox, oy) of its targets, without the operator's prefactor; SHORT: superblocks
+// of a.sbs < kSuperBlock sources
 // ---------------------------------------------------------------------------
-template <int OP, int PREC, int TPT, int NI>
+template <int OP, int PREC, int TPT, int NI, bool SHORT = false>
 __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int split, int lane, const double *ltab,
                                          double (&ox)[TPT], double (&oy)[TPT]) {
     // superblock range of the split, wave-uniform: the loop runs on the scalar
     // unit and the record addresses it forms stay scalar (n_sb < 2^31)
-    const int sbs = a.sbs;
+    const int sbs = SHORT ? a.sbs : kSuperBlock;
     const int sb0 = __builtin_amdgcn_readfirstlane((int)min((int64_t)split * a.sb_per_split, a.n_sb));
     const int sb1 = __builtin_amdgcn_readfirstlane((int)min((int64_t)sb0 + a.sb_per_split, a.n_sb));
 
@@ -420,7 +421,7 @@ __device__ __forceinline__ void pair_sum(const PairArgs &a, int64_t tile, int sp
     // from records that another XCD has just written: one vector load per line
     // brings a split's records into this XCD's L2 beside the targets' loads.
     uint32_t touched = 0;
-    if (sbs < kSuperBlock) {
+    if constexpr (SHORT) {
         constexpr uint32_t rec = PREC == S2D_FP64 ? sizeof(Rec64Of<OP>) : sizeof(Rec32Of<OP>);
         const uint32_t bytes = (uint32_t)((sb1 - sb0) * sbs) * rec;
         const char *r = (const char *)a.rec + (int64_t)sb0 * sbs * (int64_t)rec;

@@ -86,26 +86,23 @@ __device__ __forceinline__ void kress_self_one(int64_t i, int64_t n_src, const i
     const double xi = x[gi], yi = y[gi];
     for (int k = k0; k < N; k += step) {
         const int gk = lo + k;
-        const double gx = w[gk] * fx[gk], gy = w[gk] * fy[gk];
-        double coef, rrx, rry;
-        if (k == ii) {
-            const double sp = w[gk] * (double)N * 0.15915494309189535;   // N / (2 pi)
-            coef = T[lo] - log(sp);
-            const double ng = nx[gk] * gx + ny[gk] * gy;
-            rrx = gx - nx[gk] * ng;
-            rry = gy - ny[gk] * ng;
-        } else {
-            int m = ii - k;
-            if (m < 0) m += N;
-            const double rx = xi - x[gk], ry = yi - y[gk];
-            const double q = rx * rx + ry * ry;
-            coef = T[lo + m] - 0.5 * log64_tab(q, ltab);
-            const double t = (rx * gx + ry * gy) * rcp64(q);
-            rrx = rx * t;
-            rry = ry * t;
-        }
-        sx += coef * gx + rrx;
-        sy += coef * gy + rry;
+        const bool other = k != ii;                     // the node itself: below
+        const double gx = other ? w[gk] * fx[gk] : 0.0, gy = other ? w[gk] * fy[gk] : 0.0;
+        int m = ii - k;
+        if (m < 0) m += N;
+        const double rx = xi - x[gk], ry = yi - y[gk];
+        const double q = other ? rx * rx + ry * ry : 1.0;
+        const double coef = T[lo + m] - 0.5 * log64_tab(q, ltab);
+        const double t = (rx * gx + ry * gy) * rcp64(q);
+        sx += coef * gx + rx * t;
+        sy += coef * gy + ry * t;
+    }
+    if (ii >= k0 && (ii - k0) % step == 0) {
+        const double gx = w[gi] * fx[gi], gy = w[gi] * fy[gi];
+        const double coef = T[lo] - log(w[gi] * (double)N * 0.15915494309189535);   // N / (2 pi)
+        const double ng = nx[gi] * gx + ny[gi] * gy;
+        sx += coef * gx + (gx - nx[gi] * ng);
+        sy += coef * gy + (gy - ny[gi] * ng);
     }
 }
 
