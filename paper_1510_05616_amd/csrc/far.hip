@@ -345,6 +345,9 @@ __global__ __launch_bounds__(256) void far_tiles(int64_t ns, int64_t nt, int64_t
             txy[p] = x;
             txy[nt + p] = y;
         }
+        // a point that is not finite stays out of its circle, as a NaN does in
+        // fmin and fmax: its own sum or its terms come out so in any case
+        if (!(fabs(x) + fabs(y) < __builtin_inf())) x = y = __builtin_nan("");
     }
     const double gx = __shfl_down(x, 1, kWave) - x, gy = __shfl_down(y, 1, kWave) - y;
     const double gap = lane + 1 < count ? gx * gx + gy * gy : -1.0;

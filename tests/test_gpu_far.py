@@ -265,3 +265,31 @@ def test_pressure_and_traction_routes(mode, nv, sizes, n_free, img):
         e = np.abs(far.cpu().numpy()[:len(r), idx] - r).max() / np.abs(r).max()
         print(f"op {op} against the oracle {e:.1e}", flush=True)
         assert e < 1e-12
+
+
+# A target that is not finite keeps that to itself, wherever its tile lies
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_targets_that_are_not_finite(bad):
+    import torch
+    import types
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    x, y, off, d = _lattice(100, (96,), 3)
+    rng = np.random.default_rng(8)
+    c = types.SimpleNamespace(x=x, y=y, nx=np.cos(x), ny=np.sin(x), w=np.full(len(x), 1e-2), kappa=None,
+                              fx=rng.standard_normal(len(x)), fy=rng.standard_normal(len(x)), curve_off=off)
+    src = s2d.Curves(c)
+    tx, ty = rng.uniform(0, d, 9000), rng.uniform(1.0, 1.4, 9000)
+    ref, out = (torch.zeros(4, 9000, dtype=torch.float64, device="cuda") for _ in range(2))
+    k = np.array([7, 4000, 4001, 8999])
+    for o in (ref, out):
+        t = s2d.Targets(tx, ty)
+        s2d.stokes2d_slp_eval(0, src, t, d, -1, 1, 1.0, o[0], o[1])
+        s2d.stokes2d_dlp_eval(0, src, t, d, -1, 1, o[2], o[3])
+        tx[k[:2]] = bad
+        ty[k[1:]] = bad
+    torch.cuda.synchronize()
+    rest = torch.ones(9000, dtype=torch.bool, device="cuda")
+    rest[k] = False
+    assert not torch.isfinite(out[:, ~rest]).any()
+    _close(out[:, rest], ref[:, rest])
