@@ -293,3 +293,72 @@ def test_targets_that_are_not_finite(bad):
     rest[k] = False
     assert not torch.isfinite(out[:, ~rest]).any()
     _close(out[:, rest], ref[:, rest])
+
+
+def _time(f):
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(4):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 4)
+    return best
+
+
+# A few points far outside the others (placeholder coordinates) must not take
+# the sort keys' resolution from them: the sum stays right everywhere and costs
+# their own tiles, here 3 of 450 (every pair near would cost thirty times the
+# sum; the bar leaves a factor of two for the clock).  Target outliers on either
+# axis, at 1e3 and 1e30 channel lengths, infinite (any number of those); a source
+# outlier.
+@pytest.mark.parametrize("where", ["target x", "target y", "huge", "inf", "many inf", "nan", "source"])
+def test_outliers_keep_the_rest_far(where):
+    import torch
+    import types
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    x, y, off, d = _lattice(300, (96,), 11)
+    rng = np.random.default_rng(4)
+    c = types.SimpleNamespace(x=x, y=y, nx=np.cos(x), ny=np.sin(x), w=np.full(len(x), 1e-2), kappa=None,
+                              fx=rng.standard_normal(len(x)), fy=rng.standard_normal(len(x)), curve_off=off)
+    tx, ty = rng.uniform(0, d, len(x)), rng.uniform(1.0, 1.4, len(x))
+    base = s2d.Curves(c), s2d.Targets(tx, ty)
+    k = [7, 15000, 28000] if where != "many inf" else np.arange(20000, 23000)
+    if where == "source":
+        c.x = x.copy()
+        c.x[k] = 3e3 * d
+    elif where == "target y":
+        ty = ty.copy()
+        ty[k] = -1e3 * d
+    else:
+        tx = tx.copy()
+        tx[k] = {"target x": 1e3 * d, "huge": 1e30 * d, "nan": np.nan}.get(where, np.inf)
+        tx[k[1:]] *= -1             # among the first tiles in the sort order, too
+    src, trg = s2d.Curves(c), s2d.Targets(tx, ty)
+    out = torch.zeros(2, len(x), dtype=torch.float64, device="cuda")
+    ws = torch.empty(s2d.stokes2d_workspace_size(0, 0, src, trg), dtype=torch.uint8, device="cuda")
+    plain = _time(lambda: s2d.stokes2d_slp_eval(0, *base, d, -1, 1, 1.0, out[0], out[1], 0, ws))
+    t = _time(lambda: s2d.stokes2d_slp_eval(0, src, trg, d, -1, 1, 1.0, out[0], out[1], 0, ws))
+    print(f"{where}: {t:.3f} ms, without outliers {plain:.3f}", flush=True)
+    ref = torch.zeros_like(out)
+    # the direct sum of the same targets, 1,000 at a time (fewer than the far route takes)
+    for i in range(0, len(x), 1000):
+        s2d.stokes2d_slp_eval(0, src, s2d.Targets(tx[i:i + 1000], ty[i:i + 1000]), d, -1, 1, 1.0, ref[0, i:i + 1000],
+                              ref[1, i:i + 1000])
+    torch.cuda.synchronize()
+    fa, fb = torch.isfinite(out), torch.isfinite(ref)
+    assert torch.equal(fa, fb)
+    near = torch.ones(len(x), dtype=torch.bool, device="cuda")
+    near[k] = False
+    for sel in (near, ~near):
+        a, b, f = out[:, sel], ref[:, sel], fa[:, sel]
+        if f.any():
+            e = float((a[f] - b[f]).abs().max() / b[f].abs().max())
+            print(f"{where}: far against direct {e:.1e}", flush=True)
+            assert e < 1e-12
+    assert t < 2 * plain
