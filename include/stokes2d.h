@@ -34,15 +34,20 @@
  *   - signed curvature kappa = -(x'' . n) / |x'|^2 (positive on a convex curve
  *     with outward normal);  normals are taken as given.
  *
- * Large sums.  A sum whose (source, target) pairs times images (at most three
- * counted) reach 3 * 2^26 in S2D_FP64 or 2^29 in S2D_FP32C, with 2,048 sources
- * and 1,024 targets at least, takes the far-field route, in FP64 in either
- * mode: sources and targets are sorted along a space-filling curve, near nodes
- * are summed term by term and well separated clusters through expansions
- * truncated below 1e-15 of their terms, in a fixed order.  It needs the
- * workspace stokes2d_workspace_size() gives (about 100 bytes per source node
- * and 70 per target); with a smaller one that still holds the direct sum, the
- * call sums directly in its mode's arithmetic.
+ * Large sums.  With 2,048 sources and 1,024 targets at least, a sum of so many
+ * (source, target) pairs times images (at most three counted) that the
+ * far-field route is the faster one takes that route, in FP64 in either mode:
+ * from 1.2e8 (velocities, one image, S2D_FP64) to 4.5e8 (single-layer pressure,
+ * three images, S2D_FP32C), and later where sources far outnumber targets.
+ * Sources and targets are sorted along a space-filling curve, near nodes are
+ * summed term by term and well separated clusters through expansions truncated
+ * at about 1e-15 of their terms, in a fixed order.  It needs the workspace
+ * stokes2d_workspace_size() gives (about 100 bytes per source node and 70 per
+ * target, and partial sums of up to 256 bytes per target, 2 MB at most); with a
+ * smaller one that still holds the direct sum, the call sums directly in its
+ * mode's arithmetic.  A few points far outside the others cost nothing more;
+ * where many are (several clusters more than about a thousand of their extents
+ * apart), tiles overlap and the route loses its gain.
  *
  * Memory and ownership.  Every array argument is a DEVICE pointer to
  * caller-owned memory, structure-of-arrays, FP64 (int32 for indices), in

@@ -287,7 +287,7 @@ size_t direct_workspace(int op, int mode, const s2d_curves *src, const s2d_targe
 
 size_t layer_workspace(int op, int mode, const s2d_curves *src, const s2d_targets *trg) {
     const size_t direct = direct_workspace(op, mode, src, trg);
-    if (direct == 0 || !far_worth(mode, src->n_nodes, trg->n, 3, false)) return direct;
+    if (direct == 0 || !far_possible(mode, src->n_nodes, trg->n)) return direct;
     return std::max(direct, far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr).total);
 }
 
@@ -295,7 +295,7 @@ int layer_eval(int op, int mode, const s2d_curves *src, const s2d_targets *trg, 
                int32_t img_hi, double mu, double *u, double *v, int accumulate, void *ws, size_t ws_bytes,
                void *stream, const LayerOpts &o) {
     const bool far = trg && src && op >= S2D_OP_SLP && op <= S2D_OP_SLP_TRACTION &&
-                     far_worth(mode, src->n_nodes, trg->n, img_hi - img_lo + 1, o.ready != nullptr);
+                     far_worth(op, mode, src->n_nodes, trg->n, img_hi - img_lo + 1, o.ready != nullptr);
     const FarLayout L = far ? far_layout(op, src->n_nodes, trg->n, trg->on_curve != nullptr) : FarLayout{};
     if (!far || !ws || ws_bytes < L.total)
         return eval(op, mode, src, trg, d, img_lo, img_hi, mu, u, v, accumulate, ws, ws_bytes, stream, o.tnx, o.tny,
@@ -1242,7 +1242,7 @@ NearWallLayout near_wall_layout(int method, const s2d_curves *w, const s2d_targe
     // layouts grow with the target count, so the full one covers AUTO's lists
     if (method != S2D_NEAR_MLP)
         for (const s2d_curves *c : {(const s2d_curves *)&f, w})
-            if (s2d::far_worth(S2D_FP64, c->n_nodes, t->n, 3, false))
+            if (s2d::far_possible(S2D_FP64, c->n_nodes, t->n))
                 fb = std::max(fb, s2d::far_layout(S2D_OP_DLP, c->n_nodes, t->n, false).total);
     L.pair = o;
     L.need = o + align256(pb);

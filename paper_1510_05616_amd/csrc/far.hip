@@ -1119,15 +1119,34 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve) {
     return L;
 }
 
-// Velocities measured at vesicle and wall sources, images -1..1, far (set-up
-// included) / direct FP64 / direct FP32C, ms: 2^25.7 pairs 0.20 / 0.17 / 0.08;
-// 2^26.9 0.23 / 0.30 / 0.15; 2^27.7 0.24 / 0.45 / 0.23; 2^28.6 0.29 / 0.86 /
-// 0.39; 2^30.1 0.36 / 2.05 / 0.98; 2^33.5 0.68 / 18.9 / 8.7.  A direct sum
-// costs as much per image, the far-field one hardly more for three images than
-// for one; without the set-up (0.08 ms) the lines meet at half the size.
-bool far_worth(int mode, int64_t ns, int64_t nt, int n_img, bool reuse) {
-    const int64_t least = reuse ? (int64_t)3 << 25 : mode == S2D_FP64 ? (int64_t)3 << 26 : (int64_t)1 << 29;
-    return ns >= 2048 && nt >= 1024 && ns + nt < (int64_t)1 << 28 && ns * nt * std::min(n_img, 3) >= least;
+// A direct sum takes about 22 us and kDirect[op][mode][images not grouped by
+// three] us per 2^20 (source, target, image) triples; the far-field one, set-up
+// included, about 140 us, 0.45 us per 1,000 sources, 1 us per 1,000 targets and
+// 0.6 us for every source per target (a target tile's share of near sources
+// grows as targets thin out), hardly more for three images than for one.  Far / direct, us, images -1..1,
+// FP64 single layer, its pressure, FP32C single layer: 2,496 sources x 30,000
+// targets 148 / 145, 130 / 90, 147 / 88; 9,984 x 14,000 151 / 270, 136 / 162, 150
+// / 152; 60,000 x 5,000 181 / 646, 162 / 395, 182 / 365; 256,000 x 1,100 416 / 538,
+// 385 / 327, 415 / 293; 256,000 x 3,000 274 / 1,502, 253 / 904, 275 / 796.  With a
+// set-up for several densities (about 80 us) the velocities' lines lie at half
+// the size.
+bool far_worth(int op, int mode, int64_t ns, int64_t nt, int n_img, bool reuse) {
+    static const double kDirect[5][2][2] = {{{0.66, 1.10}, {0.35, 0.56}},
+                                            {{0.59, 0.74}, {0.37, 0.52}},
+                                            {{0.40, 0.51}, {0.29, 0.41}},
+                                            {{0.60, 0.83}, {0.38, 0.58}},
+                                            {{0.60, 0.74}, {0.42, 0.49}}};
+    if (op < S2D_OP_SLP || op > S2D_OP_SLP_TRACTION || ns < 2048 || nt < 1024 || ns + nt >= (int64_t)1 << 28) return false;
+    const double triples = (double)ns * (double)nt * std::min(n_img, 3);
+    if (reuse) return triples >= (double)(3 << 25);
+    const double direct = triples / (1 << 20) * kDirect[op][mode != S2D_FP64][n_img % 3 != 0];
+    return direct >= 118.0 + 0.45e-3 * (double)ns + 1e-3 * (double)nt + 0.6 * (double)ns / (double)nt;
+}
+
+bool far_possible(int mode, int64_t ns, int64_t nt) {
+    for (int op = S2D_OP_SLP; op <= S2D_OP_SLP_TRACTION; ++op)
+        if (far_worth(op, mode, ns, nt, 4, false)) return true;
+    return false;
 }
 
 hipError_t far_setup(int op, const FarLayout &L, const s2d_curves *s, const s2d_targets *t, void *ws,

@@ -21,7 +21,12 @@ FarLayout far_layout(int op, int64_t ns, int64_t nt, bool on_curve);
 
 // Whether the far-field sum is the faster route for these sizes and images;
 // reuse: one set-up serves several densities.
-bool far_worth(int mode, int64_t ns, int64_t nt, int n_img, bool reuse);
+bool far_worth(int op, int mode, int64_t ns, int64_t nt, int n_img, bool reuse);
+
+// Whether it is for some operator and number of images: workspaces are sized
+// alike for all (the direct sum's cost is highest for four images, counted as
+// three ungrouped ones).
+bool far_possible(int mode, int64_t ns, int64_t nt);
 
 // Orders sources and targets along a space-filling curve and boxes their
 // tiles; with Kress's tables when the single layer's targets sit on curves.

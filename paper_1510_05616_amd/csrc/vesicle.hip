@@ -1180,7 +1180,7 @@ StepLayout step_layout(int64_t n, int32_t nc, const ves_step_params *p) {
     }
     L.need = o;
     L.far = o;
-    if (far_worth(S2D_FP64, n, n, p->img_hi - p->img_lo + 1, true)) {
+    if (far_worth(S2D_OP_SLP, S2D_FP64, n, n, p->img_hi - p->img_lo + 1, true)) {
         L.far_bytes = far_layout(S2D_OP_SLP, n, n, true).total;
         o += al256(L.far_bytes);
     }

@@ -362,3 +362,49 @@ def test_outliers_keep_the_rest_far(where):
             print(f"{where}: far against direct {e:.1e}", flush=True)
             assert e < 1e-12
     assert t < 2 * plain
+
+
+# The route taken with the queried workspace is no slower than the direct sums
+# of the same call (a workspace that holds no more than those), by a bar that
+# leaves the clock a tenth: few targets against many sources, and pressures,
+# whose direct terms are the cheapest, on both sides of the line.
+@pytest.mark.parametrize("op,mode,ns,nt", [(0, 1, 256000, 1100), (0, 1, 2880, 30000), (2, 0, 2880, 30000),
+                                           (4, 0, 2400, 30000), (2, 1, 9984, 9000), (2, 0, 20160, 20000),
+                                           (1, 0, 9984, 14000)])
+def test_route_is_the_faster_one(op, mode, ns, nt):
+    import torch
+    import types
+    import paper_1510_05616_amd as s2d
+    s2d.stokes2d_init(0)
+    x, y, off, d = _lattice(ns // 96, (96,), 5)
+    rng = np.random.default_rng(2)
+    c = types.SimpleNamespace(x=x, y=y, nx=np.cos(x), ny=np.sin(x), w=np.full(len(x), 1e-2), kappa=None,
+                              fx=rng.standard_normal(len(x)), fy=rng.standard_normal(len(x)), curve_off=off)
+    src, trg = s2d.Curves(c), s2d.Targets(rng.uniform(0, d, nt), rng.uniform(-1.2, 1.2, nt))
+    u = torch.zeros(4, nt, dtype=torch.float64, device="cuda")
+    full = s2d.stokes2d_workspace_size(op, mode, src, trg)
+
+    def call(ws):
+        if op == 0:
+            s2d.stokes2d_slp_eval(mode, src, trg, d, -1, 1, 1.0, u[0], u[1], 0, ws)
+        elif op == 1:
+            s2d.stokes2d_dlp_eval(mode, src, trg, d, -1, 1, u[0], u[1], 0, ws)
+        elif op == 2:
+            s2d.stokes2d_slp_pressure_eval(mode, src, trg, d, -1, 1, u[0], 0, ws)
+        else:
+            s2d.stokes2d_slp_traction_eval(mode, src, trg, u[2], u[3], d, -1, 1, u[0], u[1], 0, ws)
+
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    # the least workspace that the call takes is the direct plan's
+    lo, hi = 256, full
+    while hi - lo > 4096:
+        mid = (lo + hi) // 2 // 256 * 256
+        try:
+            call(ws[:mid])
+            hi = mid
+        except s2d.S2DError:
+            lo = mid
+    direct = min(_time(lambda: call(ws[:hi])) for _ in range(2))
+    t = min(_time(lambda: call(ws)) for _ in range(2))
+    print(f"operator {op} mode {mode}, {ns} x {nt}: {t:.3f} ms, direct {direct:.3f}", flush=True)
+    assert t < 1.1 * direct
