@@ -76,7 +76,8 @@ S2D_API int ves_measure(int64_t n_nodes, int32_t n_curves, const int32_t *curve_
  * right-hand side and every residual b - A z in FP64, each correction
  * A dz = r by GMRES with FP32C sums to a relative 1e-4 (FP32C sums alone
  * stall GMRES near 1e-5: D_s^4 amplifies their rounding); they reach the
- * same tolerance as S2D_FP64. */
+ * same tolerance as S2D_FP64.  On the far-field route, whose sums are FP64
+ * anyway, they solve as in S2D_FP64, with the same result. */
 typedef struct ves_step_params {
     int32_t mode;
     double dt, kappa_b, mu;

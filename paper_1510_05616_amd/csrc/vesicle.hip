@@ -1628,8 +1628,8 @@ int krylov(StepCtx &C, const double *rhs, double rhs_norm, double *x, double tol
 constexpr double kInnerTol = 1e-4;
 constexpr int kMaxRefine = 30;
 
-// The step system A z = b.  FP64: GMRES with FP64 single-layer sums.
-// FP32C: iterative refinement; b and every residual b - A z in FP64, each
+// The step system A z = b.  FP64, and either mode on the far-field route: GMRES
+// with FP64 single-layer sums.  FP32C by direct sums: iterative refinement; b and every residual b - A z in FP64, each
 // correction A dz = r solved by GMRES with FP32C sums to a relative
 // kInnerTol (or to what the tolerance still asks), z += dz.
 // The solve from z = 0, or (warm) from the z passed in: then GMRES works on
@@ -1652,9 +1652,13 @@ int gmres_run(StepCtx &C, double *z, bool warm, int32_t *iters_out, double *res_
         S2D_TRY(dots(C, 1, r, r, &rr2));
         rnorm = std::sqrt(rr2);
     }
-    if (C.p->mode == S2D_FP64 && !warm) {
+    // FP32C: refinement around cheaper sums; the far-field ones are FP64 in
+    // either mode and need none (1,000 curves of 96 nodes: 25 sums with, 20
+    // without)
+    const bool f64 = C.p->mode == S2D_FP64 || C.far;
+    if (f64 && !warm) {
         S2D_TRY(krylov(C, b, bnorm, z, C.p->tol, S2D_FP64, C.p->max_iter, iters, rel));
-    } else if (C.p->mode == S2D_FP64) {
+    } else if (f64) {
         rel = bnorm == 0.0 ? 0.0 : rnorm / bnorm;
         if (bnorm > 0.0 && std::isfinite(rnorm) && rel > C.p->tol) {
             double irel = 0.0;
