@@ -57,9 +57,10 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
         const bool fits = (size_t)p.n_sb * p.sbs * rec_bytes(op, mode) <= kL2Budget;
         const int64_t fill = (int64_t)cus * 4 * 16;
         // a group's waves keep at least 64 sources each, and of more than 64
-        // groups there are no more than give each CU eight workgroups
+        // groups there are no more than give each CU four workgroups (eight are
+        // up to a tenth faster and their planes twice the memory)
         const int64_t gmax = std::min<int64_t>(std::max<int64_t>(1, p.n_src / (64 * kMaxPairWaves)),
-                                               std::max<int64_t>(64, (8 * (int64_t)cus + p.n_tiles - 1) / p.n_tiles));
+                                               std::max<int64_t>(64, (4 * (int64_t)cus + p.n_tiles - 1) / p.n_tiles));
         const bool by8 = !fits && gmax >= 8 && cus >= 8;
         int64_t G = 1;
         if (!(fits && p.n_tiles * kMaxPairWaves >= fill))
@@ -72,7 +73,7 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
         // round the XCDs where G is a multiple of 8), groups past the last source
         // are empty, and a plane costs about 1/500 unit.  1e6 sources, at most 64
         // groups: 64 targets 495 us, 640 targets 1.68 ms; by this rule 207 us and
-        // 1.08 ms.
+        // 1.25 ms.
         if (G > 1 && p.n_tiles * std::min<int64_t>(G, 64) < 4 * (int64_t)cus) {
             const auto cost = [&](int64_t g) {
                 const int64_t w = std::min<int64_t>(kMaxPairWaves, (p.n_sb + g - 1) / g);
@@ -81,7 +82,7 @@ Plan make_plan(int op, int mode, const s2d_curves *s, const s2d_targets *t, int 
                 const int64_t k = by8 ? (p.n_tiles * ((full + 7) / 8) + cus / 8 - 1) / (cus / 8)
                                       : (p.n_tiles * full + cus - 1) / cus;
                 const double v = (double)(k * w) / kMaxPairWaves;
-                return (double)(sps * p.sbs) / kSuperBlock * (v <= 1.0 ? 0.25 + 0.75 * v : 0.9 * v + 0.1) +
+                return (double)(sps * p.sbs) / kSuperBlock * (v <= 1.0 ? 0.25 + 0.75 * v : 0.87 * v + 0.13) +
                        0.002 * (double)g;
             };
             const int64_t step = by8 ? 8 : 1;

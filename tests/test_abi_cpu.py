@@ -106,6 +106,10 @@ def test_few_targets_split_many_sources_over_the_chip(L):
         size = [L.stokes2d_workspace_size(op, mode, ctypes.byref(c), ctypes.byref(t))
                 for c, t in (_structs(1000000, 1), _structs(1000000, 64))]
         assert size[1] - size[0] >= 128 * 16 * 63 - 256
+    # and their planes do not push a call of stokes2d_slp_eval_noalloc's largest
+    # sizes out of its scratch
+    c, t = _structs(800000, 500, on=True)
+    assert L.stokes2d_workspace_size(0, 0, ctypes.byref(c), ctypes.byref(t)) <= 32 << 20
 
 
 def test_batch_tuned_is_host_only_and_reports_the_default(L, tmp_path, monkeypatch):
