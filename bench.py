@@ -439,9 +439,8 @@ def step_section(prob, steps=3, dt=1e-4, kappa_b=1.0):
     layer over images -1..1, d = 64 pi; no wall response): the step system
     solved by GMRES (right-preconditioned by the factored per-vesicle self
     blocks), update, area correction, reparameterization; solved to 1e-10
-    with FP64 single-layer sums, and by iterative refinement with FP32C sums
-    (FP64 right-hand side and residuals, FP32C corrections).  The oracle
-    times one step of 4 of the vesicles on the host."""
+    in both modes, which solve alike on the far-field route (FP64 sums).  The
+    oracle times one step of 4 of the vesicles on the host."""
     import torch
     import oracle
     import paper_1510_05616_amd as s2d
@@ -485,10 +484,8 @@ def step_section(prob, steps=3, dt=1e-4, kappa_b=1.0):
             log(f"step {name}: {ms:.1f} ms per time step, GMRES {its}, {kn / steps:.1f} single-layer sums per "
                 f"step ({kms / steps:.1f} ms, {avg:.2f} ms each)")
         else:
-            # FP64 right-hand side and residuals, FP32C corrections: the
-            # launches are of both precisions
             what = ("close evaluation of %d near pairs (8x), " % out["near_pairs"]) if near else ""
-            log(f"step {name} ({what}FP32C corrections, FP64 residuals): {ms:.1f} ms per time step, GMRES {its}, "
+            log(f"step {name} ({what}FP64 far-field sums): {ms:.1f} ms per time step, GMRES {its}, "
                 f"{kn / steps:.1f} single-layer sums per step ({kms / steps:.1f} ms)")
     # the oracle: one step of 4 vesicles (dense solve of the 1,152-unknown system)
     off = ves.curve_off
@@ -571,9 +568,8 @@ def channel_section(prob, steps=2, dt=1e-4, kappa_b=1.0, p_drive=10.0, n_proxy=1
     ves = prob.ves
     out = {"workload": f"Algorithm 1 in the 128k channel: walls at 2 x {wall_nodes:,} nodes, K = 32, M = 128 (cell factored "
                        "once), 1,000 vesicles x 96 nodes, dt = %g, kappa_B = %g, p_drive = %g per period; "
-                       "response in FP64, the step solved to 1e-10 with FP64 sums (f64) or by FP32C corrections "
-                       "with FP64 residuals (f32; f32_near: with close evaluation of near vesicle pairs, 8x "
-                       "upsampled, band 5 spacings)" % (dt, kappa_b, p_drive),
+                       "response in FP64, the step solved to 1e-10 by FP64 far-field sums in either mode (f32_near: "
+                       "with close evaluation of near vesicle pairs, 8x upsampled, band 5 spacings)" % (dt, kappa_b, p_drive),
            "cell_factor_s": t_factor}
     for name, mode, near in (("f64", 0, 0), ("f32", 1, 0), ("f32_near", 1, 1)):
         V = pv.Vesicles(ves.x, ves.y, ves.curve_off)

@@ -438,7 +438,7 @@ CellLayout cell_layout(const CellArgs &g) {
     L.E = off;    off = al(off + (size_t)r * 8);
     L.P = off;    off = al(off + (size_t)nc * mr * 8);
     L.y = off;    off = al(off + (size_t)n * 8);
-    L.rr = off;   off = al(off + (size_t)mr * 8);
+    L.rr = off;   off = al(off + (size_t)mr * 8);         // not in use; the total is known to callers
     L.ipiv = off; off = al(off + (size_t)n * 4);
     L.perm = off; off = al(off + (size_t)n * 4);
     L.Tf = off;   off = al(off + (size_t)n * kTileW * 8);

@@ -29,8 +29,10 @@
 //
 // Acceptance.  A source node of radius r_s and a target tile of radius r_t at
 // distance D are far when r_s < th (D - r_t) and r_t < th (D - r_s), th = 0.32:
-// both truncations are below 0.32^31 = 5e-16 relative to the sum of the terms'
-// magnitudes.  Against the direct sums, with the density on one node, errors
+// the series' first dropped powers are 0.32^31 = 5e-16 (0.32^32 for a source
+// node's), times the factors k that psi's and the derivatives' terms carry and a
+// geometric tail of 1.5: an estimate of about 1e-15 of the terms' magnitudes in
+// the worst place, not a bound.  Against the direct sums, with the density on one node, errors
 // over |term| stay at rounding (largest 4.0e-15 for velocities, 6.1e-15 for
 // pressures and traction) for th = 0.28 and 0.32 alike, double at 0.34 and are
 // 2e-13 at 0.37; the channel step below takes 0.93, 0.87, 0.84 and 0.81 ms.
@@ -43,11 +45,11 @@
 // those far outside cost their own tiles term by term and nothing else.
 //
 // Measured (MI355X): single layer of 1,000 vesicles x 96 nodes at their own
-// nodes, images -1..1: 15.1 ms direct; here 0.18 ms near part, 0.13 ms far
-// part, 0.05 ms own-curve and source expansions, 0.1 ms set-up (once per
-// geometry).  Walls of 2 x 16,000 nodes refined 8 times at 20,000 near-wall
-// points: 8.6 ms direct; near and far parts of both sums 0.29 ms, set-up
-// 0.1 ms each.  Both parts are bound by FP64 issue and the latency of its
+// nodes (the channel's three rows, 64 pi long), images -1..1: 15.1 ms direct;
+// here 0.23 ms near part, 0.17 ms far part, 0.06 ms own curves and source
+// expansions, 0.1 ms set-up (once per geometry).  Walls of 2 x 16,000 nodes
+// refined 8 times at 20,000 near-wall points: 8.6 ms direct; near and far parts
+// of both sums 0.33 ms, set-up 0.1 ms each.  Both parts are bound by FP64 issue and the latency of its
 // dependent chains at 3-5 waves per SIMD.
 //
 // Every sum runs in a fixed order (stable sort, ballots, no floating-point

@@ -24,8 +24,9 @@ namespace s2d {
 // targets at 64 sources, workgroups of a wave, 173 us (228 with both in one
 // kernel).
 template <int OP, int PREC, int NI, bool OWN, bool SHORT>
-// register allocation held to 8 waves per SIMD (64 VGPRs): every pair kernel
-// fits without spills, and two 16-wave workgroups then share a CU
+// register allocation held to 8 waves per SIMD (64 VGPRs), so that two 16-wave
+// workgroups share a CU: every pair kernel fits (the FP64 single layer of three
+// images with OWN and SHORT keeps one register in scratch)
 __global__ __launch_bounds__(kMaxPairWaves * kWave) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void pair_kernel(PairArgs a, FinalArgs f) {
     constexpr bool kTab = OP == S2D_OP_SLP && (PREC == S2D_FP64 || OWN);

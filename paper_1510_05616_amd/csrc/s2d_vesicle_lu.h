@@ -7,7 +7,7 @@
 namespace s2d {
 
 constexpr int kTri = 32;         // rows of an inverted diagonal triangle
-constexpr int kLuMax = 512;      // largest block, a thread per row
+constexpr int kLuMax = 512;      // largest block, up to two rows per thread
 
 // nc column-major n x n matrices at Pm, factored in place for pc_solve; perm
 // [nc][n]: row r of the factors is row perm[r] of the matrix; info [nc]: the

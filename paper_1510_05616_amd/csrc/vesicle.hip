@@ -1064,8 +1064,8 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct StepLayout {
     size_t geo, dens, tgt, b, r, w, dz, ri, V, z, part, dots, slp, slp_bytes;
     // preconditioner (precond != 0): Kress table, per-curve D_s, D_s^2, D_s^4,
-    // S_cc, B, S_cc B, P (LU with inverted diagonal triangles), pivots (then the
-    // row permutation), info, two [3n] vectors
+    // S_cc, B's last columns, P (LU with inverted diagonal triangles), pivots
+    // (then the row permutation), info, two [3n] vectors
     size_t T, Dm, D2, D4, Sm, Bm, Pm, ipiv, info, t1, t2;
     // close evaluation (near != 0): curve boxes, per-node counts and list
     // offsets, the near pairs (node, curve, shifted coordinates, corrections),
@@ -1508,7 +1508,7 @@ int pc_build(StepCtx &C) {
     e = hipGetLastError();
     if (e != hipSuccess) return hipf(e, "preconditioner fill");
     rocblas_int *ipiv = (rocblas_int *)(b + C.L.ipiv), *info = (rocblas_int *)(b + C.L.info);
-    // blocks of more rows than a workgroup has threads: the library's
+    // blocks of more than kLuMax rows: the library's
     const bool own = 3 * Nm <= kLuMax;
     if (own) {
         e = pc_lu_launch(3 * Nm, nc, a.Pm, ipiv, info, C.st);

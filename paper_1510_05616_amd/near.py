@@ -224,8 +224,9 @@ def near_wall_correct_eval(walls: Curves, trg: Targets, d, img_lo, img_hi, upsam
                            method=S2D_NEAR_UPSAMPLE, trg_curve=None, blob=None, threshold=0.0, used_fallback=None,
                            ws=None, stream=None, curve_tol=None) -> None:
     """du, dv (device float64, [trg.n]) = (or +=) D_P - D_1 of the walls:
-    by the refined walls (UPSAMPLE), the learned route (MLP) or per target
-    (AUTO; trg_curve names each target's wall)."""
+    by the refined walls (UPSAMPLE: exact, and the fastest on the walls
+    measured), the learned route (MLP) or per target (AUTO; trg_curve names each
+    target's wall)."""
     L = _bind()
     cs, ts = walls.struct(), trg.struct()
     if ws is None:
